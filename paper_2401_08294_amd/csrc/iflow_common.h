@@ -271,6 +271,7 @@ hipError_t launch_qgemm_small_fused(int format, const void *packed, int64_t rows
                                     const uint16_t *aux, float eps, const uint16_t *residual, uint16_t *Y, hipStream_t s);
 hipError_t launch_qgemm_small(int format, const void *packed, int64_t rows, int64_t cols,
                               const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s);
+constexpr int64_t QGEMM_MFMA_MAX_COLS = 1 << 22;   // byte offsets inside a tile (up to 256 rows of activations) are 32-bit
 hipError_t launch_qgemm_mfma(int format, const void *packed, int64_t rows, int64_t cols,
                              const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s);
 hipError_t launch_qgemv_rows(int format, const void *packed, int64_t rows, int64_t cols, const uint16_t *x, int batch, uint16_t *y,

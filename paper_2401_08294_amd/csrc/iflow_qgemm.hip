@@ -1,287 +1,524 @@
-// Dequantize-and-multiply on the matrix cores for batches large enough to make the product a dense
-// contraction: Y[b][n] = sum_k w'[n][k] X[b][k].
+// Dequantize-and-multiply on the matrix cores for 17 and more activation vectors: Y[b][n] = sum_k w'[n][k] X[b][k].
 //
-// A workgroup of four wavefronts owns a 128 (batch; 64 for batches up to 64) x 64 (weight rows) tile of Y and walks along K in
-// chunks of 64 columns, i.e. one quantization block per weight row (two for the 32-wide formats).  Per chunk
-// it (1) copies the 128 x 64 fp16 activation tile into LDS, (2) decodes its 64 packed blocks into fp16
-// weights in LDS - Eq.5 and Eq.2 of the paper, with the same single-rounded fp16 fused multiply-add as the
-// stand-alone dequantizer, so the tile holds exactly the values iflow_dequant would produce - and (3) runs
-// v_mfma_f32_32x32x16_f16 from LDS, fp32 accumulation.  Each wavefront owns a 64 x 32 part of the tile (two
-// 32 x 32 output tiles).  Rows of the LDS tiles are padded to 72 halves (144 bytes) so that 16-byte operand reads
-// of neighbouring rows fall into different banks.
+// A wavefront owns RT x 32 weight rows and MB x 32 vectors and walks along K in chunks of 64 columns (one quantization block per
+// weight row, two for the 32-wide formats) with v_mfma_f32_32x32x16_f16.  It decodes its weights - Eq.5 and Eq.2 of the paper with the
+// single-rounded fp16 fused multiply-add, exactly the values iflow_dequant produces - from packed bytes straight into operand
+// registers: nobody else needs these rows, so decoded weights never go through LDS.  The activations do: WR wavefronts side by side
+// along the rows share them.  WK such groups split K among them, where rows x vectors alone give too few wavefronts.
+//   - Everything comes from memory by copies straight into LDS, several steps ahead, and is waited for by count: no registers are
+//     held by loads in flight, and a step's matrix instructions never wait for memory (before, one 64-column chunk took 530 ns for
+//     256 cycles of matrix work).
+//   - The operands of a k-step of 16 columns are read and decoded while the matrix instructions of the k-step before run.
+//   - Which lane holds which k of a chunk is free as long as both operands agree: lane half h takes columns 32 h .. 32 h + 31,
+//     so that a lane's weights are 32 consecutive ones of one row.
+// What bounds it: for large batches the power limit (a loop of nothing but these matrix instructions on random data runs at 1.5 to 1.8
+// PFLOP/s, 1.5 to 1.8 GHz) and the decode next to it, which is why the largest tile has 256 vectors per decoded weight; for small ones the
+// activations, which every workgroup reads from L2 (1 MB for 128 vectors of 4096 columns, about 100 KB of LDS to hold what is on its way).
+// Measured (3.5-bit; before: 128 x 64 tiles with both operands decoded or copied into LDS): 11008 x 4096, 512 vectors 84.9 -> 59 us (780
+// TFLOP/s), 2048 vectors 354 -> 211 us; 4096 x 4096, 64 vectors 23.8 -> 8.9 us.
 #include "iflow_common.h"
 
 namespace iflow {
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int GM_BN = 64, GM_BK = 64, GM_LD = 72;   // weight rows and columns per tile (batch rows: a template parameter); LDS row pitch in halves (144 bytes)
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pack_h2(half2_t v) { return as_u32(v); }
 
-// Raw material for sixteen consecutive weights (k = 16*qd .. 16*qd+15 of a 64-column chunk) of one row:
-// the code words and the block header bits this thread can see.
-struct Raw16 { uint32_t d[4]; uint32_t hdr; };
-
-// (bit-plane formats: d[0..1] = the low plane's 8 or 4 bytes, d[2] = the high plane's word; `plane_b` = where the high
-// plane starts in the packed matrix)
-template <int F>
-__device__ __forceinline__ void load16(const uint8_t *packed, int64_t header_offset, int64_t plane_b, int64_t row, int nbk,
-                                       int kb /* 64-column chunk */, int qd, Raw16 &r)
+// N (16 or 4) bytes per lane from memory straight into LDS: lane l's to lds + N l.  Written out because the compiler, which cannot
+// tell which LDS reads such a copy may overlap, puts a wait for all of them in front of the next read; the waits are placed by hand.
+// (m0, the copy's LDS address, is a reserved register: it cannot be named as clobbered, and nothing else in these kernels uses it.)
+template <int N>
+__device__ __forceinline__ void copy_to_lds(const uint8_t *base /* wavefront-uniform */, uint32_t offset, uint32_t lds)
 {
-    typedef Fmt<F> T;
-    if constexpr (kind_has_planes(T::kind)) {
-        constexpr int WA = Planes<T::kind>::WA, WB = Planes<T::kind>::WB;
-        const int64_t cols = (int64_t)nbk * T::block;
-        const int k0 = kb * 64 + qd * 16;
-        r.hdr = *reinterpret_cast<const uint32_t *>(packed + header_offset + (row * nbk + k0 / T::block) * 4);
-        r.d[1] = 0; r.d[2] = 0; r.d[3] = 0;
-        if constexpr (WA == 4) {
-            const uint2 two = *reinterpret_cast<const uint2 *>(packed + row * (cols / 2) + k0 / 2);
-            r.d[0] = two.x; r.d[1] = two.y;
-        } else {
-            r.d[0] = *reinterpret_cast<const uint32_t *>(packed + row * (cols / 4) + k0 / 4);
-        }
-        if constexpr (WB == 2) r.d[2] = *reinterpret_cast<const uint32_t *>(packed + plane_b + row * (cols / 4) + k0 / 4);
-        if constexpr (WB == 1) r.d[2] = *reinterpret_cast<const uint32_t *>(packed + plane_b + row * (cols / 8) + (k0 / 32) * 4);
-    } else if (T::kind == KIND_Q3H) {
-        // words 2qd, 2qd+1 of the block: plane qd/2, 8 bytes at offset (qd%2)*8 inside the block's 16 bytes
-        const int t = kb >> 6, jin = kb & 63;
-        const int n_t = min(64, nbk - (t << 6));
-        const uint8_t *p = packed + row * (int64_t)nbk * 32 + (int64_t)t * 2048 + (qd >> 1) * n_t * 16 + jin * 16 + (qd & 1) * 8;
-        const uint2 two = *reinterpret_cast<const uint2 *>(p);
-        r.d[0] = two.x; r.d[1] = two.y; r.d[2] = 0; r.d[3] = 0; r.hdr = 0;
-    } else {
-        const int k0 = kb * 64 + qd * 16;
-        r.hdr = *reinterpret_cast<const uint32_t *>(packed + header_offset + (row * nbk + k0 / T::block) * 4);
-        if (T::kind == KIND_Q4) {
-            const uint2 two = *reinterpret_cast<const uint2 *>(packed + row * (int64_t)(nbk * T::block / 2) + k0 / 2);
-            r.d[0] = two.x; r.d[1] = two.y; r.d[2] = 0; r.d[3] = 0;
-        } else {
-            const uint4 four = *reinterpret_cast<const uint4 *>(packed + row * (int64_t)(nbk * T::block) + k0);
-            r.d[0] = four.x; r.d[1] = four.y; r.d[2] = four.z; r.d[3] = four.w;
-        }
-    }
+    if constexpr (N == 16)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory");
 }
 
-// Eq.5 and Eq.2: the sixteen weights as eight fp16 pairs in natural order, bit-identical to iflow_dequant.
-template <int F>
-__device__ __forceinline__ void decode16(const Raw16 &r, int qd, uint32_t (&out)[8])
-{
+// ---- packed weights of 32 rows: memory -> LDS -> registers -----------------------------------------------------------------
+// A 64-column chunk of a row is, per format, one to three runs of consecutive bytes ("parts": the low or only plane's codes, the high
+// plane's, the headers; the 3.5-bit format: its two planes).  Parts of G consecutive chunks of a row are consecutive too, so a
+// wavefront fetches 32 rows x G chunks at once, with neighbouring lanes on neighbouring pieces of a row: segments of 64 bytes and
+// more where G is 4, 2 or 1 by the format's width.  (One 16-byte piece per row and instruction - 64 cache lines each - cost a fifth of
+// the whole kernel.)
+template <int F> struct Parts {
     typedef Fmt<F> T;
-    if constexpr (kind_has_planes(T::kind)) {
-        constexpr int WA = Planes<T::kind>::WA, WB = Planes<T::kind>::WB;
-        const half2_t so = as_h2(r.hdr);
-        const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-        half2_t lo[8], hi[8];
-        plane_fields16<WA>(&r.d[0], 0, lo);
-        if constexpr (WB > 0) plane_fields16<WB>(&r.d[2], qd & 1, hi);                 // a 1-bit word serves two quarters
-        const half2_t up = {(half_t)(float)(1 << WA), (half_t)(float)(1 << WA)};
+    static constexpr bool q3h = T::kind == KIND_Q3H, planes = kind_has_planes(T::kind);
+    static constexpr int WA = T::kind == KIND_Q8 ? 8 : planes ? Planes<T::kind>::WA : 4, WB = planes ? Planes<T::kind>::WB : 0;   // bits
+    static constexpr int A = q3h ? 16 : 8 * WA, B = q3h ? 16 : 8 * WB, H = q3h ? 0 : 256 / T::block;   // bytes of a row's chunk per part
+    static constexpr int G = T::kind == KIND_Q8 ? 1 : q3h || WA == 2 ? 4 : 2;
+    static constexpr int PB = B == 8 ? 4 : 16;                 // bytes per lane and piece (8 bytes a chunk: rows are only 8-byte aligned)
+    static constexpr int NA = 32 * G * A / 1024, NB = 32 * G * B / (64 * PB), NH = (32 * G * H + 255) / 256;   // pieces (instructions) per part
+    static constexpr int LA = 0, LB = 32 * G * A, LH = LB + 32 * G * B, BYTES = LH + 256 * NH;         // places in LDS, total
+    static constexpr int BUFFERS = G == 1 ? 3 : 2;             // groups of G chunks in LDS: the one in use and those on their way
+};
+
+// One lane's 32 weights of a row: half h of a chunk.
+template <int F> struct RawHalf { uint32_t a[Parts<F>::WA], b[Parts<F>::WB ? Parts<F>::WB : 1], hdr; };
+
+template <int F> struct WeightRows {
+    typedef Fmt<F> T;
+    typedef Parts<F> P;
+    static constexpr int G = P::G;
+    const uint8_t *a, *b, *hdr;                                // row r0's start in each part (wavefront-uniform)
+    uint32_t ra, rb, rh;                                       // bytes of a row in each part
+    int last;                                                  // rows past the matrix's end: row r0 + last again
+    int nchunks, lane;
+    __device__ __forceinline__ void open(const uint8_t *packed, int rows, int cols, int64_t header_offset, int r0, int l)
+    {
+        ra = (uint32_t)cols / 64u * (P::q3h ? 32 : P::A); rb = (uint32_t)cols / 64u * P::B; rh = (uint32_t)cols / 64u * P::H;
+        a = packed + (int64_t)r0 * ra;
+        b = packed + (int64_t)rows * ra + (int64_t)r0 * rb;
+        hdr = packed + header_offset + (int64_t)r0 * rh;
+        last = rows - 1 - r0; nchunks = cols / 64; lane = l;
+    }
+    // piece i of a part with `per` bytes a chunk, `each` bytes a lane: the lane's row and byte in that row's G chunks.  The 16-byte
+    // slots of a row are permuted by the row, so that 16-byte reads of neighbouring rows' same chunk fall into different banks.
+    template <int PER, int EACH> __device__ __forceinline__ void place(int i, int &row, int &byte) const
+    {
+        constexpr int LANES = G * PER / EACH;                  // lanes per row
+        row = ((i * 64 + lane) / LANES) & 31;                  // (a piece of 32 rows x 4 bytes fills half the lanes: the rest repeat)
+        const int slot = lane % LANES;
+        byte = (EACH == 16 ? slot ^ spread<LANES>(row) : slot) * EACH;
+    }
+    template <int LANES> static __device__ __forceinline__ int spread(int row)
+    {
+        return row / (16 / LANES) & (LANES - 1);               // 256 bytes, one turn of the banks, hold 16 / LANES rows
+    }
+    // chunks kc .. kc + G - 1 (kc a multiple of G, wavefront-uniform) of rows r0 + 32 t .. + 31 -> LDS; chunks past the end: the
+    // row's last bytes again
+    __device__ __forceinline__ void request(int t, int kc, uint32_t lds) const
+    {
+        int row, byte;
+        if constexpr (P::q3h) {
+            const int strip = kc >> 6, n_t = min(64, nchunks - (strip << 6)), in = (kc & 63) * 16;
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            half2_t level = lo[m];
-            if constexpr (WB > 0) level = __builtin_elementwise_fma(hi[m], up, lo[m]);   // exact: an integer below 64
-            out[m] = pack_h2(__builtin_elementwise_fma(level, s2, o2));                  // Eq.2, one rounding
+            for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+                for (int i = 0; i < P::NA; ++i) {
+                    place<16, 16>(i, row, byte);
+                    const int at = min(in + byte, (n_t - 1) * 16);
+                    copy_to_lds<16>(a + strip * 2048 + pl * (n_t * 16), (uint32_t)min(32 * t + row, last) * ra + at, lds + (pl ? P::LB : P::LA) + 1024 * i);
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < P::NA; ++i) {
+                place<P::A, 16>(i, row, byte);
+                copy_to_lds<16>(a, (uint32_t)min(32 * t + row, last) * ra + min(kc * P::A + byte, (int)ra - 16), lds + P::LA + 1024 * i);
+            }
+            if constexpr (P::B > 0) {
+#pragma unroll
+                for (int i = 0; i < P::NB; ++i) {
+                    place<P::B, P::PB>(i, row, byte);
+                    copy_to_lds<P::PB>(b, (uint32_t)min(32 * t + row, last) * rb + min(kc * P::B + byte, (int)rb - P::PB), lds + P::LB + 64 * P::PB * i);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < P::NH; ++i) {
+                place<P::H, 4>(i, row, byte);
+                copy_to_lds<4>(hdr, (uint32_t)min(32 * t + row, last) * rh + min(kc * P::H + byte, (int)rh - 4), lds + P::LH + 256 * i);
+            }
         }
-    } else if (T::kind == KIND_Q3H) {
-        // header: word i carries scale bits 2i,2i+1 at 14-15 and offset bits at 30-31; the four threads of a
-        // block sit in one quad of lanes and OR their parts together
-        uint32_t h = 0;
+    }
+    template <int PER, int LANE_BYTES> static __device__ __forceinline__ const uint8_t *slot_of(const uint8_t *lds, int row, int byte)
+    {
+        constexpr int LANES = G * PER / LANE_BYTES;
+        if constexpr (LANE_BYTES == 16) return lds + row * (G * PER) + (((byte >> 4) ^ spread<LANES>(row)) << 4) + (byte & 15);
+        else return lds + row * (G * PER) + byte;
+    }
+    // ... and half h of chunk c of the group, row `row` of the 32, from there into registers
+    static __device__ __forceinline__ void read(const uint8_t *lds, int row, int c, int h, RawHalf<F> &r)
+    {
+        if constexpr (P::q3h) {
+            const u32x4_t v = *reinterpret_cast<const u32x4_t *>(slot_of<16, 16>(lds + (h ? P::LB : P::LA), row, c * 16));
+            r.a[0] = v.x; r.a[1] = v.y; r.a[2] = v.z; r.a[3] = v.w;
+        } else if constexpr (P::WA == 2) {
+            const u32x2_t v = *reinterpret_cast<const u32x2_t *>(slot_of<P::A, 16>(lds + P::LA, row, c * 16 + h * 8));
+            r.a[0] = v.x; r.a[1] = v.y;
+        } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int wi = 2 * qd + i;
-            h |= ((r.d[i] >> 14) & 3u) << (2 * wi) | ((r.d[i] >> 30) & 3u) << (16 + 2 * wi);
+            for (int i = 0; i < P::WA / 4; ++i) {
+                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(slot_of<P::A, 16>(lds + P::LA, row, c * P::A + h * (P::A / 2) + i * 16));
+                r.a[4 * i] = v.x; r.a[4 * i + 1] = v.y; r.a[4 * i + 2] = v.z; r.a[4 * i + 3] = v.w;
+            }
         }
-        h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0xB1, 0xF, 0xF, true);
-        h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x4E, 0xF, 0xF, true);
-        const half2_t so = as_h2(h);
-        const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-        const half2_t m1025 = {(half_t)-1025.0f, (half_t)-1025.0f}, m1024 = {(half_t)-1024.0f, (half_t)-1024.0f};
-        const half2_t m11 = {(half_t)-11.0f, (half_t)-11.0f};
+        if constexpr (!P::q3h && P::WB == 2) {
+            const u32x2_t v = *reinterpret_cast<const u32x2_t *>(slot_of<P::B, 16>(lds + P::LB, row, c * 16 + h * 8));
+            r.b[0] = v.x; r.b[1] = v.y;
+        }
+        if constexpr (P::WB == 1) r.b[0] = *reinterpret_cast<const uint32_t *>(slot_of<P::B, 4>(lds + P::LB, row, c * 8 + h * 4));
+        if constexpr (P::H > 0) r.hdr = *reinterpret_cast<const uint32_t *>(slot_of<P::H, 4>(lds + P::LH, row, c * P::H + (T::block == 32 ? h * 4 : 0)));
+    }
+};
+
+// Constants the decoders OR and AND with, held in registers: v_and_or_b32 takes no literals, and with literals the compiler makes two
+// instructions of each.  (magic[p]: the fp16 pair whose mantissa bit p counts 1, for the fields that start at bit p.)
+struct DecodeConstants {
+    uint32_t at0, at4, at2, at6;
+    __device__ __forceinline__ void open()
+    {
+        at0 = 0x64006400u; at4 = 0x54005400u; at2 = 0x5C005C00u; at6 = 0x4C004C00u;
+        asm volatile("" : "+v"(at0), "+v"(at4), "+v"(at2), "+v"(at6));
+    }
+};
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t with)
+{
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(mask), "v"(with));
+    return r;
+}
+// Weights 2p, 2p + 1 of the eight whose low-plane bits sit in the low WA * 4 bits of both halves of `lo` (pair p at bit WA * p; WA = 4: two
+// pairs per byte, the second two in `lo8` = lo >> 8) and whose high-plane bits sit in the low WB * 4 bits of both halves of `hi`: the
+// level's bits next to each other in the mantissa of an fp16 number, minus that number's own value.
+template <int WA, int WB>
+__device__ __forceinline__ half2_t plane_level(uint32_t lo, uint32_t lo8, uint32_t hi, int p, const DecodeConstants &k)
+{
+    const int at = WA == 4 ? 4 * (p & 1) : 2 * p;              // where the level's lowest bit lies
+    const uint32_t magic = at == 0 ? k.at0 : at == 2 ? k.at2 : at == 4 ? k.at4 : k.at6;
+    uint32_t v = and_or(WA == 4 && p >= 2 ? lo8 : lo, (((1u << WA) - 1u) << at) * 0x00010001u, magic);
+    if constexpr (WB > 0) {
+        const int shift = at + WA - WB * p;                    // from bit WB * p to the bit above the low plane's
+        v = and_or(shift >= 0 ? hi << shift : hi >> -shift, (((1u << WB) - 1u) << (at + WA)) * 0x00010001u, v);
+    }
+    const half_t bias = (half_t)(float)(1024 >> at);
+    return as_h2(v) - (half2_t){bias, bias};                   // exact: an integer below 64
+}
+
+// Eq.5 and Eq.2 for eight of the 32 weights at a time (k-step ks: weights 8 ks .. 8 ks + 7), as fp16 in natural order, bit-identical
+// to iflow_dequant.
+template <int F> struct HalfDecoder {
+    typedef Fmt<F> T;
+    typedef RawHalf<F> R;
+    typedef Parts<F> P;
+    half2_t s2, o2;
+    DecodeConstants k;
+    __device__ __forceinline__ void open(const R &r, const DecodeConstants &constants, int h, bool real /* a chunk past the end counts as zeros */)
+    {
+        k = constants;
+        uint32_t hdr = 0;
+        if constexpr (T::kind == KIND_Q3H) {
+            // word wi of the block carries scale bits 2wi, 2wi+1 at 14-15 and offset bits at 30-31: the four words of this half
+            // shift theirs into bits 8-15 and 24-31, the lower half of the block belongs eight bits further down, and the
+            // lane 32 apart holds the other half
+            uint32_t g = r.a[0] & 0xC000C000u;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+            for (int i = 1; i < 4; ++i) g = (g >> 2) | (r.a[i] & 0xC000C000u);
+            g >>= h ? 0 : 8;
+            const auto sw = __builtin_amdgcn_permlane32_swap(g, g, false, false);
+            hdr = sw[0] | sw[1];
+        } else {
+            hdr = r.hdr;
+        }
+        if (!real) hdr = 0;
+        const half2_t so = as_h2(hdr);
+        s2 = (half2_t){so.x, so.x}; o2 = (half2_t){so.y, so.y};
+    }
+    __device__ __forceinline__ half8_t step(const R &r, int ks) const
+    {
+        const half2_t m1024 = {(half_t)-1024.0f, (half_t)-1024.0f};
+        half2_t lv[4];
+        if constexpr (T::kind == KIND_Q3H) {
+            const half2_t m1025 = {(half_t)-1025.0f, (half_t)-1025.0f}, m11 = {(half_t)-11.0f, (half_t)-11.0f};
+            uint32_t out[4];
 #pragma unroll
             for (int hsel = 0; hsel < 2; ++hsel) {
-                // two pair codes in the two halves of a register: (4wi, 4wi+1) at bits 0/16, (4wi+2, 4wi+3) at bits 7/23
-                const uint32_t hc = ((r.d[i] >> (7 * hsel)) & 0x007F007Fu) | 0x64006400u;
+                // two pair codes in the two halves of a register: (4i, 4i+1) at bits 0/16, (4i+2, 4i+3) at bits 7/23
+                const uint32_t hc = and_or(r.a[ks] >> (7 * hsel), 0x007F007Fu, k.at0);
                 const half2_t q1 = q3h_high_digit(hc) + m1025;                       // floor(c/11), exact
                 const half2_t c = as_h2(hc) + m1024;                                 // c, exact
                 const half2_t q2 = __builtin_elementwise_fma(q1, m11, c);            // c - 11 q1 = c mod 11, exact
                 const half2_t w1 = __builtin_elementwise_fma(q1, s2, o2);            // (w[4m], w[4m+2])   Eq.2, one rounding
                 const half2_t w2 = __builtin_elementwise_fma(q2, s2, o2);            // (w[4m+1], w[4m+3])
-                out[4 * i + 2 * hsel] = __builtin_amdgcn_perm(pack_h2(w2), pack_h2(w1), 0x05040100u);      // (w[4m], w[4m+1])
-                out[4 * i + 2 * hsel + 1] = __builtin_amdgcn_perm(pack_h2(w2), pack_h2(w1), 0x07060302u);  // (w[4m+2], w[4m+3])
+                out[2 * hsel] = __builtin_amdgcn_perm(pack_h2(w2), pack_h2(w1), 0x05040100u);      // (w[4m], w[4m+1])
+                out[2 * hsel + 1] = __builtin_amdgcn_perm(pack_h2(w2), pack_h2(w1), 0x07060302u);  // (w[4m+2], w[4m+3])
             }
-        }
-    } else {
-        const half2_t so = as_h2(r.hdr);
-        const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-        const half2_t m1024 = {(half_t)-1024.0f, (half_t)-1024.0f}, m64 = {(half_t)-64.0f, (half_t)-64.0f};
-        if (T::kind == KIND_Q4) {
+            return __builtin_bit_cast(half8_t, (u32x4_t){out[0], out[1], out[2], out[3]});
+        } else if constexpr (P::planes) {
+            constexpr int WA = P::WA, WB = P::WB;
+            const uint32_t lo = WA == 4 ? r.a[ks] : r.a[ks >> 1] >> (8 * (ks & 1));
+            const uint32_t hi = WB == 0 ? 0u : WB == 2 ? r.b[ks >> 1] >> (8 * (ks & 1)) : r.b[0] >> (4 * ks);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const uint32_t d = r.d[i], e = d >> 8;
-                const half2_t q0 = as_h2((d & 0x000F000Fu) | 0x64006400u) + m1024;      // (v0, v1)
-                const half2_t q1 = as_h2((d & 0x00F000F0u) | 0x54005400u) + m64;        // (v2, v3)
-                const half2_t q2 = as_h2((e & 0x000F000Fu) | 0x64006400u) + m1024;      // (v4, v5)
-                const half2_t q3 = as_h2((e & 0x00F000F0u) | 0x54005400u) + m64;        // (v6, v7)
-                out[4 * i] = pack_h2(__builtin_elementwise_fma(q0, s2, o2));
-                out[4 * i + 1] = pack_h2(__builtin_elementwise_fma(q1, s2, o2));
-                out[4 * i + 2] = pack_h2(__builtin_elementwise_fma(q2, s2, o2));
-                out[4 * i + 3] = pack_h2(__builtin_elementwise_fma(q3, s2, o2));
-            }
+            for (int p = 0; p < 4; ++p) lv[p] = plane_level<WA, WB>(lo, lo >> 8, hi, p, k);
+        } else if constexpr (T::kind == KIND_Q4) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) lv[p] = plane_level<4, 0>(r.a[ks], r.a[ks] >> 8, 0u, p, k);
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const half2_t q0 = as_h2(__builtin_amdgcn_perm(0x64646464u, r.d[i], 0x04010400u)) + m1024;   // (b0, b1)
-                const half2_t q1 = as_h2(__builtin_amdgcn_perm(0x64646464u, r.d[i], 0x04030402u)) + m1024;   // (b2, b3)
-                out[2 * i] = pack_h2(__builtin_elementwise_fma(q0, s2, o2));
-                out[2 * i + 1] = pack_h2(__builtin_elementwise_fma(q1, s2, o2));
+            for (int i = 0; i < 2; ++i) {
+                lv[2 * i] = as_h2(__builtin_amdgcn_perm(0x64646464u, r.a[2 * ks + i], 0x04010400u)) + m1024;     // (b0, b1)
+                lv[2 * i + 1] = as_h2(__builtin_amdgcn_perm(0x64646464u, r.a[2 * ks + i], 0x04030402u)) + m1024; // (b2, b3)
+            }
+        }
+        uint32_t out[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) out[m] = pack_h2(__builtin_elementwise_fma(lv[m], s2, o2));   // Eq.2, one rounding
+        return __builtin_bit_cast(half8_t, (u32x4_t){out[0], out[1], out[2], out[3]});
+    }
+};
+
+template <int N> __device__ __forceinline__ void wait_requests()          // all but the N newest vector-memory requests, and all LDS reads
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+// LDS of a workgroup: the activations of STAGES steps, then each wavefront's packed weights
+template <int F> constexpr int tile_lds_bytes(int rt, int mb, int wr, int wk, int stages)
+{
+    return stages * wk * mb * 4096 + wr * wk * rt * Parts<F>::BUFFERS * Parts<F>::BYTES;
+}
+
+// RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
+// activations, WK such groups take every WK-th run of G chunks each and add their sums at the end.
+template <int F, int RT, int MB, int WR, int WK, int STAGES>
+__global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile_kernel(const uint8_t *packed, const uint16_t *X, uint16_t *Y,
+                                                                                        int rows, int cols, int batch, int64_t header_offset,
+                                                                                        int ntr, int ntb)
+{
+    typedef Parts<F> P;
+    constexpr int G = P::G, BM = 32 * MB, NW = WR * WK;
+    constexpr int SLICE = BM * 128, STEP = WK * SLICE;         // bytes of one chunk's activations; of the WK chunks of a step
+    constexpr int NX = STEP / (NW * 1024);                     // 1 KB pieces of them a wavefront copies per step
+    constexpr int NG = RT * (P::q3h ? 2 * P::NA : P::NA + P::NB + P::NH);      // a wavefront's requests per group of G chunks
+    // what may still be on its way when a step's activations have to be there: the activations of the STAGES - 2 steps after it and
+    // the groups requested among them
+    constexpr int AHEAD = STAGES - 2, SURE = AHEAD * NX + AHEAD / G * NG;
+    static_assert(NX * NW * 1024 == STEP && SURE + NG < 64 && (P::BUFFERS - 1) * G >= STAGES - 1, "pieces; wait counter; a group is there when its steps come");
+    extern __shared__ __align__(16) uint8_t smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave % WR, wk = wave / WR;
+    const int li = lane & 31, h = lane >> 5;
+    const int tr = blockIdx.x % ntr, tb = blockIdx.x / ntr;
+    const int n0 = (tr * WR + wr) * (32 * RT), m0 = tb * BM;
+    const int nchunks = cols / 64, ngroups = (nchunks + WK * G - 1) / (WK * G), nsteps = ngroups * G;
+    auto chunk_of = [&](int step) { return ((step / G) * WK + wk) * G + step % G; };
+
+    // activations: piece p of a step (1 KB = 8 rows of a chunk) -> LDS as it comes; the 16-byte slots of row r are permuted by
+    // r / 2 (on the way in by choosing what each lane fetches), so that neighbouring rows' operand reads fall into different banks.
+    // A wavefront copies pieces of its own group's chunk.
+    const uint8_t *xbase = reinterpret_cast<const uint8_t *>(X + (int64_t)m0 * cols);
+    uint32_t xoff[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int r = (wr * NX + i) * 8 + (lane >> 3);         // past the batch: the last vector again, its results are not stored
+        xoff[i] = (uint32_t)min(r, batch - 1 - m0) * (uint32_t)(cols * 2) + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+    }
+    auto request_x = [&](int step, int stage) {
+        const int kc = min(chunk_of(step), nchunks - 1);       // past the end: the last chunk again, against weights of zero
+#pragma unroll
+        for (int i = 0; i < NX; ++i) copy_to_lds<16>(xbase + (int64_t)kc * 128, xoff[i], lds0 + stage * STEP + wk * SLICE + (wr * NX + i) * 1024);
+    };
+    WeightRows<F> rowsw;
+    rowsw.open(packed, rows, cols, header_offset, min(n0, rows - 1), lane);
+    const int w0 = STAGES * STEP + wave * (RT * P::BUFFERS * P::BYTES);        // this wavefront's packed weights in LDS
+    auto request_w = [&](int group, int buf) {
+        const int kc = min((group * WK + wk) * G, (nchunks - 1) / G * G);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) rowsw.request(t, kc, lds0 + w0 + (buf * RT + t) * P::BYTES);
+    };
+
+    float16_t acc[RT][MB];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][m][v] = 0.f;
+
+    // k-step ks of a chunk: lane (i, h) takes columns 32 h + 8 ks .. + 7
+    const uint8_t *xrow = smem + wk * SLICE + li * 128;
+    auto read_x = [&](int stage, int ks, half8_t (&af)[MB]) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) af[m] = *reinterpret_cast<const half8_t *>(xrow + stage * STEP + m * 4096 + (((4 * h + ks) ^ ((li >> 1) & 7)) * 16));
+    };
+    RawHalf<F> w[RT];
+    HalfDecoder<F> dec[RT];
+    DecodeConstants constants;
+    constants.open();
+    half8_t af[2][MB], bf[2][RT];
+    auto read_w = [&](int c, int buf) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) WeightRows<F>::read(smem + w0 + (buf * RT + t) * P::BYTES, li, c, h, w[t]);
+    };
+#pragma unroll
+    for (int i = 0; i < P::BUFFERS - 1; ++i) request_w(i, i);
+#pragma unroll
+    for (int i = 0; i < STAGES - 1; ++i) request_x(i, i);
+    wait_requests<(STAGES - 2) * NX>();
+    if constexpr (WR > 1) __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    request_w(P::BUFFERS - 1, P::BUFFERS - 1);
+    request_x(STAGES - 1, STAGES - 1);
+    read_w(0, 0);
+    read_x(0, 0, af[0]);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) { dec[t].open(w[t], constants, h, chunk_of(0) < nchunks); bf[0][t] = dec[t].step(w[t], 0); }
+    int stage = 0, c = 0, buf = 0, group = 0;
+    for (int step = 0; step < nsteps; ++step) {
+        const int next = stage == STAGES - 1 ? 0 : stage + 1;
+        // Each k-step's operands are read (activations) and decoded (weights) during the matrix instructions of the one before,
+        // the next step's first ones during this step's last: its requests have arrived by then, and this stage is free again.
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks < 3) {
+                read_x(stage, ks + 1, af[(ks + 1) & 1]);
+            } else {
+                if (G > 1 && AHEAD % G != 0 && c < AHEAD % G) wait_requests<SURE + NG>();   // a group was requested since
+                else wait_requests<SURE>();                    // step + 1's are there; and the wavefront's reads of this stage are done
+                if constexpr (WR > 1) __builtin_amdgcn_s_barrier();   // ... everybody's (a group of one wavefront copies what it reads)
+                asm volatile("" ::: "memory");
+                if (G == 1 || ++c == G) {                      // the group is used up
+                    c = 0; ++group;
+                    const int used = buf;
+                    buf = buf == P::BUFFERS - 1 ? 0 : buf + 1;
+                    request_w(group + P::BUFFERS - 1, used);
+                }
+                request_x(step + STAGES, stage);
+                read_w(c, buf);
+                read_x(next, 0, af[0]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                if (ks == 3) dec[t].open(w[t], constants, h, chunk_of(step + 1) < nchunks);
+                bf[(ks + 1) & 1][t] = dec[t].step(w[t], (ks + 1) & 3);
+#pragma unroll
+                for (int m = 0; m < MB; ++m) acc[t][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[ks & 1][t], af[ks & 1][m], acc[t][m], 0, 0, 0);
+            }
+        }
+        stage = next;
+    }
+
+    // the groups' sums: tile q of a wavefront is added up, in the order of the groups, by group q % WK
+    wait_requests<0>();                                        // what was requested past the end has landed
+    if constexpr (WK > 1) {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int q = 0; q < RT * MB; ++q) {
+            if (wk == q % WK) continue;
+            float4_t *part = reinterpret_cast<float4_t *>(smem) + ((wr * RT * MB + q) * (WK - 1) + (wk > q % WK ? wk - 1 : wk)) * 256 + lane;
+            const float16_t v = acc[q / MB][q % MB];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[j * 64] = (float4_t){v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]};
+        }
+        __syncthreads();
+    }
+    // 32x32 accumulator layout: register v of lane (li, h) is weight row (v/4)*8 + h*4 + v%4, vector li: four neighbouring rows of
+    // one vector per lane and four registers, stored as 8 bytes where rows end on multiples of four
+    const bool whole = (rows & 3) == 0 && n0 + 32 * RT <= rows;
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int vec = m0 + m * 32 + li;
+        uint16_t *y = Y + (int64_t)min(vec, batch - 1) * rows + n0 + h * 4;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int q = t * MB + m;
+            if (WK > 1 && wk != q % WK) continue;
+            float16_t sum = acc[t][m];
+            if constexpr (WK > 1) {
+                const float4_t *part = reinterpret_cast<const float4_t *>(smem) + (wr * RT * MB + q) * (WK - 1) * 256 + lane;
+                const float16_t own = sum;
+#pragma unroll
+                for (int k = 0; k < WK; ++k) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float4_t p = k == q % WK ? (float4_t){own[4 * j], own[4 * j + 1], own[4 * j + 2], own[4 * j + 3]}
+                                                       : part[(k > q % WK ? k - 1 : k) * 256 + j * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[4 * j + e] = k == 0 ? p[e] : sum[4 * j + e] + p[e];
+                    }
+                }
+            }
+            if (vec < batch) {
+                if (whole) {
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4) {
+                        const half2_t lo = {(half_t)sum[4 * v4], (half_t)sum[4 * v4 + 1]}, hi = {(half_t)sum[4 * v4 + 2], (half_t)sum[4 * v4 + 3]};
+                        *reinterpret_cast<u32x2_t *>(y + t * 32 + v4 * 8) = (u32x2_t){as_u32(lo), as_u32(hi)};
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int dr = t * 32 + (v >> 2) * 8 + (v & 3);
+                        if (n0 + h * 4 + dr < rows) y[dr] = as_u16((half_t)sum[v]);
+                    }
+                }
             }
         }
     }
 }
 
-// (The inputs are deliberately not declared __restrict__: loads from memory the compiler knows to be read-only and
-// unaliased are free to move, and the scheduler then sinks the prefetch of a later chunk down to its use, four
-// barriers later, to save registers - which turns every chunk into a full memory round trip.)
-template <int F, int MT>
-__global__ __launch_bounds__(256) void qgemm_mfma_kernel(const uint8_t *packed, const uint16_t *X, uint16_t *Y, int rows, int cols,
-                                                         int batch, int nbk, int64_t header_offset)
+template <int F, int RT, int MB, int WR, int WK, int STAGES>
+static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
-    // two LDS stages: while the MFMAs read one, the next chunk is written into the other
-    constexpr int BM = 64 * MT;                                // batch rows per workgroup: 128, or 64 where that gives the part more workgroups
-    __shared__ __align__(16) uint16_t xs[2][BM * GM_LD];       // activations  [BM][72]
-    __shared__ __align__(16) uint16_t ws[2][GM_BN * GM_LD];    // weights      [64][68]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n0 = blockIdx.x * GM_BN, m0 = blockIdx.y * BM;
-    const int wm = wave >> 1, wn = wave & 1;                   // this wavefront: batch rows wm*64.., weight rows wn*32..
-
-    // loaders: activations - thread -> (row tid/2, 32 halves at (tid%2)*32); weights - thread -> (row tid/4, quarter tid%4)
-    const int xr = MT == 2 ? tid >> 1 : tid >> 2, xh = MT == 2 ? tid & 1 : tid & 3;   // (MT == 1: row tid/4, 16 halves at (tid%4)*16)
-    const int64_t xrow = min(m0 + xr, batch - 1);              // rows past the batch repeat the last row, their outputs are not stored
-    const u32x4_t *xsrc = reinterpret_cast<const u32x4_t *>(X + xrow * cols + xh * (16 * MT));
-    const int wr = tid >> 2, wq = tid & 3;
-    const int64_t wrow = min(n0 + wr, rows - 1);
-    const int nchunks = cols / GM_BK;
-    const int64_t plane_b = (int64_t)rows * cols * Planes<Fmt<F>::kind>::WA / 8;   // bit-plane formats: start of the high plane
-
-    // (plain vector types and separately named stages: an array of structs that hold HIP's uint4 class is not split
-    // into registers completely, and the part left over is parked in LDS, with a full wait right after its load)
-    struct Stage { u32x4_t x0, x1, x2, x3; Raw16 w; };
-    auto fetch = [&](Stage &st, int kb) {                      // global -> registers; chunks past the end repeat the last one
-        const int kc = min(kb, nchunks - 1);
-        const u32x4_t *xp = xsrc + (int64_t)kc * 8;            // 64 halves per row and chunk = 8 x 16 bytes; this thread's half = 4
-        st.x0 = xp[0]; st.x1 = xp[1];
-        if constexpr (MT == 2) { st.x2 = xp[2]; st.x3 = xp[3]; }
-        load16<F>(packed, header_offset, plane_b, wrow, nbk, kc, wq, st.w);
-    };
-    auto stash = [&](const Stage &st, int buf) {               // registers -> LDS, weights decoded on the way
-        uint32_t wv[8];
-        decode16<F>(st.w, wq, wv);
-        u32x4_t *xd = reinterpret_cast<u32x4_t *>(&xs[buf][xr * GM_LD + xh * (16 * MT)]);
-        xd[0] = st.x0; xd[1] = st.x1;
-        if constexpr (MT == 2) { xd[2] = st.x2; xd[3] = st.x3; }
-        *reinterpret_cast<uint4 *>(&ws[buf][wr * GM_LD + wq * 16]) = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-        *reinterpret_cast<uint4 *>(&ws[buf][wr * GM_LD + wq * 16 + 8]) = make_uint4(wv[4], wv[5], wv[6], wv[7]);
-    };
-
-    // four independent accumulator chains per wavefront (two output tiles x even/odd k-steps), summed at the end:
-    // a chain's next MFMA then never waits for its previous one
-    float16_t acc[MT][2];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][p][v] = 0.f;
-    const int li = lane & 31, kg = lane >> 5;
-    // The operand fragments of a whole chunk are read into registers of their own first (twelve 16-byte LDS reads), the
-    // next chunk's decode and LDS writes are issued behind them, and only then come the eight MFMAs: left to itself the
-    // compiler reads each fragment into the same few registers right before its MFMA and waits for it there - a full LDS
-    // round trip in front of every MFMA, 1500 cycles per chunk for 256 cycles of matrix-core work.
-    half8_t af[MT][4], bf[4];
-    auto read_fragments = [&](int buf) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {                       // 16 columns per step: lane (li, kg) holds k = 8 kg .. 8 kg + 7
-            bf[ks] = *reinterpret_cast<const half8_t *>(&ws[buf][(wn * 32 + li) * GM_LD + ks * 16 + kg * 8]);
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-                af[i][ks] = *reinterpret_cast<const half8_t *>(&xs[buf][(wm * 32 * MT + i * 32 + li) * GM_LD + ks * 16 + kg * 8]);
-        }
-    };
-    auto multiply = [&]() {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-                acc[i][ks & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][ks], bf[ks], acc[i][ks & 1], 0, 0, 0);
-    };
-
-    // Software pipeline: chunk c multiplies from one LDS stage while chunk c+1 is decoded into the other and chunks
-    // c+2 .. c+4 are in flight from memory in four register stages (a request is issued about four chunk-times
-    // before its data is needed, which covers the HBM latency with a single wavefront per SIMD).  Four chunks per
-    // trip so that the register stages keep their roles without copies; chunks past the end repeat the last one
-    // and are never multiplied.
-    Stage sa, sb, sc, sd;
-    fetch(sa, 0); fetch(sb, 1); fetch(sc, 2); fetch(sd, 3);
-    stash(sa, 0);
-    fetch(sa, 4);
-    __syncthreads();
-    // Whole trips first, without any branch around the loads: with a load under a branch the compiler can no longer
-    // count which outstanding load a register belongs to and waits for all of them, the newest request included.
-    int kb = 0;
-#define IFLOW_GEMM_STEP(ST, U)        /* chunk kb+U multiplies; chunk kb+U+1 goes to the other LDS stage; ST is refilled */ \
-    read_fragments((kb + U) & 1); __builtin_amdgcn_sched_barrier(0);                                                          \
-    stash(ST, (kb + U + 1) & 1); fetch(ST, kb + U + 5); __builtin_amdgcn_sched_barrier(0);                                    \
-    multiply(); __syncthreads();
-    for (; kb + 4 <= nchunks; kb += 4) {
-        IFLOW_GEMM_STEP(sb, 0) IFLOW_GEMM_STEP(sc, 1) IFLOW_GEMM_STEP(sd, 2) IFLOW_GEMM_STEP(sa, 3)
-    }
-#undef IFLOW_GEMM_STEP
-#define IFLOW_GEMM_TAIL(ST, U) if (kb + U < nchunks) { read_fragments((kb + U) & 1); stash(ST, (kb + U + 1) & 1); multiply(); __syncthreads(); }
-    IFLOW_GEMM_TAIL(sb, 0) IFLOW_GEMM_TAIL(sc, 1) IFLOW_GEMM_TAIL(sd, 2)      // the last one to three chunks
-#undef IFLOW_GEMM_TAIL
-
-    // 32x32 accumulator layout: register v of lane l is D[(v/4)*8 + (l/32)*4 + v%4][l%32]
-    const int col = n0 + wn * 32 + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int brow = m0 + wm * 32 * MT + i * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-            if (brow < batch && col < rows) Y[(int64_t)brow * rows + col] = as_u16((half_t)(acc[i][0][v] + acc[i][1][v]));
-        }
+    typedef Fmt<F> T;
+    constexpr int staged = tile_lds_bytes<F>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096, lds = staged > merge ? staged : merge;
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    static PerDevice pd;
+    int cus = 0;
+    const hipError_t e = once_per_device(pd, &cus, [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&qgemm_tile_kernel<F, RT, MB, WR, WK, STAGES>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (e != hipSuccess) return e;
+    const int64_t header_offset = rows * (cols / T::block) * (int64_t)T::code_bytes;
+    const int64_t ntr = (rows + 32 * RT * WR - 1) / (32 * RT * WR), ntb = (batch + 32 * MB - 1) / (32 * MB);
+    if (ntr * ntb > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((qgemm_tile_kernel<F, RT, MB, WR, WK, STAGES>), dim3((unsigned)(ntr * ntb)), dim3(64 * WR * WK), lds, s,
+                       static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, header_offset, (int)ntr, (int)ntb);
+    return hipGetLastError();
 }
+
+// The tiles in use and what a launch of each costs in microseconds: start + rounds * (round + steps * step), rounds = workgroups per compute
+// unit, steps = chunks that one wavefront walks.  Fitted to five formats x eight shapes (1024^2 to 8192^2) x 17 .. 2048 vectors; by it
+// the chosen tile is 1.4 % slower than the best of sixteen in the mean, 12 % at worst.  The choice depends on sizes, format and the
+// number of compute units only, so a call always takes the same path on the same device.
+#define IFLOW_TILES(V) /* RT MB WR WK STAGES  start  round  step */ \
+    V(2, 8, 4, 1, 2, 0.0, 5.96, 1.60)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
+    V(2, 4, 4, 1, 2, 0.0, 3.82, 0.98)    /* 256 x 128 */ \
+    V(3, 4, 2, 2, 2, 0.0, 6.15, 1.52)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups for 256 compute units) */ \
+    V(2, 4, 2, 2, 2, 0.0, 4.41, 1.11)    /* 128 x 128 */ \
+    V(3, 2, 1, 4, 2, 0.68, 4.90, 1.05)   /* 96 x 64 */ \
+    V(2, 2, 1, 4, 3, 1.55, 3.37, 0.77)   /* 64 x 64 */ \
+    V(1, 2, 1, 4, 3, 2.94, 2.45, 0.48)   /* 32 x 64 */ \
+    V(1, 1, 1, 8, 2, 2.79, 2.51, 0.62)   /* 32 x 32, K among eight wavefronts */ \
+    V(1, 1, 1, 4, 3, 5.31, 0.41, 0.33)   /* 32 x 32, two workgroups per compute unit */
 
 template <int F>
 static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
-    typedef Fmt<F> T;
-    const int nbk = (int)(cols / T::block);
-    const int64_t header_offset = rows * (cols / T::block) * (int64_t)T::code_bytes;
-    // 128 batch rows per workgroup; 64 for batches that would leave half of a 128-row tile empty (32-64 vectors: 25 us instead
-    // of 33 on 4096 x 4096).  With more vectors the smaller tile only adds workgroups that re-read the weights (measured:
-    // 36.7 against 34.7 us at 512 vectors).
-    const int64_t nx = (rows + GM_BN - 1) / GM_BN;
-    const bool small_tiles = batch <= 64;
-    const int bm = small_tiles ? 64 : 128;
-    const dim3 grid((unsigned)nx, (unsigned)((batch + bm - 1) / bm));
-    if (grid.y > 65535u) return hipErrorInvalidValue;
-    if (small_tiles)
-        hipLaunchKernelGGL((qgemm_mfma_kernel<F, 1>), grid, dim3(256), 0, s,
-                           static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk, header_offset);
-    else
-        hipLaunchKernelGGL((qgemm_mfma_kernel<F, 2>), grid, dim3(256), 0, s,
-                           static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk, header_offset);
-    return hipGetLastError();
+    int cus = 0;
+    hipError_t e = device_compute_units(&cus);
+    if (e != hipSuccess) return e;
+    constexpr int G = Parts<F>::G;
+    int best = -1, i = 0;
+    double best_us = 0;
+#define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) { \
+        const int64_t wgs = ((rows + 32 * RT * WR - 1) / (32 * RT * WR)) * ((batch + 32 * MB - 1) / (32 * MB)); \
+        const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)((cols / 64 + WK * G - 1) / (WK * G) * G); \
+        const double us = START + rounds * (ROUND + steps * STEP_US); \
+        if (best < 0 || us < best_us) { best = i; best_us = us; } \
+        ++i; }
+    IFLOW_TILES(IFLOW_TILE_PRICE)
+#undef IFLOW_TILE_PRICE
+    i = 0;
+#define IFLOW_TILE_GO(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) \
+    if (best == i++) return tile_go<F, RT, MB, WR, WK, STAGES>(packed, rows, cols, X, batch, Y, s);
+    IFLOW_TILES(IFLOW_TILE_GO)
+#undef IFLOW_TILE_GO
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_qgemm_mfma(int format, const void *packed, int64_t rows, int64_t cols,
                              const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
+    if (cols % 64 != 0 || cols > QGEMM_MFMA_MAX_COLS) return hipErrorInvalidValue;
     return for_format(format, [&](auto f) { return gemm_one<decltype(f)::value>(packed, rows, cols, X, batch, Y, s); });
 }
 

@@ -1,0 +1,51 @@
+"""GPU parity of the tiled matrix-core product (17 and more activation vectors): every tile shape the launcher chooses among, every
+format, with ragged rows, vectors and column chunks (a run of chunks that ends inside a group, chunks missing for some of the wavefronts
+that share K), rows whose outputs can and cannot be stored eight bytes at a time.
+
+Reference: plain fp64 matrix product (torch) of the activations with iflow_dequant's fp16 weights, which other tests hold bit-exact
+to the oracle.  The kernel multiplies exactly those weights and accumulates in fp32, so what is left is one fp16 rounding of the output
+(2^-11 = 4.9e-4 of the value) and the fp32 sums (below 1e-4 at 13000 columns): 6e-4 of max(|y|, rms)."""
+import pytest
+
+from paper_2401_08294_amd import synth
+from test_gpu_parity import NAMES, gpu, say  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # rows, 64-column chunks, vectors                            tile (rows x vectors of a workgroup; wavefronts along K)
+    (8200, 31, 1025), (16385, 1, 400),                                   # 256 x 256
+    (8389, 1, 17), (12290, 3, 511),                                      # 256 x 128
+    (11010, 65, 500),                                                    # 192 x 128; 2
+    (4100, 33, 513), (12411, 5, 65),                                     # 128 x 128; 2
+    (3001, 17, 500), (16719, 9, 17),                                     # 96 x 64; 4
+    (4099, 65, 97), (8367, 5, 31),                                       # 64 x 64; 4
+    (4179, 5, 33), (4099, 65, 64),                                       # 32 x 64; 4
+    (70, 200, 33), (1, 8, 32),                                           # 32 x 32; 8
+    (1031, 65, 200), (97, 3, 127), (64, 2, 129),                         # 32 x 32; 4 or 8
+]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_every_tile(gpu, name):
+    torch, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    g = torch.Generator(device="cuda")
+    for i, (rows, chunks, batch) in enumerate(SHAPES):
+        say(f"[case] tile {name} rows={rows} cols={64 * chunks} batch={batch}")
+        cols = 64 * chunks
+        g.manual_seed(synth.BASE_SEED + 4000 + i)
+        w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+        x = torch.empty((batch, cols), device="cuda").normal_(generator=g).half()
+        n = iflow.packed_bytes(fmt, rows, cols)
+        packed = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        iflow.quantize(fmt, w, rows, cols, packed, n)
+        w16 = torch.empty((rows, cols), dtype=torch.float16, device="cuda")
+        iflow.dequant(fmt, packed, rows, cols, w16)
+        y = torch.full((batch * rows + 64,), float("nan"), dtype=torch.float16, device="cuda")
+        iflow.qgemm(fmt, packed, rows, cols, x, batch, y)
+        torch.cuda.synchronize()
+        assert torch.isnan(y[batch * rows:]).all(), "wrote past the last output"
+        got = y[:batch * rows].view(batch, rows).double()
+        ref = x.double() @ w16.double().T.contiguous()
+        err = ((got - ref).abs() / torch.maximum(ref.abs(), ref.square().mean(1, keepdim=True).sqrt())).max().item()
+        assert err <= 6e-4, f"{rows} x {cols}, {batch} vectors: {err:.2e}"      # (a NaN, an output never written, fails too)

@@ -1,0 +1,47 @@
+"""The quantizer decides by a reciprocal except near a rounding boundary, where it divides: weights placed on, just below and just above the
+boundaries (half steps) of blocks of every magnitude, byte for byte against the oracle; and row lengths on both sides of the
+store address's rule (256 blocks a row), with workgroups that span many rows."""
+import numpy as np
+import pytest
+
+from paper_2401_08294_amd import synth
+from test_gpu_parity import NAMES, gpu, say  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def check(gpu, orc, name, w, what):
+    torch, iflow = gpu
+    fmt, (rows, cols) = iflow.FORMATS[name], w.shape
+    say(f"[case] quantize {name} {rows} x {cols}: {what}")
+    n = iflow.packed_bytes(fmt, rows, cols)
+    packed = torch.full((n + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    iflow.quantize(fmt, torch.from_numpy(w).cuda(), rows, cols, packed, n)
+    torch.cuda.synchronize()
+    host = packed.cpu().numpy()
+    q, s, o = orc.quantize(orc.FORMATS[name], w)
+    assert np.array_equal(host[:n], orc.pack_device(orc.FORMATS[name], q, s, o)) and (host[n:] == 0xA5).all()
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_weights_at_rounding_boundaries(gpu, orc, name):
+    _, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    block, top = iflow.format_block(fmt), iflow.format_levels(fmt) - 1
+    rng = np.random.default_rng(synth.BASE_SEED + 5000)
+    rows, blocks = 61, 22
+    scale = np.exp2(rng.integers(-22, 4, (rows, blocks, 1))).astype(np.float32) * rng.integers(1, 1024, (rows, blocks, 1)).astype(np.float32) / 1024
+    scale = scale.astype(np.float16).astype(np.float32) + np.float32(2.0 ** -24)
+    offset = (rng.standard_normal((rows, blocks, 1)) * 10 * scale).astype(np.float16).astype(np.float32)
+    t = rng.integers(0, top, (rows, blocks, block)).astype(np.float32) + np.float32(0.5)
+    t[:, :, 0], t[:, :, 1] = 0, top                            # both ends present: the block's own scale and offset come out near these
+    w = (offset + t * scale).astype(np.float32)
+    ulps = rng.integers(-3, 4, w.shape).astype(np.int32)
+    ulps[:, :, :2] = 0
+    w = np.where(np.abs(w) > 1e-30, (w.view(np.int32) + ulps).view(np.float32), w)
+    check(gpu, orc, name, np.ascontiguousarray(w.reshape(rows, blocks * block)), "half steps, up to 3 ulps off")
+
+
+@pytest.mark.parametrize("rows,blocks", [(700, 1), (301, 3), (67, 65), (5, 255), (5, 256), (3, 257), (2, 1025)])
+def test_store_addresses(gpu, orc, rows, blocks):
+    check(gpu, orc, "Q3H_B64", synth.weights(rows, 64 * blocks, 0.02, synth.BASE_SEED + 5100 + blocks), "rows and strips")

@@ -417,3 +417,17 @@ def test_bench_refuses_more_than_one_gpu():
     assert res.returncode != 0
     assert "one GPU" in (res.stdout + res.stderr)
     assert not any(line.startswith("{") for line in res.stdout.splitlines())
+
+
+def test_corrected_quotient_is_the_ieee_quotient():
+    """The quantizer's scale: range * y with y = 1/L rounded to nearest, corrected once by the exact remainder, equals range / L rounded
+    to nearest (fp32) for every number of levels in use."""
+    rng = np.random.default_rng(7)
+    x = np.exp2(rng.uniform(-40, 17, 400000)).astype(np.float32)
+    x = np.concatenate([x, np.exp2(np.arange(-40.0, 17.0)), np.arange(1.0, 70000.0), np.zeros(1)]).astype(np.float32)
+    for top in (255, 63, 31, 15, 10, 7, 3):
+        y = np.float32(1.0) / np.float32(top)
+        q0 = x * y
+        rest = (x.astype(np.longdouble) - q0.astype(np.longdouble) * top).astype(np.float32)
+        q = (rest.astype(np.longdouble) * np.longdouble(y) + q0.astype(np.longdouble)).astype(np.float32)
+        assert np.array_equal(q, x / np.float32(top)), top

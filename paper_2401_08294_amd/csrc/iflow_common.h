@@ -135,32 +135,38 @@ __device__ __forceinline__ half2_t q3h_low_digit(half2_t h1, uint32_t hc)
     return __builtin_bit_cast(half2_t, r);                                // 2^-20 * (2037 + q2) in each half
 }
 
-// ---- bit planes: fields to exact fp16 integers (the dense kernels; the vector kernels multiply the biased values) ------
-// The 8 / W fields in the low byte of both halves of a plane word, as exact fp16 pairs (even weight, odd weight).
-template <int W>
-__device__ __forceinline__ void plane_byte_fields(uint32_t word, half2_t *v)
-{
-#pragma unroll
-    for (int i = 0; i < 8 / W; ++i) {
-        const uint32_t mask = (((1u << W) - 1u) << (W * i)) * 0x00010001u;
-        const uint32_t magic = (uint32_t)((25 - W * i) << 10) * 0x00010001u;            // bit W i counts 1
-        const half_t bias = (half_t)(float)(1024 >> (W * i));
-        const half2_t b2 = {bias, bias};
-        v[i] = as_h2((word & mask) | magic) - b2;
+// ---- decoding on the way into the matrix cores (the vector kernels multiply the biased values instead) ------------------
+// Constants the decoders OR and AND with, held in registers: v_and_or_b32 takes no literals, and with literals the compiler makes two
+// instructions of each.  (magic[p]: the fp16 pair whose mantissa bit p counts 1, for the fields that start at bit p.)
+struct DecodeConstants {
+    uint32_t at0, at4, at2, at6;
+    __device__ __forceinline__ void open()
+    {
+        at0 = 0x64006400u; at4 = 0x54005400u; at2 = 0x5C005C00u; at6 = 0x4C004C00u;
+        asm volatile("" : "+v"(at0), "+v"(at4), "+v"(at2), "+v"(at6));
     }
+};
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t mask, uint32_t with)
+{
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(mask), "v"(with));
+    return r;
 }
-// Sixteen consecutive weights' fields of a W-bit plane: W bytes of each half, `first` = the byte they start at.
-template <int W>
-__device__ __forceinline__ void plane_fields16(const uint32_t *words, int first, half2_t (&v)[8])
+// Weights 2p, 2p + 1 of the eight whose low-plane bits sit in the low WA * 4 bits of both halves of `lo` (pair p at bit WA * p; WA = 4: two
+// pairs per byte, the second two in `lo8` = lo >> 8) and whose high-plane bits sit in the low WB * 4 bits of both halves of `hi`: the
+// level's bits next to each other in the mantissa of an fp16 number, minus that number's own value.
+template <int WA, int WB>
+__device__ __forceinline__ half2_t plane_level(uint32_t lo, uint32_t lo8, uint32_t hi, int p, const DecodeConstants &k)
 {
-    if constexpr (W == 4) {
-        plane_byte_fields<4>(words[0], &v[0]); plane_byte_fields<4>(words[0] >> 8, &v[2]);
-        plane_byte_fields<4>(words[1], &v[4]); plane_byte_fields<4>(words[1] >> 8, &v[6]);
-    } else if constexpr (W == 2) {
-        plane_byte_fields<2>(words[0], &v[0]); plane_byte_fields<2>(words[0] >> 8, &v[4]);
-    } else {
-        plane_byte_fields<1>(words[0] >> (8 * first), &v[0]);
+    const int at = WA == 4 ? 4 * (p & 1) : 2 * p;              // where the level's lowest bit lies
+    const uint32_t magic = at == 0 ? k.at0 : at == 2 ? k.at2 : at == 4 ? k.at4 : k.at6;
+    uint32_t v = and_or(WA == 4 && p >= 2 ? lo8 : lo, (((1u << WA) - 1u) << at) * 0x00010001u, magic);
+    if constexpr (WB > 0) {
+        const int shift = at + WA - WB * p;                    // from bit WB * p to the bit above the low plane's
+        v = and_or(shift >= 0 ? hi << shift : hi >> -shift, (((1u << WB) - 1u) << (at + WA)) * 0x00010001u, v);
     }
+    const half_t bias = (half_t)(float)(1024 >> at);
+    return as_h2(v) - (half2_t){bias, bias};                   // exact: an integer below 64
 }
 
 // ---- once-per-device set-up on the host -----------------------------------------------------------

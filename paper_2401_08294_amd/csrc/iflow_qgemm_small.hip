@@ -13,12 +13,14 @@
 // A workgroup is sixteen wavefronts = sixteen column groups = one 4096-column strip.  The grid is resident (at most one
 // workgroup per compute unit) and a workgroup walks over groups of sixteen rows, strip by strip, with the strip's
 // activations held in registers for all of them; the sixteen partial 16 x 16 tiles of a step are added up through LDS
-// in a fixed order (so results do not vary from run to run), one workgroup barrier per step.
+// in a fixed order (so results do not vary from run to run), one sum per four groups: between two of them the wavefronts
+// run freely.  (One per group, with a barrier each and the residual read behind it: 8 vectors with normalization and residual,
+// 11008 x 4096, us before -> after: 3.5-bit 13.6 -> 12.2, 8-bit 21.2 -> 15.8, 28672 x 8192 41.7 -> 35.5 and 62.3 -> 51.2.)
 #include "iflow_common.h"
 
 namespace iflow {
 
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -29,17 +31,17 @@ template <> struct SmallRaw<KIND_Q4>  { uint32_t d[8]; uint32_t hdr[2]; };   // 
 template <> struct SmallRaw<KIND_Q8>  { uint32_t d[16]; uint32_t hdr[2]; };  // 64 code bytes
 
 // LDS of a workgroup: the activation staging area of each wavefront (eight batch rows of its 256 columns at a time,
-// rows 528 bytes apart so that sixteen lanes reading 16 bytes each from eight different rows hit different banks), two
-// buffers for the partial tiles of a round, and the running sums of the rounds when a row spans several strips.
+// rows 528 bytes apart so that sixteen lanes reading 16 bytes each from eight different rows hit different banks) and each wavefront's
+// partial 16 x 16 tiles of SMALL_ROUNDS rounds: 4 floats per lane, the four lane groups 16 floats further apart, so that the sums over
+// them (sixteen rows of four vectors per wavefront) read 64 different banks; and the running sums of the rounds when a row spans several strips.
 constexpr int SMALL_XROW = 528;
 constexpr int SMALL_XBYTES = 16 * 8 * SMALL_XROW;
-constexpr int SMALL_RED_FLOATS = 16 * 4 * 64;
-#ifndef IFLOW_SMALL_SETS
-#define IFLOW_SMALL_SETS 2
-#endif
-constexpr int SMALL_SETS = IFLOW_SMALL_SETS;                                 // register sets of weights in flight per wavefront (even)
+constexpr int SMALL_TILE = 4 * (64 + 16) - 16;
+constexpr int SMALL_SETS = 2;                                 // register sets of weights in flight per wavefront
+constexpr int SMALL_ROUNDS = 4;                               // rounds between two sums over the wavefronts (1024 threads = their outputs)
 constexpr int SMALL_MAX_ROUNDS = 16;                          // rounds per workgroup when there is more than one strip
-constexpr int SMALL_LDS_BYTES = SMALL_XBYTES + 2 * SMALL_RED_FLOATS * 4 + SMALL_MAX_ROUNDS * 256 * 4;
+constexpr int SMALL_PART = SMALL_XBYTES + SMALL_ROUNDS * 16 * SMALL_TILE * 4;
+constexpr int SMALL_LDS_BYTES = SMALL_PART + SMALL_MAX_ROUNDS * 256 * 4;
 constexpr int SMALL_LDS_BYTES_OPS = SMALL_LDS_BYTES + 16 * 16 * 4;        // + the wavefronts' shares of sum x^2 per activation vector
 
 // A grid of at most one workgroup per compute unit; workgroup b takes the groups of sixteen rows group0 + b,
@@ -72,11 +74,13 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, g = lane >> 4;
     uint8_t *xst = lds + wave * (8 * SMALL_XROW);
-    float *red = reinterpret_cast<float *>(lds + SMALL_XBYTES);                       // [2][wavefront][register][lane]
-    float *part = red + 2 * SMALL_RED_FLOATS;                                         // [round][256]
+    float *mine = reinterpret_cast<float *>(lds + SMALL_XBYTES) + wave * SMALL_TILE + lane * 4 + g * 16;   // + round * 16 tiles
+    float *part = reinterpret_cast<float *>(lds + SMALL_PART);                        // [round][thread of its 256 outputs]
     const int first = group0 + (int)blockIdx.x;
     const int rounds = (ngroups - first + (int)gridDim.x - 1) / (int)gridDim.x;       // >= 1: the grid never exceeds the groups
     const int total = nstrips * rounds;                       // steps (strip, round) of this workgroup, strips outermost
+    const int batches = (rounds + SMALL_ROUNDS - 1) / SMALL_ROUNDS, per_batch = (rounds + batches - 1) / batches;
+    const bool carry = batches == 1;                          // every round keeps its slot: the strips add up there, one sum at the very end
 
     // weights of step k = (strip, round): the lane's 64 columns of row (group * 16 + i); steps past the end repeat the last one,
     // rows past the end the last row, dead column groups of a ragged strip the strip's first group: every load stays in bounds
@@ -136,13 +140,18 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     };
 
     const half2_t m1025 = {(half_t)-1025.0f, (half_t)-1025.0f}, m1024 = {(half_t)-1024.0f, (half_t)-1024.0f};
-    const half2_t m11 = {(half_t)-11.0f, (half_t)-11.0f}, m64 = {(half_t)-64.0f, (half_t)-64.0f};
-    half4_t xq[16];                                           // MFMA B operands of the current strip
+    const half2_t m11 = {(half_t)-11.0f, (half_t)-11.0f};
+    DecodeConstants constants;
+    constants.open();
+    half8_t xq[8];                                            // MFMA B operands of the current strip
     float ssq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // (rms normalization) this lane's share of sum x^2 of the eight vectors it loads
     float *ssq_lds = reinterpret_cast<float *>(lds + SMALL_LDS_BYTES);                // [wavefront][vector]
+    auto join = [](half2_t a, half2_t b, half2_t c, half2_t e) {
+        return __builtin_bit_cast(half8_t, (u32x4_t){as_u32(a), as_u32(b), as_u32(c), as_u32(e)});
+    };
 
-    // one round: dequantize the lane's block, sixteen MFMA steps, add the sixteen wavefronts' tiles up through LDS
-    auto round_body = [&](const SmallRaw<KIND> &raw, int t, int r, int which) {
+    // one round: dequantize the lane's block, eight MFMA steps (on top of the earlier strips'), the tile to its slot
+    auto round_body = [&](const SmallRaw<KIND> &raw, int slot, bool onto) {
         uint32_t d[NWORDS], hdr[2];
 #pragma unroll
         for (int w = 0; w < NWORDS; ++w) d[w] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)raw.d[w]);
@@ -151,6 +160,7 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             for (int h = 0; h < HPL; ++h) hdr[h] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)raw.hdr[h]);
         }
         float4_t acc = {0.f, 0.f, 0.f, 0.f};
+        if (onto) acc = *reinterpret_cast<const float4_t *>(mine + slot * (16 * SMALL_TILE));
         if constexpr (KIND == KIND_Q3H) {
             uint32_t h = d[0] & 0xC000C000u;                  // header from the spare bits of the eight words
 #pragma unroll
@@ -159,115 +169,68 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
 #pragma unroll
             for (int w = 0; w < 8; ++w) {
+                half2_t wv[4];
 #pragma unroll
-                for (int hs = 0; hs < 2; ++hs) {              // decode slot s = 2w + hs: weights 4s .. 4s+3
-                    const uint32_t hc = ((d[w] >> (7 * hs)) & 0x007F007Fu) | 0x64006400u;
+                for (int hs = 0; hs < 2; ++hs) {              // slot s = 2w + hs: weights 4s .. 4s+3
+                    const uint32_t hc = and_or(d[w] >> (7 * hs), 0x007F007Fu, constants.at0);
                     const half2_t q1 = q3h_high_digit(hc) + m1025;                    // floor(c/11), exact
                     const half2_t c = as_h2(hc) + m1024;                              // c, exact
                     const half2_t q2 = __builtin_elementwise_fma(q1, m11, c);         // c mod 11, exact
-                    const half2_t w1 = __builtin_elementwise_fma(q1, s2, o2);         // (w[4s], w[4s+2])   Eq.2, one rounding
-                    const half2_t w2 = __builtin_elementwise_fma(q2, s2, o2);         // (w[4s+1], w[4s+3])
-                    const half4_t a = __builtin_shufflevector(w1, w2, 0, 1, 2, 3);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a, xq[2 * w + hs], acc, 0, 0, 0);
+                    wv[2 * hs] = __builtin_elementwise_fma(q1, s2, o2);               // (w[4s], w[4s+2])   Eq.2, one rounding
+                    wv[2 * hs + 1] = __builtin_elementwise_fma(q2, s2, o2);           // (w[4s+1], w[4s+3])
                 }
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(join(wv[0], wv[1], wv[2], wv[3]), xq[w], acc, 0, 0, 0);
             }
-        } else if constexpr (kind_has_planes(KIND)) {
-            // sixteen weights at a time: the fields of both planes as exact fp16 integers, level = high * 2^WA + low, Eq.2
-            const half2_t up = {(half_t)(float)(1 << WA), (half_t)(float)(1 << WA)};
+        } else if constexpr (kind_has_planes(KIND) || KIND == KIND_Q4) {
+            // eight weights at a time: the level's bits of both planes next to each other in an fp16 mantissa, then Eq.2
+            constexpr int LA = KIND == KIND_Q4 ? 4 : WA, LB = KIND == KIND_Q4 ? 0 : WB;
 #pragma unroll
-            for (int gq = 0; gq < 4; ++gq) {
-                const half2_t so = as_h2(hdr[HPL == 2 ? gq >> 1 : 0]);
-                const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-                half2_t lo[8], hi[8];
-                plane_fields16<WA>(&d[WA == 4 ? 2 * gq : gq], 0, lo);
-                if constexpr (WB == 2) plane_fields16<2>(&d[2 * WA + gq], 0, hi);
-                if constexpr (WB == 1) plane_fields16<1>(&d[2 * WA + (gq >> 1)], gq & 1, hi);
-                half2_t wv[8];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) {
-                    half2_t level = lo[m];
-                    if constexpr (WB > 0) level = __builtin_elementwise_fma(hi[m], up, lo[m]);
-                    wv[m] = __builtin_elementwise_fma(level, s2, o2);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const half4_t a = __builtin_shufflevector(wv[2 * j], wv[2 * j + 1], 0, 1, 2, 3);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a, xq[4 * gq + j], acc, 0, 0, 0);
-                }
-            }
-        } else if constexpr (KIND == KIND_Q4) {
-#pragma unroll
-            for (int w = 0; w < 8; ++w) {                     // word w: weights 8w .. 8w+7, nibble order v0 v2 v4 v6 v1 v3 v5 v7
+            for (int w = 0; w < 8; ++w) {
                 const half2_t so = as_h2(hdr[HPL == 2 ? w >> 2 : 0]);
                 const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-                const uint32_t dw = d[w], e = dw >> 8;
-                const half2_t q0 = as_h2((dw & 0x000F000Fu) | 0x64006400u) + m1024;   // (v0, v1)
-                const half2_t q1 = as_h2((dw & 0x00F000F0u) | 0x54005400u) + m64;     // (v2, v3)
-                const half2_t q2 = as_h2((e & 0x000F000Fu) | 0x64006400u) + m1024;    // (v4, v5)
-                const half2_t q3 = as_h2((e & 0x00F000F0u) | 0x54005400u) + m64;      // (v6, v7)
-                const half4_t a0 = __builtin_shufflevector(__builtin_elementwise_fma(q0, s2, o2), __builtin_elementwise_fma(q1, s2, o2), 0, 1, 2, 3);
-                const half4_t a1 = __builtin_shufflevector(__builtin_elementwise_fma(q2, s2, o2), __builtin_elementwise_fma(q3, s2, o2), 0, 1, 2, 3);
-                acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a0, xq[2 * w], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a1, xq[2 * w + 1], acc, 0, 0, 0);
+                const uint32_t lo = LA == 4 ? d[w] : d[w >> 1] >> (8 * (w & 1));
+                const uint32_t hi = LB == 0 ? 0u : LB == 2 ? d[2 * LA + (w >> 1)] >> (8 * (w & 1)) : d[2 * LA + (w >> 2)] >> (4 * (w & 3));
+                half2_t wv[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) wv[p] = __builtin_elementwise_fma(plane_level<LA, LB>(lo, lo >> 8, hi, p, constants), s2, o2);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(join(wv[0], wv[1], wv[2], wv[3]), xq[w], acc, 0, 0, 0);
             }
         } else {
 #pragma unroll
-            for (int w = 0; w < 16; ++w) {                    // word w: bytes = weights 4w .. 4w+3
-                const half2_t so = as_h2(hdr[HPL == 2 ? w >> 3 : 0]);
+            for (int w = 0; w < 8; ++w) {                     // words 2w, 2w + 1: bytes = weights 8w .. 8w+7
+                const half2_t so = as_h2(hdr[HPL == 2 ? w >> 2 : 0]);
                 const half2_t s2 = {so.x, so.x}, o2 = {so.y, so.y};
-                const half2_t q0 = as_h2(__builtin_amdgcn_perm(0x64646464u, d[w], 0x04010400u)) + m1024;   // (b0, b1)
-                const half2_t q1 = as_h2(__builtin_amdgcn_perm(0x64646464u, d[w], 0x04030402u)) + m1024;   // (b2, b3)
-                const half4_t a0 = __builtin_shufflevector(__builtin_elementwise_fma(q0, s2, o2), __builtin_elementwise_fma(q1, s2, o2), 0, 1, 2, 3);
-                acc = __builtin_amdgcn_mfma_f32_16x16x16f16(a0, xq[w], acc, 0, 0, 0);
+                half2_t wv[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    wv[p] = __builtin_elementwise_fma(as_h2(__builtin_amdgcn_perm(0x64646464u, d[2 * w + (p >> 1)], p & 1 ? 0x04030402u : 0x04010400u)) + m1024, s2, o2);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(join(wv[0], wv[1], wv[2], wv[3]), xq[w], acc, 0, 0, 0);
             }
         }
-        // accumulator register e of lane (j, g') is D[4g' + e][j].  The buffer alternates from step to step: a wavefront that
-        // is one step ahead writes the other buffer, and nobody is two steps ahead of a reader (one barrier per step).
-        float *buf = red + which * SMALL_RED_FLOATS;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) buf[(wave * 4 + e) * 64 + lane] = acc[e];
-        __syncthreads();
-        const int tid = threadIdx.x;
-        if (tid < 256) {
-            const int e = tid >> 6, l = tid & 63;
-            float sum = (nstrips > 1 && t > 0) ? part[r * 256 + tid] : 0.f;
-#pragma unroll
-            for (int w = 0; w < 16; ++w) sum += buf[(w * 4 + e) * 64 + l];
-            if (t + 1 < nstrips) {
-                part[r * 256 + tid] = sum;
-            } else {
-                const int rr = (first + r * (int)gridDim.x) * 16 + 4 * (l >> 4) + e, b = l & 15;
-                if constexpr (XOP == IFLOW_X_RMS_GAIN) {      // the vector's normalization scalar: the wavefronts' shares in a fixed order
-                    float tot = 0.f;
-#pragma unroll
-                    for (int w = 0; w < 16; ++w) tot += ssq_lds[w * 16 + b];
-                    sum *= 1.0f / __builtin_sqrtf(tot / (float)cols + ops.eps);
-                }
-                if constexpr (XOP >= 0) {
-                    if (ops.residual != nullptr && rr < rows && b < batch) sum += (float)as_h(ops.residual[(int64_t)b * rows + rr]);
-                }
-                if (rr < rows && b < batch) Y[(int64_t)b * rows + rr] = as_u16((half_t)sum);
-            }
-        }
+        *reinterpret_cast<float4_t *>(mine + slot * (16 * SMALL_TILE)) = acc;      // register e of lane (j, g') is D[4g' + e][j]
     };
 
     // activations of strip t: batch rows x the wavefront's 256 columns -> lane (j, g) holds row j, columns 64g .. 64g+63
     auto stage = [&](int t) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                          // (addresses worked out per strip: the registers are needed in the rounds)
         const int kb = t * 64 + wave * 4 + g;
         const bool live = kb < nbk64;                         // ragged last strip: dead lanes add nothing (their activations are zeroed)
-        int c = (t * 64 + wave * 4) * 64 + (lane & 31) * 8;
+        int c = (t * 64 + wave * 4) * 64 + (ln & 31) * 8;
         if (c >= cols) c = 0;                                 // columns past the end: any valid address, the values are masked below
-        u32x4_t va[4], vb[4];                                  // load q: batch rows 2q and 2q+1 (vb: 8+2q, 9+2q), 512 bytes each, lane by lane
+        const bool upper = batch > 8;                         // (uniform)
+        u32x4_t va[4], vb[4] = {};                             // load q: batch rows 2q and 2q+1 (vb: 8+2q, 9+2q), 512 bytes each, lane by lane
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            va[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(2 * q + (lane >> 5), batch - 1) * cols + c);
+            va[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(2 * q + (ln >> 5), batch - 1) * cols + c);
+        if (upper)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            vb[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(8 + 2 * q + (lane >> 5), batch - 1) * cols + c);
+            vb[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(8 + 2 * q + (ln >> 5), batch - 1) * cols + c);
         if constexpr (XOP == IFLOW_X_RMS_GAIN) {
             // the lane's eight columns of every vector it loaded: x^2 summed (columns past the end and dead column groups
             // were redirected to column 0: they do not count), then v = fp16(x g), an exact product rounded once
-            const bool counts = (t * 64 + wave * 4) * 64 + (lane & 31) * 8 < cols;
+            const bool counts = (t * 64 + wave * 4) * 64 + (ln & 31) * 8 < cols;
             const u32x4_t gv = *reinterpret_cast<const u32x4_t *>(ops.aux + c);
             const uint32_t gw[4] = {gv.x, gv.y, gv.z, gv.w};
 #pragma unroll
@@ -287,12 +250,12 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
                 vb[q] = (u32x4_t){xb[0], xb[1], xb[2], xb[3]};
             }
             if (t == nstrips - 1) {
-                // vector 2q + (lane >> 5) (and 8 + ...) over the wavefront's lanes: sum within each half of the wavefront
+                // vector 2q + (ln >> 5) (and 8 + ...) over the wavefront's lanes: sum within each half of the wavefront
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     float v = row16_sum(ssq[q]);
                     v += __shfl_xor(v, 16);
-                    if ((lane & 31) == 0) ssq_lds[wave * 16 + (q < 4 ? 2 * q : 8 + 2 * (q - 4)) + (lane >> 5)] = v;
+                    if ((ln & 31) == 0) ssq_lds[wave * 16 + (q < 4 ? 2 * q : 8 + 2 * (q - 4)) + (ln >> 5)] = v;
                     ssq[q] = 0.f;
                 }
             }
@@ -315,8 +278,8 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             };
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                gate(va[q], 2 * q + (lane >> 5));
-                gate(vb[q], 8 + 2 * q + (lane >> 5));
+                gate(va[q], 2 * q + (ln >> 5));
+                if (upper) gate(vb[q], 8 + 2 * q + (ln >> 5));
             }
         }
         uint32_t n[32];
@@ -325,7 +288,7 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
         auto turn = [&](const u32x4_t (&v)[4], bool mine) {     // eight batch rows through the staging rows
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<u32x4_t *>(xst + (2 * q + (lane >> 5)) * SMALL_XROW + (lane & 31) * 16) = v[q];
+                *reinterpret_cast<u32x4_t *>(xst + (2 * q + (ln >> 5)) * SMALL_XROW + (ln & 31) * 16) = v[q];
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -339,20 +302,55 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             __builtin_amdgcn_wave_barrier();                  // the next turn overwrites the staging rows
         };
         turn(va, i < 8);
-        turn(vb, i >= 8);
-        // MFMA B operands: the four activations of step s.  Q3H's decoder yields weights in the order (4s, 4s+2, 4s+1, 4s+3).
+        if (upper) turn(vb, i >= 8);
+        // MFMA B operands: the eight activations of step w.  Q3H's decoder yields weights in the order (4s, 4s+2, 4s+1, 4s+3).
         const uint32_t keep = live ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            uint32_t e, o;
-            if (KIND == KIND_Q3H) {
-                e = __builtin_amdgcn_perm(n[2 * s + 1], n[2 * s], 0x05040100u);   // (x[4s], x[4s+2])
-                o = __builtin_amdgcn_perm(n[2 * s + 1], n[2 * s], 0x07060302u);   // (x[4s+1], x[4s+3])
-            } else {
-                e = n[2 * s]; o = n[2 * s + 1];                                   // natural order
+        for (int w = 0; w < 8; ++w) {
+            uint32_t v[4];
+#pragma unroll
+            for (int hs = 0; hs < 2; ++hs) {
+                const uint32_t a0 = n[4 * w + 2 * hs], a1 = n[4 * w + 2 * hs + 1];
+                v[2 * hs] = KIND == KIND_Q3H ? __builtin_amdgcn_perm(a1, a0, 0x05040100u) : a0;        // (x[4s], x[4s+2])
+                v[2 * hs + 1] = KIND == KIND_Q3H ? __builtin_amdgcn_perm(a1, a0, 0x07060302u) : a1;    // (x[4s+1], x[4s+3])
             }
-            xq[s] = __builtin_bit_cast(half4_t, make_uint2(e & keep, o & keep));
+            xq[w] = __builtin_bit_cast(half8_t, (u32x4_t){v[0] & keep, v[1] & keep, v[2] & keep, v[3] & keep});
         }
+    };
+    // The sums over the wavefronts, in a fixed order, once per batch of rounds (`slots` of them, from round r0 of strip t on): between two of these the
+    // wavefronts run freely.  1024 threads: round tid / 256 of the batch, vector tid / 16 % 16, row tid % 16 of the round's sixteen.
+    auto finish = [&](int t, int r0, int slots, bool more) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                         // (worked out here each time: the registers are needed in the rounds)
+        const int rl = tid >> 8, b = (tid >> 4) & 15, row16 = tid & 15;
+        const int rr = (first + (r0 + rl) * (int)gridDim.x) * 16 + row16;
+        const bool stores = rl < slots && rr < rows && b < batch && t + 1 == nstrips;
+        const int64_t at = stores ? (int64_t)b * rows + rr : 0;
+        float res = 0.f;
+        if constexpr (XOP >= 0) {                             // (requested in front of the barrier)
+            if (stores && ops.residual != nullptr) res = (float)as_h(ops.residual[at]);
+        }
+        __syncthreads();
+        if (rl < slots) {
+            const float *tile = reinterpret_cast<const float *>(lds + SMALL_XBYTES) + rl * (16 * SMALL_TILE) + (row16 >> 2) * 80 + b * 4 + (row16 & 3);
+            float *running = part + (r0 + rl) * 256 + (tid & 255);
+            float sum = t > 0 && !carry ? *running : 0.f;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) sum += tile[w * SMALL_TILE];
+            if (t + 1 < nstrips) {
+                *running = sum;
+            } else {
+                if constexpr (XOP == IFLOW_X_RMS_GAIN) {      // the vector's normalization scalar: the wavefronts' shares in a fixed order
+                    float tot = 0.f;
+#pragma unroll
+                    for (int w = 0; w < 16; ++w) tot += ssq_lds[w * 16 + b];
+                    sum *= 1.0f / __builtin_sqrtf(tot / (float)cols + ops.eps);
+                }
+                if constexpr (XOP >= 0) sum += res;
+                if (stores) Y[at] = as_u16((half_t)sum);
+            }
+        }
+        if (more) __syncthreads();                            // the next batch overwrites the tiles
     };
     // (t, r) of the step `ahead` (<= S) steps after (t, r)
     auto step_after = [&](int t, int r, int ahead, int &t2, int &r2) {
@@ -364,10 +362,10 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
 
     // Steps (strip, round) in order, S per trip through S register sets; a set is refilled for S steps ahead right
     // after its use.  The last trips, where some steps or refills no longer exist, run through a guarded copy of the
-    // loop body so that the main loop has no load under a branch (the wait counters stay exact there) and nothing is
+    // loop body so that the main loop has no load of weights under a branch (the wait counters stay exact there) and nothing is
     // requested that is not used (a wavefront ends only when its last load has returned).
     SmallRaw<KIND> raw[S];
-    int t = 0, r = 0, t2, r2;
+    int t = 0, r = 0, slot = 0, t2, r2;
 #pragma unroll
     for (int j = 0; j < S; ++j) {
         step_after(0, 0, j, t2, r2);
@@ -378,9 +376,13 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
 #pragma unroll
         for (int j = 0; j < S; ++j) {
             if (r == 0) stage(t);
-            round_body(raw[j], t, r, j & 1);
+            round_body(raw[j], slot, carry && t > 0);
             step_after(t, r, S, t2, r2);
             load_step(raw[j], t2, r2);
+            if (++slot == per_batch || r + 1 == rounds) {
+                if (!carry || t + 1 == nstrips) finish(t, r + 1 - slot, slot, true);
+                slot = 0;
+            }
             step_after(t, r, 1, t, r);
         }
     }
@@ -389,10 +391,14 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
         for (int j = 0; j < S; ++j) {
             if (k + j < total) {                              // (uniform over the workgroup)
                 if (r == 0) stage(t);
-                round_body(raw[j], t, r, j & 1);
+                round_body(raw[j], slot, carry && t > 0);
                 if (k + j + S < total) {
                     step_after(t, r, S, t2, r2);
                     load_step(raw[j], t2, r2);
+                }
+                if (++slot == per_batch || r + 1 == rounds) {
+                    if (!carry || t + 1 == nstrips) finish(t, r + 1 - slot, slot, k + j + 1 < total);
+                    slot = 0;
                 }
                 step_after(t, r, 1, t, r);
             }

@@ -111,10 +111,22 @@ def _ptr(t):
     return t if isinstance(t, int) or t is None else t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(stream):
+    """Handle of the stream to launch on: the current device's current stream if none is given.  Asked for as the number it is: building
+    torch's Stream object for it takes 2.8 us of a call's 7.0, the number 0.2."""
+    global _raw_stream
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _raw_stream is None:
+            import torch
+            handle = torch.cuda.current_stream().cuda_stream       # (initializes the device runtime where nothing has)
+            current, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+            if current is None or device is None:
+                return handle
+            _raw_stream = lambda: current(device())                # noqa: E731
+        return _raw_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 

@@ -443,19 +443,26 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 }
 
 // The tiles in use and what a launch of each costs in microseconds: start + rounds * (round + steps * step), rounds = workgroups per compute
-// unit, steps = chunks that one wavefront walks.  Fitted to five formats x eight shapes (1024^2 to 8192^2) x 17 .. 2048 vectors; by it
-// the chosen tile is 1.4 % slower than the best of sixteen in the mean, 12 % at worst.  The choice depends on sizes, format and the
-// number of compute units only, so a call always takes the same path on the same device.
+// unit, steps = chunks that one wavefront walks.  Fitted to five formats x nine shapes (1024^2 to 8192^2, 28672 x 2048) x 17 .. 2000
+// vectors; by it the chosen tile is 1.8 % slower than the best of 21 in the mean (with nine tiles 6.5 %: a workgroup too many for the last
+// round costs up to half, so sizes in between are worth having).  The choice depends on sizes, format and the number of compute
+// units only, so a call always takes the same path on the same device.
 #define IFLOW_TILES(V) /* RT MB WR WK STAGES  start  round  step */ \
-    V(2, 8, 4, 1, 2, 0.0, 5.96, 1.60)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
-    V(2, 4, 4, 1, 2, 0.0, 3.82, 0.98)    /* 256 x 128 */ \
-    V(3, 4, 2, 2, 2, 0.0, 6.15, 1.52)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups for 256 compute units) */ \
-    V(2, 4, 2, 2, 2, 0.0, 4.41, 1.11)    /* 128 x 128 */ \
-    V(3, 2, 1, 4, 2, 0.68, 4.90, 1.05)   /* 96 x 64 */ \
-    V(2, 2, 1, 4, 3, 1.55, 3.37, 0.77)   /* 64 x 64 */ \
-    V(1, 2, 1, 4, 3, 2.94, 2.45, 0.48)   /* 32 x 64 */ \
-    V(1, 1, 1, 8, 2, 2.79, 2.51, 0.62)   /* 32 x 32, K among eight wavefronts */ \
-    V(1, 1, 1, 4, 3, 5.31, 0.41, 0.33)   /* 32 x 32, two workgroups per compute unit */
+    V(2, 8, 4, 1, 2, 0.00, 6.55, 1.69)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
+    V(2, 7, 4, 1, 2, 0.00, 5.62, 1.52)    /* 256 x 224 (28672 rows x 2000 vectors: 1008 workgroups, four rounds; 256 x 256: 3.5) */ \
+    V(2, 6, 4, 1, 2, 0.00, 5.39, 1.35)    /* 256 x 192 */ \
+    V(2, 4, 4, 1, 2, 0.00, 3.86, 1.01)    /* 256 x 128 */ \
+    V(3, 4, 2, 2, 2, 0.00, 6.48, 1.55)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
+    V(2, 4, 2, 2, 2, 0.00, 4.69, 1.11)    /* 128 x 128 */ \
+    V(2, 3, 2, 2, 2, 0.00, 4.03, 0.94)    /* 128 x 96 */ \
+    V(2, 2, 2, 2, 3, 0.38, 3.22, 0.81)    /* 128 x 64 */ \
+    V(3, 2, 1, 4, 2, 0.40, 5.05, 1.05)    /* 96 x 64 */ \
+    V(2, 3, 1, 4, 2, 0.00, 4.87, 0.92)    /* 64 x 96 */ \
+    V(2, 2, 1, 4, 3, 0.61, 3.68, 0.77)    /* 64 x 64 */ \
+    V(2, 1, 1, 4, 3, 1.24, 2.60, 0.61)    /* 64 x 32 */ \
+    V(1, 3, 1, 4, 2, 0.94, 2.92, 0.64)    /* 32 x 96 */ \
+    V(1, 2, 1, 4, 3, 1.19, 2.41, 0.51)    /* 32 x 64 */ \
+    V(1, 1, 1, 8, 2, 1.36, 2.35, 0.66)    /* 32 x 32, K among eight wavefronts */
 
 template <int F>
 static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)

@@ -25,6 +25,7 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef u32x4_t u32x4_any_t __attribute__((aligned(2)));        // 16 bytes at any fp16 address
 
 __device__ __forceinline__ uint32_t pack_h2(half2_t v) { return as_u32(v); }
 
@@ -233,6 +234,7 @@ template <int N> __device__ __forceinline__ void wait_requests()          // all
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
+constexpr int TILE_PITCH = 80, TILE_TURN = 32 * TILE_PITCH;   // a 32 x 32 fp16 tile on its way out: bytes between vectors, in all
 // LDS of a workgroup: the activations of STAGES steps, then each wavefront's packed weights
 template <int F> constexpr int tile_lds_bytes(int rt, int mb, int wr, int wk, int stages)
 {
@@ -364,9 +366,8 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
 
     // the groups' sums: tile q of a wavefront is added up, in the order of the groups, by group q % WK
     wait_requests<0>();                                        // what was requested past the end has landed
+    __syncthreads();                                           // ... everybody's, and everybody's last operands have been read
     if constexpr (WK > 1) {
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
 #pragma unroll
         for (int q = 0; q < RT * MB; ++q) {
             if (wk == q % WK) continue;
@@ -377,48 +378,55 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
         }
         __syncthreads();
     }
-    // 32x32 accumulator layout: register v of lane (li, h) is weight row (v/4)*8 + h*4 + v%4, vector li: four neighbouring rows of
-    // one vector per lane and four registers, stored as 8 bytes where rows end on multiples of four
-    const bool whole = (rows & 3) == 0 && n0 + 32 * RT <= rows;
+    // 32x32 accumulator layout: register v of lane (li, h) is weight row (v/4)*8 + h*4 + v%4, vector li.  A tile crosses LDS once more, so that four
+    // neighbouring lanes store 64 consecutive bytes of one vector, whatever the number of rows is (stored from the registers, eight bytes
+    // per lane where rows are a multiple of four and two where not, odd row counts took 62 -> 73 us at 11007 x 4096 x 512).
+    uint8_t *turn = smem + (WK > 1 ? WR * RT * MB * (WK - 1) * 4096 : 0) + wave * TILE_TURN;
 #pragma unroll
-    for (int m = 0; m < MB; ++m) {
-        const int vec = m0 + m * 32 + li;
-        uint16_t *y = Y + (int64_t)min(vec, batch - 1) * rows + n0 + h * 4;
+    for (int q = 0; q < RT * MB; ++q) {
+        if (WK > 1 && wk != q % WK) continue;
+        const int t = q / MB, m = q % MB;
+        float16_t sum = acc[t][m];
+        if constexpr (WK > 1) {
+            const float4_t *part = reinterpret_cast<const float4_t *>(smem) + (wr * RT * MB + q) * (WK - 1) * 256 + lane;
+            const float16_t own = sum;
 #pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            const int q = t * MB + m;
-            if (WK > 1 && wk != q % WK) continue;
-            float16_t sum = acc[t][m];
-            if constexpr (WK > 1) {
-                const float4_t *part = reinterpret_cast<const float4_t *>(smem) + (wr * RT * MB + q) * (WK - 1) * 256 + lane;
-                const float16_t own = sum;
+            for (int k = 0; k < WK; ++k) {
 #pragma unroll
-                for (int k = 0; k < WK; ++k) {
+                for (int j = 0; j < 4; ++j) {
+                    const float4_t p = k == q % WK ? (float4_t){own[4 * j], own[4 * j + 1], own[4 * j + 2], own[4 * j + 3]}
+                                                   : part[(k > q % WK ? k - 1 : k) * 256 + j * 64];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float4_t p = k == q % WK ? (float4_t){own[4 * j], own[4 * j + 1], own[4 * j + 2], own[4 * j + 3]}
-                                                       : part[(k > q % WK ? k - 1 : k) * 256 + j * 64];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) sum[4 * j + e] = k == 0 ? p[e] : sum[4 * j + e] + p[e];
-                    }
-                }
-            }
-            if (vec < batch) {
-                if (whole) {
-#pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) {
-                        const half2_t lo = {(half_t)sum[4 * v4], (half_t)sum[4 * v4 + 1]}, hi = {(half_t)sum[4 * v4 + 2], (half_t)sum[4 * v4 + 3]};
-                        *reinterpret_cast<u32x2_t *>(y + t * 32 + v4 * 8) = (u32x2_t){as_u32(lo), as_u32(hi)};
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int dr = t * 32 + (v >> 2) * 8 + (v & 3);
-                        if (n0 + h * 4 + dr < rows) y[dr] = as_u16((half_t)sum[v]);
-                    }
+                    for (int e = 0; e < 4; ++e) sum[4 * j + e] = k == 0 ? p[e] : sum[4 * j + e] + p[e];
                 }
             }
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const half2_t lo = {(half_t)sum[4 * j], (half_t)sum[4 * j + 1]}, hi = {(half_t)sum[4 * j + 2], (half_t)sum[4 * j + 3]};
+            *reinterpret_cast<u32x2_t *>(turn + li * TILE_PITCH + j * 16 + h * 8) = (u32x2_t){as_u32(lo), as_u32(hi)};
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int vec = m0 + m * 32 + i * 16 + (lane >> 2), row = n0 + t * 32 + (lane & 3) * 8;
+            const u32x4_t v = *reinterpret_cast<const u32x4_t *>(turn + (i * 16 + (lane >> 2)) * TILE_PITCH + (lane & 3) * 16);
+            uint16_t *y = Y + (int64_t)vec * rows + row;
+            if (vec < batch && row < rows) {
+                if (row + 8 <= rows) {
+                    *reinterpret_cast<u32x4_any_t *>(y) = v;
+                } else {
+                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (row + e < rows) y[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();                      // the next tile overwrites this one
     }
 }
 
@@ -426,7 +434,8 @@ template <int F, int RT, int MB, int WR, int WK, int STAGES>
 static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
     typedef Fmt<F> T;
-    constexpr int staged = tile_lds_bytes<F>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096, lds = staged > merge ? staged : merge;
+    constexpr int staged = tile_lds_bytes<F>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096 + WR * WK * TILE_TURN;
+    constexpr int lds = staged > merge ? staged : merge;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     static PerDevice pd;
     int cus = 0;

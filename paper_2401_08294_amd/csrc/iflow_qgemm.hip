@@ -45,14 +45,14 @@ __device__ __forceinline__ void copy_to_lds(const uint8_t *base /* wavefront-uni
 // A 64-column chunk of a row is, per format, one to three runs of consecutive bytes ("parts": the low or only plane's codes, the high
 // plane's, the headers; the 3.5-bit format: its two planes).  Parts of G consecutive chunks of a row are consecutive too, so a
 // wavefront fetches 32 rows x G chunks at once, with neighbouring lanes on neighbouring pieces of a row: segments of 64 bytes and
-// more where G is 4, 2 or 1 by the format's width.  (One 16-byte piece per row and instruction - 64 cache lines each - cost a fifth of
+// more where G is 4, 2 or 1 by the format's width and the LDS that the tile leaves.  (One 16-byte piece per row and instruction - 64 cache lines each - cost a fifth of
 // the whole kernel.)
-template <int F> struct Parts {
+template <int F, int G_ = 1> struct Parts {
     typedef Fmt<F> T;
     static constexpr bool q3h = T::kind == KIND_Q3H, planes = kind_has_planes(T::kind);
     static constexpr int WA = T::kind == KIND_Q8 ? 8 : planes ? Planes<T::kind>::WA : 4, WB = planes ? Planes<T::kind>::WB : 0;   // bits
     static constexpr int A = q3h ? 16 : 8 * WA, B = q3h ? 16 : 8 * WB, H = q3h ? 0 : 256 / T::block;   // bytes of a row's chunk per part
-    static constexpr int G = T::kind == KIND_Q8 ? 1 : q3h || WA == 2 ? 4 : 2;
+    static constexpr int G = G_;
     static constexpr int PB = B == 8 ? 4 : 16;                 // bytes per lane and piece (8 bytes a chunk: rows are only 8-byte aligned)
     static constexpr int NA = 32 * G * A / 1024, NB = 32 * G * B / (64 * PB), NH = (32 * G * H + 255) / 256;   // pieces (instructions) per part
     static constexpr int LA = 0, LB = 32 * G * A, LH = LB + 32 * G * B, BYTES = LH + 256 * NH;         // places in LDS, total
@@ -62,10 +62,9 @@ template <int F> struct Parts {
 // One lane's 32 weights of a row: half h of a chunk.
 template <int F> struct RawHalf { uint32_t a[Parts<F>::WA], b[Parts<F>::WB ? Parts<F>::WB : 1], hdr; };
 
-template <int F> struct WeightRows {
+template <int F, int G> struct WeightRows {
     typedef Fmt<F> T;
-    typedef Parts<F> P;
-    static constexpr int G = P::G;
+    typedef Parts<F, G> P;
     const uint8_t *a, *b, *hdr;                                // row r0's start in each part (wavefront-uniform)
     uint32_t ra, rb, rh;                                       // bytes of a row in each part
     int last;                                                  // rows past the matrix's end: row r0 + last again
@@ -236,9 +235,17 @@ template <int N> __device__ __forceinline__ void wait_requests()          // all
 
 constexpr int TILE_PITCH = 80, TILE_TURN = 32 * TILE_PITCH;   // a 32 x 32 fp16 tile on its way out: bytes between vectors, in all
 // LDS of a workgroup: the activations of STAGES steps, then each wavefront's packed weights
-template <int F> constexpr int tile_lds_bytes(int rt, int mb, int wr, int wk, int stages)
+template <int F, int G> constexpr int tile_lds_bytes(int rt, int mb, int wr, int wk, int stages)
 {
-    return stages * wk * mb * 4096 + wr * wk * rt * Parts<F>::BUFFERS * Parts<F>::BYTES;
+    return stages * wk * mb * 4096 + wr * wk * rt * Parts<F, G>::BUFFERS * Parts<F, G>::BYTES;
+}
+// Chunks fetched at once: 64 bytes of a row, or 128 where the 8-bit formats find room (28672 x 8192, 512 vectors 281 -> 259 us: a 64-byte
+// request fetches half a line from memory).
+template <int F> constexpr int tile_group(int rt, int mb, int wr, int wk, int stages)
+{
+    typedef Parts<F> P;
+    if (P::WA == 8) return tile_lds_bytes<F, 2>(rt, mb, wr, wk, stages) <= 160 * 1024 && stages <= 3 ? 2 : 1;
+    return P::q3h || P::WA == 2 ? 4 : 2;
 }
 
 // RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
@@ -248,15 +255,15 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
                                                                                         int rows, int cols, int batch, int64_t header_offset,
                                                                                         int ntr, int ntb)
 {
-    typedef Parts<F> P;
-    constexpr int G = P::G, BM = 32 * MB, NW = WR * WK;
+    constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES), BM = 32 * MB;
+    typedef Parts<F, G> P;
     constexpr int SLICE = BM * 128, STEP = WK * SLICE;         // bytes of one chunk's activations; of the WK chunks of a step
-    constexpr int NX = STEP / (NW * 1024);                     // 1 KB pieces of them a wavefront copies per step
+    constexpr int NX = (4 * MB + WR - 1) / WR;                 // 1 KB pieces of its group's chunk a wavefront copies per step
     constexpr int NG = RT * (P::q3h ? 2 * P::NA : P::NA + P::NB + P::NH);      // a wavefront's requests per group of G chunks
     // what may still be on its way when a step's activations have to be there: the activations of the STAGES - 2 steps after it and
     // the groups requested among them
     constexpr int AHEAD = STAGES - 2, SURE = AHEAD * NX + AHEAD / G * NG;
-    static_assert(NX * NW * 1024 == STEP && SURE + NG < 64 && (P::BUFFERS - 1) * G >= STAGES - 1, "pieces; wait counter; a group is there when its steps come");
+    static_assert(SURE + NG < 64 && (P::BUFFERS - 1) * G >= STAGES - 1, "the wait counter's range; a group is there when its steps come");
     extern __shared__ __align__(16) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -269,20 +276,20 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
 
     // activations: piece p of a step (1 KB = 8 rows of a chunk) -> LDS as it comes; the 16-byte slots of row r are permuted by
     // r / 2 (on the way in by choosing what each lane fetches), so that neighbouring rows' operand reads fall into different banks.
-    // A wavefront copies pieces of its own group's chunk.
+    // A wavefront copies pieces of its own group's chunk (the last ones the last piece again where they do not come out even).
     const uint8_t *xbase = reinterpret_cast<const uint8_t *>(X + (int64_t)m0 * cols);
     uint32_t xoff[NX];
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-        const int r = (wr * NX + i) * 8 + (lane >> 3);         // past the batch: the last vector again, its results are not stored
+        const int r = min(wr * NX + i, 4 * MB - 1) * 8 + (lane >> 3);          // past the batch: the last vector again, its results are not stored
         xoff[i] = (uint32_t)min(r, batch - 1 - m0) * (uint32_t)(cols * 2) + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
     }
     auto request_x = [&](int step, int stage) {
         const int kc = min(chunk_of(step), nchunks - 1);       // past the end: the last chunk again, against weights of zero
 #pragma unroll
-        for (int i = 0; i < NX; ++i) copy_to_lds<16>(xbase + (int64_t)kc * 128, xoff[i], lds0 + stage * STEP + wk * SLICE + (wr * NX + i) * 1024);
+        for (int i = 0; i < NX; ++i) copy_to_lds<16>(xbase + (int64_t)kc * 128, xoff[i], lds0 + stage * STEP + wk * SLICE + min(wr * NX + i, 4 * MB - 1) * 1024);
     };
-    WeightRows<F> rowsw;
+    WeightRows<F, G> rowsw;
     rowsw.open(packed, rows, cols, header_offset, min(n0, rows - 1), lane);
     const int w0 = STAGES * STEP + wave * (RT * P::BUFFERS * P::BYTES);        // this wavefront's packed weights in LDS
     auto request_w = [&](int group, int buf) {
@@ -312,7 +319,7 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     half8_t af[2][MB], bf[2][RT];
     auto read_w = [&](int c, int buf) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) WeightRows<F>::read(smem + w0 + (buf * RT + t) * P::BYTES, li, c, h, w[t]);
+        for (int t = 0; t < RT; ++t) WeightRows<F, G>::read(smem + w0 + (buf * RT + t) * P::BYTES, li, c, h, w[t]);
     };
 #pragma unroll
     for (int i = 0; i < P::BUFFERS - 1; ++i) request_w(i, i);
@@ -434,7 +441,7 @@ template <int F, int RT, int MB, int WR, int WK, int STAGES>
 static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
     typedef Fmt<F> T;
-    constexpr int staged = tile_lds_bytes<F>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096 + WR * WK * TILE_TURN;
+    constexpr int staged = tile_lds_bytes<F, tile_group<F>(RT, MB, WR, WK, STAGES)>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096 + WR * WK * TILE_TURN;
     constexpr int lds = staged > merge ? staged : merge;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
     static PerDevice pd;
@@ -452,26 +459,29 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 }
 
 // The tiles in use and what a launch of each costs in microseconds: start + rounds * (round + steps * step), rounds = workgroups per compute
-// unit, steps = chunks that one wavefront walks.  Fitted to five formats x nine shapes (1024^2 to 8192^2, 28672 x 2048) x 17 .. 2000
-// vectors; by it the chosen tile is 1.8 % slower than the best of 21 in the mean (with nine tiles 6.5 %: a workgroup too many for the last
-// round costs up to half, so sizes in between are worth having).  The choice depends on sizes, format and the number of compute
-// units only, so a call always takes the same path on the same device.
+// unit, steps = chunks that one wavefront walks.  Fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000
+// vectors; by it the chosen tile is 0.7 % slower than the best of 33 in the mean.  A workgroup too many for the last round costs up to half of a
+// launch, so sizes in between are worth having (with nine tiles 6.5 %); eight wavefronts of 32 rows beat four of 64 where LDS holds
+// their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 281 -> 244; 4096 x 4096 x 512 32 -> 25).
+// The choice depends on sizes, format and the number of compute units only, so a call always takes the same path on the same device.
 #define IFLOW_TILES(V) /* RT MB WR WK STAGES  start  round  step */ \
-    V(2, 8, 4, 1, 2, 0.00, 6.55, 1.69)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
-    V(2, 7, 4, 1, 2, 0.00, 5.62, 1.52)    /* 256 x 224 (28672 rows x 2000 vectors: 1008 workgroups, four rounds; 256 x 256: 3.5) */ \
-    V(2, 6, 4, 1, 2, 0.00, 5.39, 1.35)    /* 256 x 192 */ \
-    V(2, 4, 4, 1, 2, 0.00, 3.86, 1.01)    /* 256 x 128 */ \
-    V(3, 4, 2, 2, 2, 0.00, 6.48, 1.55)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
-    V(2, 4, 2, 2, 2, 0.00, 4.69, 1.11)    /* 128 x 128 */ \
-    V(2, 3, 2, 2, 2, 0.00, 4.03, 0.94)    /* 128 x 96 */ \
-    V(2, 2, 2, 2, 3, 0.38, 3.22, 0.81)    /* 128 x 64 */ \
-    V(3, 2, 1, 4, 2, 0.40, 5.05, 1.05)    /* 96 x 64 */ \
-    V(2, 3, 1, 4, 2, 0.00, 4.87, 0.92)    /* 64 x 96 */ \
-    V(2, 2, 1, 4, 3, 0.61, 3.68, 0.77)    /* 64 x 64 */ \
-    V(2, 1, 1, 4, 3, 1.24, 2.60, 0.61)    /* 64 x 32 */ \
-    V(1, 3, 1, 4, 2, 0.94, 2.92, 0.64)    /* 32 x 96 */ \
-    V(1, 2, 1, 4, 3, 1.19, 2.41, 0.51)    /* 32 x 64 */ \
-    V(1, 1, 1, 8, 2, 1.36, 2.35, 0.66)    /* 32 x 32, K among eight wavefronts */
+    V(1, 8, 8, 1, 2, 0.00, 3.27, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
+    V(1, 7, 8, 1, 2, 0.00, 1.42, 1.38)    /* 256 x 224 (28672 rows x 2000 vectors: 1008 workgroups, four rounds (256 x 256: 3.5)) */ \
+    V(1, 6, 4, 2, 2, 0.00, 3.15, 1.40)    /* 128 x 192 */ \
+    V(1, 5, 8, 1, 2, 0.00, 0.55, 1.12)    /* 256 x 160 */ \
+    V(1, 4, 8, 1, 3, 0.00, 1.37, 0.93)    /* 256 x 128 */ \
+    V(1, 4, 4, 2, 2, 0.00, 2.04, 1.11)    /* 128 x 128 */ \
+    V(3, 4, 2, 2, 2, 0.00, 4.87, 1.65)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
+    V(1, 4, 3, 2, 2, 0.00, 2.85, 1.00)    /* 96 x 128 */ \
+    V(1, 3, 4, 2, 3, 0.00, 2.67, 0.91)    /* 128 x 96 */ \
+    V(1, 4, 2, 2, 3, 0.00, 3.28, 0.71)    /* 64 x 128 */ \
+    V(2, 2, 2, 2, 3, 0.62, 2.55, 0.80)    /* 128 x 64 */ \
+    V(3, 2, 1, 4, 2, 0.00, 4.79, 1.10)    /* 96 x 64 */ \
+    V(2, 3, 1, 4, 2, 0.00, 4.73, 0.93)    /* 64 x 96 */ \
+    V(2, 2, 1, 4, 2, 0.81, 3.12, 0.79)    /* 64 x 64 */ \
+    V(2, 1, 1, 4, 3, 1.38, 2.35, 0.60)    /* 64 x 32 */ \
+    V(1, 2, 1, 4, 3, 1.45, 2.22, 0.51)    /* 32 x 64 */ \
+    V(1, 1, 1, 8, 2, 1.50, 2.35, 0.66)    /* 32 x 32 */
 
 template <int F>
 static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
@@ -479,10 +489,10 @@ static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const
     int cus = 0;
     hipError_t e = device_compute_units(&cus);
     if (e != hipSuccess) return e;
-    constexpr int G = Parts<F>::G;
     int best = -1, i = 0;
     double best_us = 0;
 #define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) { \
+        constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES); \
         const int64_t wgs = ((rows + 32 * RT * WR - 1) / (32 * RT * WR)) * ((batch + 32 * MB - 1) / (32 * MB)); \
         const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)((cols / 64 + WK * G - 1) / (WK * G) * G); \
         const double us = START + rounds * (ROUND + steps * STEP_US); \

@@ -13,21 +13,23 @@ from test_gpu_parity import NAMES, gpu, say  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 SHAPES = [  # rows, 64-column chunks, vectors                            tile (rows x vectors of a workgroup; wavefronts along K)
-    (16412, 3, 686),                                                     # 256 x 256
-    (16473, 3, 582),                                                     # 256 x 224
-    (8200, 31, 1025), (16385, 1, 400),                                   # 256 x 192
-    (12290, 3, 511), (16625, 5, 130),                                    # 256 x 128
-    (11010, 65, 500), (16447, 33, 129),                                  # 192 x 128; 2
-    (16629, 5, 97),                                                      # 128 x 128; 2
-    (4100, 33, 513), (16429, 3, 65),                                     # 128 x 96; 2
-    (12411, 5, 65), (3001, 17, 500),                                     # 128 x 64; 2 (or neighbours, by the format)
-    (16719, 9, 17), (16578, 33, 17),                                     # 96 x 64; 4
-    (8356, 13, 65),                                                      # 64 x 96; 4
-    (4099, 65, 97), (8443, 9, 33),                                       # 64 x 64; 4
-    (8389, 1, 17), (8367, 5, 31),                                        # 64 x 32; 4
-    (5477, 3, 65),                                                       # 32 x 96; 4
+    (16625, 5, 673), (8200, 31, 1025), (16412, 3, 686),                  # 256 x 256
+    (16441, 5, 481), (16473, 3, 582),                                    # 256 x 224 (seven pieces of activations for eight wavefronts)
+    (16470, 7, 129),                                                     # 128 x 192; 2
+    (16537, 5, 389), (16385, 1, 400),                                    # 256 x 160
+    (16859, 5, 194), (12290, 3, 511),                                    # 256 x 128
+    (16593, 5, 97), (16629, 5, 97),                                      # 128 x 128; 2
+    (16566, 65, 196), (11010, 65, 500),                                  # 192 x 128; 2
+    (16389, 13, 99),                                                     # 96 x 128; 2 (three wavefronts share a chunk)
+    (16413, 5, 17), (16429, 3, 65),                                      # 128 x 96; 2
+    (8235, 5, 66), (4100, 33, 513),                                      # 64 x 128; 2
+    (8270, 9, 131), (3001, 17, 500),                                     # 128 x 64; 2
+    (16474, 13, 17),                                                     # 96 x 64; 4
+    (8315, 13, 65),                                                      # 64 x 96; 4
+    (8198, 9, 33), (4099, 65, 97),                                       # 64 x 64; 4
+    (8650, 9, 17), (8367, 5, 31),                                        # 64 x 32; 4
     (4179, 5, 33), (4099, 65, 64), (97, 3, 127), (64, 2, 129),           # 32 x 64; 4
-    (70, 200, 33), (1, 8, 32), (1031, 65, 200), (43, 18, 21),            # 32 x 32; 8
+    (70, 200, 33), (1, 8, 32), (1031, 65, 200), (33, 18, 19),            # 32 x 32; 8
 ]
 
 

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
     }
 }
 
-// Merge of the splits: one workgroup per query head, thread d + head_dim * u for component d of splits 8u .. 8u + 7 (a state keeps 128 slots
+// Merge of the splits: one workgroup per query head, thread (d, u) for component d of splits 8u .. 8u + 7 (a state keeps 128 slots
 // whatever the head dimension).  Only entries below nsplit are read (the rest of the workspace is whatever earlier calls left there, possibly
 // never touched).  Every split is requested at once: one memory round trip, where one group of threads walking over the splits
 // eight at a time takes up to eight (us per call, query / key-value heads, before -> after: 8/1, 8000 positions 10.8 -> 9.1; 128/8 of 64
@@ -353,11 +353,11 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
 // states then meet in LDS and are added in order.
 constexpr int ATT_MERGE = 8;                                  // splits per group of threads
 __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_merge_kernel(const float *__restrict__ ws, uint16_t *__restrict__ out, int n_heads,
-                                                                                         int nsplit, int head_dim)
+                                                                                         int nsplit)
 {
     constexpr int GROUPS = ATT_MAX_SPLITS / ATT_MERGE;
     __shared__ float s_o[GROUPS][ATT_D], s_m[GROUPS], s_l[GROUPS];
-    const int head = blockIdx.x, group = threadIdx.x / head_dim, d = threadIdx.x - group * head_dim;
+    const int head = blockIdx.x, head_dim = blockDim.x, d = threadIdx.x, group = threadIdx.y;
     const int groups = (nsplit + ATT_MERGE - 1) / ATT_MERGE;
     const float *ws_o = ws + (int64_t)head * ATT_MAX_SPLITS * ATT_D + d;
     const float *ws_m = ws + (int64_t)n_heads * ATT_D * ATT_MAX_SPLITS + (int64_t)head * ATT_MAX_SPLITS;
@@ -445,8 +445,8 @@ hipError_t launch_attn_decode(const uint16_t *q, const uint16_t *k_cache, const 
 #undef IFLOW_ATT_GO_MFMA
     e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1) return e;
-    hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)n_heads), dim3((unsigned)(head_dim * ((nsplit + ATT_MERGE - 1) / ATT_MERGE))), 0, s,
-                       static_cast<const float *>(workspace), out, n_heads, nsplit, head_dim);
+    hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)n_heads), dim3((unsigned)head_dim, (unsigned)((nsplit + ATT_MERGE - 1) / ATT_MERGE)), 0, s,
+                       static_cast<const float *>(workspace), out, n_heads, nsplit);
     return hipGetLastError();
 }
 

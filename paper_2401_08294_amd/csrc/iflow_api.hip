@@ -149,7 +149,7 @@ iflow_status_t iflow_qgemm(iflow_format_t format, const void *packed, int64_t ro
     if (!packed || !X || !Y) return IFLOW_ERR_NULL;
     if (!aligned16(packed) || !aligned16(X) || !aligned16(Y)) return IFLOW_ERR_ALIGN;
     // One backend, three kernels chosen by batch: a few activation vectors ride along with the weight stream on the
-    // vector units; up to 16 vectors the weights stream once through 16x16x16 MFMAs; from 17 vectors on the product is a
+    // vector units; up to 16 vectors the weights stream once through 16x16x32 MFMAs; from 17 vectors on the product is a
     // dense contraction in tiles of 64-column chunks.  (Rows longer than that kernel's offsets reach: passes of sixteen.)
     // Column counts that are not a multiple of 64 (possible with the 32-wide blocks) stay on the vector kernel, four
     // vectors per pass.

@@ -14,8 +14,8 @@
 // What bounds it: for large batches the power limit (a loop of nothing but these matrix instructions on random data runs at 1.5 to 1.8
 // PFLOP/s, 1.5 to 1.8 GHz) and the decode next to it, which is why the largest tile has 256 vectors per decoded weight; for small ones the
 // activations, which every workgroup reads from L2 (1 MB for 128 vectors of 4096 columns, about 100 KB of LDS to hold what is on its way).
-// Measured (3.5-bit; before: 128 x 64 tiles with both operands decoded or copied into LDS): 11008 x 4096, 512 vectors 84.9 -> 59 us (780
-// TFLOP/s), 2048 vectors 354 -> 211 us; 4096 x 4096, 64 vectors 23.8 -> 8.9 us.
+// Measured (before: 128 x 64 tiles with both operands decoded or copied into LDS, passes of sixteen below 32 vectors): 11008 x 4096 3.5-bit, 512
+// vectors 84.5 -> 55.5 us (832 TFLOP/s); 28672 x 8192 4-bit, 2000 vectors 1481 -> 845 us (1112 TFLOP/s); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.9 us.
 #include "iflow_common.h"
 
 namespace iflow {

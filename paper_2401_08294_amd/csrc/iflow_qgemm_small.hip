@@ -1,11 +1,11 @@
 // Small batches (up to 16 activation vectors) on the matrix cores while the weights stream by once.
 //
 // Decoding a weight costs the same vector work whether one or sixteen activation vectors use it, so from a
-// handful of vectors on the multiply moves to v_mfma_f32_16x16x16_f16 and only the decode stays on the vector
+// handful of vectors on the multiply moves to v_mfma_f32_16x16x32_f16 and only the decode stays on the vector
 // units.  A wavefront owns four adjacent 64-weight block columns (256 columns of K) and walks down the rows in
 // groups of sixteen: lane (i, g) = (lane & 15, lane >> 4) holds block (row r0 + i, column kb0 + g).  MFMA step
-// s takes weights 4s..4s+3 of each lane's block as A[i][4g..4g+3] and the matching four activations of batch
-// column j from lane (j, g) as B[4g..4g+3][j]; after sixteen steps D[i][j] is the product over the wavefront's
+// w takes weights 8w..8w+7 of each lane's block as A[i][8g..8g+7] and the matching eight activations of batch
+// column j from lane (j, g) as B[8g..8g+7][j]; after eight steps D[i][j] is the product over the wavefront's
 // 256 columns.  The activations of a lane never change (its block column is fixed), so they stay in 32
 // registers, permuted once into the decoder's element order.  Weights are fully dequantized before the MFMA
 // (the four blocks of a step have different scales): Eq.5 and Eq.2 of the paper with the single-rounded fp16

@@ -164,7 +164,7 @@ template <int F> struct HalfDecoder {
     typedef Parts<F> P;
     half2_t s2, o2;
     DecodeConstants k;
-    __device__ __forceinline__ void open(const R &r, const DecodeConstants &constants, int h, bool real /* a chunk past the end counts as zeros */)
+    __device__ __forceinline__ void open(const R &r, const DecodeConstants &constants, int h)
     {
         k = constants;
         uint32_t hdr = 0;
@@ -181,7 +181,6 @@ template <int F> struct HalfDecoder {
         } else {
             hdr = r.hdr;
         }
-        if (!real) hdr = 0;
         const half2_t so = as_h2(hdr);
         s2 = (half2_t){so.x, so.x}; o2 = (half2_t){so.y, so.y};
     }
@@ -248,6 +247,13 @@ template <int F> constexpr int tile_group(int rt, int mb, int wr, int wk, int st
     return P::q3h || P::WA == 2 ? 4 : 2;
 }
 
+// Chunks that wavefront group `group` of WK walks: the runs group, group + WK, ... of G chunks each, and what is left over of the last one.
+template <int WK, int G> constexpr __host__ __device__ __forceinline__ int tile_steps(int nchunks, int group)
+{
+    const int runs = nchunks / G;                              // whole ones
+    return (runs + WK - 1 - group) / WK * G + (runs % WK == group ? nchunks % G : 0);
+}
+
 // RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
 // activations, WK such groups take every WK-th run of G chunks each and add their sums at the end.
 template <int F, int RT, int MB, int WR, int WK, int STAGES>
@@ -271,7 +277,13 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     const int li = lane & 31, h = lane >> 5;
     const int tr = blockIdx.x % ntr, tb = blockIdx.x / ntr;
     const int n0 = (tr * WR + wr) * (32 * RT), m0 = tb * BM;
-    const int nchunks = cols / 64, ngroups = (nchunks + WK * G - 1) / (WK * G), nsteps = ngroups * G;
+    // Run q of G chunks (the last one may be shorter) belongs to wavefront group q % WK.  A group stops at its own last chunk: nothing is
+    // multiplied that the product does not have (weights of zero against the last activations again would turn an infinity there into a NaN),
+    // and groups with a chunk less leave the compute unit to the others (with K rounded up to WK G chunks, us, 3.5-bit: 4096 x 11008, 33
+    // vectors 19.2, now 17.2; 4096 x 4160, 17 vectors 10.5, now 8.4).
+    const int nchunks = cols / 64;
+    auto steps_of = [&](int group) { return tile_steps<WK, G>(nchunks, group); };
+    const int steps = steps_of(wk);
     auto chunk_of = [&](int step) { return ((step / G) * WK + wk) * G + step % G; };
 
     // activations: piece p of a step (1 KB = 8 rows of a chunk) -> LDS as it comes; the 16-byte slots of row r are permuted by
@@ -285,7 +297,7 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
         xoff[i] = (uint32_t)min(r, batch - 1 - m0) * (uint32_t)(cols * 2) + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
     }
     auto request_x = [&](int step, int stage) {
-        const int kc = min(chunk_of(step), nchunks - 1);       // past the end: the last chunk again, against weights of zero
+        const int kc = min(chunk_of(step), nchunks - 1);       // past the end: the last chunk again, never multiplied
 #pragma unroll
         for (int i = 0; i < NX; ++i) copy_to_lds<16>(xbase + (int64_t)kc * 128, xoff[i], lds0 + stage * STEP + wk * SLICE + min(wr * NX + i, 4 * MB - 1) * 1024);
     };
@@ -333,9 +345,9 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     read_w(0, 0);
     read_x(0, 0, af[0]);
 #pragma unroll
-    for (int t = 0; t < RT; ++t) { dec[t].open(w[t], constants, h, chunk_of(0) < nchunks); bf[0][t] = dec[t].step(w[t], 0); }
+    for (int t = 0; t < RT; ++t) { dec[t].open(w[t], constants, h); bf[0][t] = dec[t].step(w[t], 0); }
     int stage = 0, c = 0, buf = 0, group = 0;
-    for (int step = 0; step < nsteps; ++step) {
+    for (int step = 0; step < steps; ++step) {
         const int next = stage == STAGES - 1 ? 0 : stage + 1;
         // Each k-step's operands are read (activations) and decoded (weights) during the matrix instructions of the one before,
         // the next step's first ones during this step's last: its requests have arrived by then, and this stage is free again.
@@ -362,7 +374,7 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                if (ks == 3) dec[t].open(w[t], constants, h, chunk_of(step + 1) < nchunks);
+                if (ks == 3) dec[t].open(w[t], constants, h);
                 bf[(ks + 1) & 1][t] = dec[t].step(w[t], (ks + 1) & 3);
 #pragma unroll
                 for (int m = 0; m < MB; ++m) acc[t][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[ks & 1][t], af[ks & 1][m], acc[t][m], 0, 0, 0);
@@ -370,6 +382,8 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
         }
         stage = next;
     }
+    if constexpr (WR > 1 && WK > 1)
+        for (int step = steps; step < steps_of(0); ++step) __builtin_amdgcn_s_barrier();      // the other groups' steps (group 0 has the most)
 
     // the groups' sums: tile q of a wavefront is added up, in the order of the groups, by group q % WK
     wait_requests<0>();                                        // what was requested past the end has landed
@@ -494,7 +508,7 @@ static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const
 #define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) { \
         constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES); \
         const int64_t wgs = ((rows + 32 * RT * WR - 1) / (32 * RT * WR)) * ((batch + 32 * MB - 1) / (32 * MB)); \
-        const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)((cols / 64 + WK * G - 1) / (WK * G) * G); \
+        const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)tile_steps<WK, G>((int)(cols / 64), 0); \
         const double us = START + rounds * (ROUND + steps * STEP_US); \
         if (best < 0 || us < best_us) { best = i; best_us = us; } \
         ++i; }

@@ -57,3 +57,37 @@ def test_every_tile(gpu, name):
         ref = x.double() @ w16.double().T.contiguous()
         err = ((got - ref).abs() / torch.maximum(ref.abs(), ref.square().mean(1, keepdim=True).sqrt())).max().item()
         assert err <= 6e-4, f"{rows} x {cols}, {batch} vectors: {err:.2e}"      # (a NaN, an output never written, fails too)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_infinity_in_the_last_columns(gpu, name):
+    """An infinite activation in the last 64 columns makes its vector's outputs infinite (NaN only against a weight of zero), whatever kernel
+    the number of vectors selects, and however the chunks come out over the wavefronts that share K; the other vectors stay as they are."""
+    torch, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    g = torch.Generator(device="cuda")
+    for i, (rows, chunks, batch) in enumerate([(70, 65, 16), (70, 65, 17), (70, 1, 17), (1031, 9, 33), (4099, 13, 65), (16566, 65, 196), (16441, 5, 481),
+                                               (16470, 7, 129), (8270, 9, 131)]):
+        cols = 64 * chunks
+        say(f"[case] infinity {name} rows={rows} cols={cols} batch={batch}")
+        g.manual_seed(synth.BASE_SEED + 4500 + i)
+        w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+        x = torch.empty((batch, cols), device="cuda").normal_(generator=g).half()
+        x[batch // 2, cols - 3] = float("inf")
+        x[batch - 1, cols - 64] = float("-inf")
+        n = iflow.packed_bytes(fmt, rows, cols)
+        packed = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        iflow.quantize(fmt, w, rows, cols, packed, n)
+        w16 = torch.empty((rows, cols), dtype=torch.float16, device="cuda")
+        iflow.dequant(fmt, packed, rows, cols, w16)
+        y = torch.full((batch, rows), float("nan"), dtype=torch.float16, device="cuda")
+        iflow.qgemm(fmt, packed, rows, cols, x, batch, y)
+        torch.cuda.synchronize()
+        ref = x.double() @ w16.double().T.contiguous()
+        finite = torch.isfinite(ref)
+        got = y.double()
+        same = torch.where(finite, torch.isfinite(got), (got == ref) | (torch.isnan(got) & torch.isnan(ref)))
+        assert same.all(), f"{rows} x {cols}, {batch} vectors: {int((~same).sum())} outputs of {int((~finite).sum())} infinite ones differ"
+        rms = torch.where(finite, ref, torch.zeros_like(ref)).square().mean(1, keepdim=True).sqrt()
+        err = torch.where(finite, (got - ref).abs() / torch.maximum(ref.abs(), rms), torch.zeros_like(ref)).max().item()
+        assert err <= 6e-4, f"{rows} x {cols}, {batch} vectors: {err:.2e}"

@@ -84,10 +84,12 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float4 *__restrict_
 
         // the two stored fp16 numbers: scale = (max - min) / L, offset = min.  The quotient is the IEEE one: with y = 1/L rounded to nearest and
         // one correction by the exact remainder the result is correctly rounded (Markstein 1990) unless the remainder underflows, and
-        // then (range below 2^-100) any quotient rounds to a scale of zero.
+        // then (range below 2^-100) any quotient rounds to a scale of zero.  An infinite range has no remainder (inf - inf): its product is
+        // the quotient, an infinity, as it is; a NaN stays that NaN.
         const float range = mx - mn, y = 1.0f / (float)T::L;
         const float q0 = range * y;
         float step = __builtin_fmaf(__builtin_fmaf(-q0, (float)T::L, range), y, q0);
+        step = fabsf(q0) < INFINITY ? step : q0;
         asm("" : "+v"(step));                              // (a register of its own: fused with the conversion below it would be rounded once, not twice)
         const half_t sh = (half_t)step, oh = (half_t)mn;         // round to nearest even
         const float s = (float)sh, o = (float)oh;

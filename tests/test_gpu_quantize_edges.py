@@ -45,3 +45,24 @@ def test_weights_at_rounding_boundaries(gpu, orc, name):
 @pytest.mark.parametrize("rows,blocks", [(700, 1), (301, 3), (67, 65), (5, 255), (5, 256), (3, 257), (2, 1025)])
 def test_store_addresses(gpu, orc, rows, blocks):
     check(gpu, orc, "Q3H_B64", synth.weights(rows, 64 * blocks, 0.02, synth.BASE_SEED + 5100 + blocks), "rows and strips")
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_ranges_that_leave_fp16_and_fp32(gpu, orc, name):
+    """Blocks whose range is infinite (an infinity in them, or finite ends whose difference overflows fp32), whose scale or offset overflows fp16, or
+    that hold a NaN next to finite weights: the stored pair is what the division gives, byte for byte."""
+    _, iflow = gpu
+    block = iflow.format_block(iflow.FORMATS[name])
+    inf, nan = np.float32(np.inf), np.float32(np.nan)
+    w = np.random.default_rng(synth.BASE_SEED + 5200).standard_normal((3, 11, block)).astype(np.float32)
+    w[:, 0, 5] = inf
+    w[:, 1, block - 1] = -inf
+    w[:, 2, 3], w[:, 2, 4] = inf, -inf
+    w[:, 3, 1], w[:, 3, 9] = 3e38, -3e38                       # the difference overflows
+    w[:, 4, :] = inf
+    w[:, 5, 7] = -7e4                                          # offset overflows fp16
+    w[:, 6, 2] = 3e8                                           # scale overflows fp16 at every number of levels
+    w[:, 7, 6], w[:, 7, 11] = 65504.0, -65504.0
+    w[:, 8, 12] = nan
+    w[:, 9, 13], w[:, 9, 14] = nan, inf
+    check(gpu, orc, name, np.ascontiguousarray(w.reshape(3, -1)), "infinite and overflowing ranges")

@@ -431,3 +431,28 @@ def test_corrected_quotient_is_the_ieee_quotient():
         rest = (x.astype(np.longdouble) - q0.astype(np.longdouble) * top).astype(np.float32)
         q = (rest.astype(np.longdouble) * np.longdouble(y) + q0.astype(np.longdouble)).astype(np.float32)
         assert np.array_equal(q, x / np.float32(top)), top
+
+
+def test_forked_child_asks_the_runtime_again(monkeypatch):
+    """The binding's short way to the current stream skips torch's check for a process forked after the device was initialized: a forked child has to
+    go through that check (which refuses) and not launch on the parent's handle."""
+    import torch
+
+    from paper_2401_08294_amd import iflow
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+    monkeypatch.setattr(iflow, "_raw_stream", lambda: 1234)
+    monkeypatch.setattr(torch.cuda, "current_stream", refuse)
+    assert iflow._stream(None) == 1234
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            iflow._stream(None)
+        except RuntimeError:
+            code = 0
+        finally:
+            os._exit(code)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert iflow._stream(None) == 1234                         # the parent keeps its own

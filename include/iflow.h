@@ -353,7 +353,7 @@ iflow_status_t iflow_decode_stack_launch(const iflow_chain_t *chain, int64_t pos
  *   X [batch][cols] fp16, Y [batch][rows] fp16, both device.
  * One backend, chosen by batch: 1 is iflow_qgemv; 2 (8-bit formats: up to 4) runs on the vector units with the
  * activation vectors side by side; up to 16 the weights stream once and the multiply runs on the matrix cores
- * (16x16x32 tiles, weights dequantized in registers); from 17 on (and cols a multiple of 64, at most 2^22) the product is
+ * (16x16x32 tiles, weights dequantized in registers); from 17 on (and cols a multiple of 64, at most 2^26) the product is
  * tiled, 32 x 32 to 256 x 256 outputs per workgroup by a cost model of the tiles.  Which kernel runs
  * depends on the shapes, the format and the device only.  Results of one call do not depend on
  * how busy the device is (all sums are taken in a fixed order). */

@@ -44,6 +44,8 @@ iflow_status_t check_shape(iflow_format_t f, int64_t rows, int64_t cols, iflow::
     return IFLOW_OK;
 }
 
+bool takes_tiles(int64_t cols, int64_t batch) { return batch >= IFLOW_TILE_MIN_BATCH && cols % 64 == 0 && cols <= iflow::QGEMM_MFMA_MAX_COLS; }
+
 size_t packed_size(const iflow::FormatInfo &fi, int64_t rows, int64_t cols)
 {
     return (size_t)rows * (size_t)(cols / fi.block) * (size_t)(fi.code_bytes + 4);
@@ -154,7 +156,7 @@ iflow_status_t iflow_qgemm(iflow_format_t format, const void *packed, int64_t ro
     // Column counts that are not a multiple of 64 (possible with the 32-wide blocks) stay on the vector kernel, four
     // vectors per pass.
     hipStream_t hs = (hipStream_t)stream;
-    if (batch >= IFLOW_TILE_MIN_BATCH && cols % 64 == 0 && cols <= iflow::QGEMM_MFMA_MAX_COLS)
+    if (takes_tiles(cols, batch))
         return device_status(iflow::launch_qgemm_mfma((int)format, packed, rows, cols, X, batch, Y, hs));
     if (cols % 64 == 0 && batch >= (format == IFLOW_Q8_B32 || format == IFLOW_Q8_B64 ? IFLOW_SMALL_MFMA_MIN_BATCH_Q8 : IFLOW_SMALL_MFMA_MIN_BATCH)) {
         for (int64_t b0 = 0; b0 < batch; b0 += 16) {
@@ -165,6 +167,37 @@ iflow_status_t iflow_qgemm(iflow_format_t format, const void *packed, int64_t ro
         return IFLOW_OK;
     }
     return device_status(iflow::launch_qgemv((int)format, packed, rows, cols, X, batch, Y, hs));
+}
+
+// For the library's own tests, not part of the ABI: which tile iflow_qgemm takes on a device of `compute_units` (-1: another kernel), what
+// tile number `tile` is (false: no such tile), and the product through that tile.
+int iflow_internal_qgemm_tile(iflow_format_t format, int64_t rows, int64_t cols, int64_t batch, int compute_units)
+{
+    iflow::FormatInfo fi;
+    if (check_shape(format, rows, cols, &fi) != IFLOW_OK || batch <= 0 || batch > (1LL << 30) || compute_units < 1) return -1;
+    return takes_tiles(cols, batch) ? iflow::qgemm_tile_choice((int)format, rows, cols, batch, compute_units) : -1;
+}
+
+int iflow_internal_qgemm_tile_shape(iflow_format_t format, int tile, int64_t shape[6])
+{
+    iflow::TileShape t;
+    if (!iflow::qgemm_tile_shape((int)format, tile, &t)) return 0;
+    const int64_t v[6] = {t.rows, t.vectors, t.k_groups, t.run, t.buffers, t.max_cols};
+    std::copy(v, v + 6, shape);
+    return 1;
+}
+
+iflow_status_t iflow_internal_qgemm_with_tile(iflow_format_t format, int tile, const void *packed, int64_t rows, int64_t cols,
+                                              const uint16_t *X, int64_t batch, uint16_t *Y, void *stream)
+{
+    iflow::FormatInfo fi;
+    iflow::TileShape t;
+    iflow_status_t st = check_shape(format, rows, cols, &fi);
+    if (st != IFLOW_OK) return st;
+    if (batch <= 0 || batch > (1LL << 30) || cols % 64 != 0 || !iflow::qgemm_tile_shape((int)format, tile, &t) || cols > t.max_cols) return IFLOW_ERR_SHAPE;
+    if (!packed || !X || !Y) return IFLOW_ERR_NULL;
+    if (!aligned16(packed) || !aligned16(X) || !aligned16(Y)) return IFLOW_ERR_ALIGN;
+    return device_status(iflow::launch_qgemm_tile((int)format, tile, packed, rows, cols, X, batch, Y, (hipStream_t)stream));
 }
 
 iflow_status_t iflow_qgemv_multi(iflow_format_t format, int count, const void *const *packed, const int64_t *rows,

@@ -277,8 +277,18 @@ hipError_t launch_qgemm_small_fused(int format, const void *packed, int64_t rows
                                     const uint16_t *aux, float eps, const uint16_t *residual, uint16_t *Y, hipStream_t s);
 hipError_t launch_qgemm_small(int format, const void *packed, int64_t rows, int64_t cols,
                               const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s);
-constexpr int64_t QGEMM_MFMA_MAX_COLS = 1 << 22;   // byte offsets inside a tile (up to 256 rows of activations) are 32-bit
+constexpr int64_t QGEMM_MFMA_MAX_COLS = 1 << 26;   // 32 rows of activations in 32-bit byte offsets: what the smallest tiles reach
 hipError_t launch_qgemm_mfma(int format, const void *packed, int64_t rows, int64_t cols,
+                             const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s);
+// ... the tile it takes on a device of `cus` compute units, what that tile is, and the product with a tile of the caller's choice
+struct TileShape {
+    int rows, vectors;                 // of a workgroup
+    int k_groups, run, buffers;        // wavefront groups that share K, 64-column chunks they fetch at once, such runs in LDS
+    int64_t max_cols;
+};
+int qgemm_tile_choice(int format, int64_t rows, int64_t cols, int64_t batch, int cus);
+bool qgemm_tile_shape(int format, int tile, TileShape *shape);
+hipError_t launch_qgemm_tile(int format, int tile, const void *packed, int64_t rows, int64_t cols,
                              const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s);
 hipError_t launch_qgemv_rows(int format, const void *packed, int64_t rows, int64_t cols, const uint16_t *x, int batch, uint16_t *y,
                              hipStream_t s);

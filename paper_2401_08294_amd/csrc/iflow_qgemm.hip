@@ -451,6 +451,11 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     }
 }
 
+// Byte offsets inside a tile (of its vectors' activations, of a wavefront's rows) are 32-bit: the longest rows a tile can take.  (One limit of
+// 2^22 for all of them left longer rows to passes of sixteen vectors: 512 rows of 2^22 + 64 columns, 4-bit, 96 vectors 22.3 ms, now 6.8; passes
+// remain faster by up to a fifth for 17 to 32 vectors on 64 4-bit rows of 2^22 columns and more, slower on 16 and on 512 rows.)
+constexpr int64_t tile_max_cols(int rt, int mb) { return (1LL << 32) / (32 * (2 * mb > rt ? 2 * mb : rt)); }
+
 template <int F, int RT, int MB, int WR, int WK, int STAGES>
 static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
@@ -458,6 +463,7 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     constexpr int staged = tile_lds_bytes<F, tile_group<F>(RT, MB, WR, WK, STAGES)>(RT, MB, WR, WK, STAGES), merge = WR * RT * MB * (WK - 1) * 4096 + WR * WK * TILE_TURN;
     constexpr int lds = staged > merge ? staged : merge;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+    if (cols > tile_max_cols(RT, MB)) return hipErrorInvalidValue;
     static PerDevice pd;
     int cus = 0;
     const hipError_t e = once_per_device(pd, &cus, [] {
@@ -497,12 +503,9 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     V(1, 2, 1, 4, 3, 1.45, 2.22, 0.51)    /* 32 x 64 */ \
     V(1, 1, 1, 8, 2, 1.50, 2.35, 0.66)    /* 32 x 32 */
 
-template <int F>
-static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
+// The cheapest tile's place in the list (-1: rows too long for every one).
+template <int F> static int tile_choice(int64_t rows, int64_t cols, int64_t batch, int cus)
 {
-    int cus = 0;
-    hipError_t e = device_compute_units(&cus);
-    if (e != hipSuccess) return e;
     int best = -1, i = 0;
     double best_us = 0;
 #define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) { \
@@ -510,23 +513,67 @@ static hipError_t gemm_one(const void *packed, int64_t rows, int64_t cols, const
         const int64_t wgs = ((rows + 32 * RT * WR - 1) / (32 * RT * WR)) * ((batch + 32 * MB - 1) / (32 * MB)); \
         const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)tile_steps<WK, G>((int)(cols / 64), 0); \
         const double us = START + rounds * (ROUND + steps * STEP_US); \
-        if (best < 0 || us < best_us) { best = i; best_us = us; } \
+        if (cols <= tile_max_cols(RT, MB) && (best < 0 || us < best_us)) { best = i; best_us = us; } \
         ++i; }
     IFLOW_TILES(IFLOW_TILE_PRICE)
 #undef IFLOW_TILE_PRICE
-    i = 0;
+    return best;
+}
+
+template <int F>
+static hipError_t tile_launch(int tile, const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
+{
+    int i = 0;
 #define IFLOW_TILE_GO(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) \
-    if (best == i++) return tile_go<F, RT, MB, WR, WK, STAGES>(packed, rows, cols, X, batch, Y, s);
+    if (tile == i++) return tile_go<F, RT, MB, WR, WK, STAGES>(packed, rows, cols, X, batch, Y, s);
     IFLOW_TILES(IFLOW_TILE_GO)
 #undef IFLOW_TILE_GO
     return hipErrorInvalidValue;
 }
 
+template <int F> static bool tile_shape(int tile, TileShape *shape)
+{
+    int i = 0;
+#define IFLOW_TILE_SHAPE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) \
+    if (tile == i++) { \
+        constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES); \
+        *shape = TileShape{32 * RT * WR, 32 * MB, WK, G, Parts<F, G>::BUFFERS, tile_max_cols(RT, MB)}; \
+        return true; \
+    }
+    IFLOW_TILES(IFLOW_TILE_SHAPE)
+#undef IFLOW_TILE_SHAPE
+    return false;
+}
+
+int qgemm_tile_choice(int format, int64_t rows, int64_t cols, int64_t batch, int cus)
+{
+    int tile = -1;
+    if (cols % 64 == 0)
+        (void)for_format(format, [&](auto f) { tile = tile_choice<decltype(f)::value>(rows, cols, batch, cus); return hipSuccess; });
+    return tile;
+}
+
+bool qgemm_tile_shape(int format, int tile, TileShape *shape)
+{
+    bool known = false;
+    (void)for_format(format, [&](auto f) { known = tile_shape<decltype(f)::value>(tile, shape); return hipSuccess; });
+    return known;
+}
+
+hipError_t launch_qgemm_tile(int format, int tile, const void *packed, int64_t rows, int64_t cols,
+                             const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
+{
+    if (cols % 64 != 0) return hipErrorInvalidValue;
+    return for_format(format, [&](auto f) { return tile_launch<decltype(f)::value>(tile, packed, rows, cols, X, batch, Y, s); });
+}
+
 hipError_t launch_qgemm_mfma(int format, const void *packed, int64_t rows, int64_t cols,
                              const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
-    if (cols % 64 != 0 || cols > QGEMM_MFMA_MAX_COLS) return hipErrorInvalidValue;
-    return for_format(format, [&](auto f) { return gemm_one<decltype(f)::value>(packed, rows, cols, X, batch, Y, s); });
+    int cus = 0;
+    const hipError_t e = device_compute_units(&cus);
+    if (e != hipSuccess) return e;
+    return launch_qgemm_tile(format, qgemm_tile_choice(format, rows, cols, batch, cus), packed, rows, cols, X, batch, Y, s);
 }
 
 }  // namespace iflow

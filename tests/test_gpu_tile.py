@@ -5,12 +5,32 @@ that share K), rows whose outputs can and cannot be stored eight bytes at a time
 Reference: plain fp64 matrix product (torch) of the activations with iflow_dequant's fp16 weights, which other tests hold bit-exact
 to the oracle.  The kernel multiplies exactly those weights and accumulates in fp32, so what is left is one fp16 rounding of the output
 (2^-11 = 4.9e-4 of the value) and the fp32 sums (below 1e-4 at 13000 columns): 6e-4 of max(|y|, rms)."""
+import ctypes as C
+
 import pytest
 
 from paper_2401_08294_amd import synth
 from test_gpu_parity import NAMES, gpu, say  # noqa: F401
 
 pytestmark = pytest.mark.gpu
+
+
+
+def with_tile(torch, iflow, fmt, tile, packed, rows, cols, x, batch, y):
+    """The product through tile number `tile`, whichever the launcher would take."""
+    p = C.c_void_p
+    st = iflow.lib().iflow_internal_qgemm_with_tile(fmt, tile, p(packed.data_ptr()), C.c_int64(rows), C.c_int64(cols), p(x.data_ptr()), C.c_int64(batch),
+                                                    p(y.data_ptr()), p(torch.cuda.current_stream().cuda_stream))
+    assert st == iflow.OK, st
+
+
+def tile_shapes(iflow, fmt):
+    """Per tile: rows, vectors, wavefront groups that share K, chunks fetched at once, such runs in LDS, longest row."""
+    shapes, v = [], (C.c_int64 * 6)()
+    while iflow.lib().iflow_internal_qgemm_tile_shape(fmt, len(shapes), v):
+        shapes.append(tuple(v))
+    return shapes
+
 
 SHAPES = [  # rows, 64-column chunks, vectors                            tile (rows x vectors of a workgroup; wavefronts along K)
     (16625, 5, 673), (8200, 31, 1025), (16412, 3, 686),                  # 256 x 256
@@ -91,3 +111,42 @@ def test_infinity_in_the_last_columns(gpu, name):
         rms = torch.where(finite, ref, torch.zeros_like(ref)).square().mean(1, keepdim=True).sqrt()
         err = torch.where(finite, (got - ref).abs() / torch.maximum(ref.abs(), rms), torch.zeros_like(ref)).max().item()
         assert err <= 6e-4, f"{rows} x {cols}, {batch} vectors: {err:.2e}"
+
+
+@pytest.mark.parametrize("name", ["Q3H_B64", "Q8_B64", "Q5_B64", "Q2_B32"])
+def test_long_rows(gpu, name):
+    """Rows around the lengths where 32-bit offsets end: every tile that differs in its limit at exactly that limit with all its rows and vectors
+    (the largest offsets there are), the launcher's choice beyond the shorter limits, and passes of sixteen beyond the longest.  fp32 sums in steps of
+    sixteen columns: 2^-24 sqrt(2^26 / 16 / 2) = 9e-5 of the rms on top of the output's rounding, bound 1e-3."""
+    torch, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.BASE_SEED + 4600)
+    shapes = tile_shapes(iflow, fmt)
+    limits = {}
+    for tile, (rows, vectors, _, _, _, max_cols) in enumerate(shapes):
+        limits.setdefault((vectors, max_cols), (tile, rows))
+    cases = [(min(rows, 96), max_cols // 64 * 64, vectors, tile) for (vectors, max_cols), (tile, rows) in sorted(limits.items()) if max_cols <= 1 << 24]
+    cases += [(3, 1 << 22, 17, None), (3, (1 << 22) + 64, 17, None), (2, (1 << 24) + 64, 40, None), (1, 1 << 26, 33, None), (1, (1 << 26) + 64, 17, None)]
+    for rows, cols, batch, tile in cases:
+        say(f"[case] long rows {name} rows={rows} cols={cols} batch={batch} tile={tile}")
+        w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+        x = torch.empty((batch, cols), dtype=torch.float16, device="cuda").normal_(generator=g)
+        n = iflow.packed_bytes(fmt, rows, cols)
+        packed = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        iflow.quantize(fmt, w, rows, cols, packed, n)
+        del w
+        w16 = torch.empty((rows, cols), dtype=torch.float16, device="cuda")
+        iflow.dequant(fmt, packed, rows, cols, w16)
+        y = torch.full((batch, rows), float("nan"), dtype=torch.float16, device="cuda")
+        if tile is None:
+            iflow.qgemm(fmt, packed, rows, cols, x, batch, y)
+        else:
+            with_tile(torch, iflow, fmt, tile, packed, rows, cols, x, batch, y)
+        ref = torch.zeros((batch, rows), dtype=torch.float64, device="cuda")
+        for k in range(0, cols, 1 << 21):
+            ref += x[:, k:k + (1 << 21)].double() @ w16[:, k:k + (1 << 21)].double().T.contiguous()
+        # (the rms of all outputs: with a row or two a vector's own can be as small as its smallest value, and the sums' error does not shrink with it)
+        err = ((y.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean().sqrt())).max().item()
+        assert err <= 1e-3, f"{rows} x {cols}, {batch} vectors, tile {tile}: {err:.2e}"
+        del x, w16, packed, y, ref

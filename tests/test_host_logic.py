@@ -456,3 +456,25 @@ def test_forked_child_asks_the_runtime_again(monkeypatch):
             os._exit(code)
     assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
     assert iflow._stream(None) == 1234                         # the parent keeps its own
+
+
+def test_tiles_reach_as_far_as_their_offsets(iflow):
+    """17 and more vectors take the tiled product up to 2^26 columns, and never a tile whose byte offsets would leave 32 bits: of its vectors' activations, or of
+    a wavefront's (at most 96) rows of at most one byte a weight."""
+    L = iflow.lib()
+    choose = L.iflow_internal_qgemm_tile
+    choose.argtypes = [C.c_int, C.c_int64, C.c_int64, C.c_int64, C.c_int]
+    shape = (C.c_int64 * 6)()
+    for fmt in iflow.FORMATS.values():
+        for cols in [64, 4096, 1 << 22, (1 << 22) + 64, (1 << 23) + 64, 1 << 25, 1 << 26]:
+            for rows, batch in [(1, 17), (64, 33), (300, 500), (20000, 2000), (1 << 30, 256)]:
+                tile = choose(fmt, rows, cols, batch, 256)
+                assert tile >= 0 and L.iflow_internal_qgemm_tile_shape(fmt, tile, shape)
+                assert cols <= shape[5] and shape[1] * cols * 2 <= 1 << 32
+        assert choose(fmt, 1, (1 << 26) + 64, 17, 256) == -1
+        assert choose(fmt, 300, 4096, 16, 256) == -1
+        tile = 0
+        while L.iflow_internal_qgemm_tile_shape(fmt, tile, shape):
+            assert 2 * shape[1] * shape[5] <= 1 << 32 and min(96, shape[0]) * shape[5] <= 3 << 32
+            tile += 1
+        assert tile > 10

@@ -478,41 +478,45 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     return hipGetLastError();
 }
 
-// The tiles in use and what a launch of each costs in microseconds: start + rounds * (round + steps * step), rounds = workgroups per compute
-// unit, steps = chunks that one wavefront walks.  Fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000
-// vectors; by it the chosen tile is 0.7 % slower than the best of 33 in the mean.  A workgroup too many for the last round costs up to half of a
-// launch, so sizes in between are worth having (with nine tiles 6.5 %); eight wavefronts of 32 rows beat four of 64 where LDS holds
-// their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 281 -> 244; 4096 x 4096 x 512 32 -> 25).
+// The tiles in use and what a launch of each costs in microseconds: rounds * (round + steps * step), rounds = workgroups per compute unit, steps =
+// chunks that one wavefront walks.  `step` is fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000 vectors,
+// `round` (start, first copies, sums and stores) is the median of what rows of 64 to 1024 columns take beyond their steps.  On 200 random products that
+// no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is 0.14 % slower than the best
+// in the mean and 10 % at worst, on 64 to 1024 columns 1.5 % and 9 %.  (`round` fitted to the long rows too came out at 0.6 to 4.9 us and took
+// 256 x 160 for nearly everything below 256 columns, 13 % slower than the best: 131072 x 64, 3.5-bit, 33 vectors 9.6 us, now 8.8; 33 x 256, 512 vectors 8.6, now 5.1.)
+// A workgroup too many for the last round costs up to half of a
+// launch, so sizes in between are worth having (with nine tiles 6.5 % slower than the best of 33 in the mean); eight wavefronts of 32 rows beat four of 64 where LDS holds
+// their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 259 -> 244; 4096 x 4096 x 512 32 -> 25).
 // The choice depends on sizes, format and the number of compute units only, so a call always takes the same path on the same device.
-#define IFLOW_TILES(V) /* RT MB WR WK STAGES  start  round  step */ \
-    V(1, 8, 8, 1, 2, 0.00, 3.27, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
-    V(1, 7, 8, 1, 2, 0.00, 1.42, 1.38)    /* 256 x 224 (28672 rows x 2000 vectors: 1008 workgroups, four rounds (256 x 256: 3.5)) */ \
-    V(1, 6, 4, 2, 2, 0.00, 3.15, 1.40)    /* 128 x 192 */ \
-    V(1, 5, 8, 1, 2, 0.00, 0.55, 1.12)    /* 256 x 160 */ \
-    V(1, 4, 8, 1, 3, 0.00, 1.37, 0.93)    /* 256 x 128 */ \
-    V(1, 4, 4, 2, 2, 0.00, 2.04, 1.11)    /* 128 x 128 */ \
-    V(3, 4, 2, 2, 2, 0.00, 4.87, 1.65)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
-    V(1, 4, 3, 2, 2, 0.00, 2.85, 1.00)    /* 96 x 128 */ \
-    V(1, 3, 4, 2, 3, 0.00, 2.67, 0.91)    /* 128 x 96 */ \
-    V(1, 4, 2, 2, 3, 0.00, 3.28, 0.71)    /* 64 x 128 */ \
-    V(2, 2, 2, 2, 3, 0.62, 2.55, 0.80)    /* 128 x 64 */ \
-    V(3, 2, 1, 4, 2, 0.00, 4.79, 1.10)    /* 96 x 64 */ \
-    V(2, 3, 1, 4, 2, 0.00, 4.73, 0.93)    /* 64 x 96 */ \
-    V(2, 2, 1, 4, 2, 0.81, 3.12, 0.79)    /* 64 x 64 */ \
-    V(2, 1, 1, 4, 3, 1.38, 2.35, 0.60)    /* 64 x 32 */ \
-    V(1, 2, 1, 4, 3, 1.45, 2.22, 0.51)    /* 32 x 64 */ \
-    V(1, 1, 1, 8, 2, 1.50, 2.35, 0.66)    /* 32 x 32 */
+#define IFLOW_TILES(V) /* RT MB WR WK STAGES  round  step */ \
+    V(1, 8, 8, 1, 2, 5.12, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
+    V(1, 7, 8, 1, 2, 4.23, 1.38)    /* 256 x 224 (28672 rows x 2000 vectors: 1008 workgroups, four rounds (256 x 256: 3.5)) */ \
+    V(1, 6, 4, 2, 2, 4.55, 1.40)    /* 128 x 192 */ \
+    V(1, 5, 8, 1, 2, 3.71, 1.12)    /* 256 x 160 */ \
+    V(1, 4, 8, 1, 3, 3.59, 0.93)    /* 256 x 128 */ \
+    V(1, 4, 4, 2, 2, 3.39, 1.11)    /* 128 x 128 */ \
+    V(3, 4, 2, 2, 2, 6.05, 1.65)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
+    V(1, 4, 3, 2, 2, 3.61, 1.00)    /* 96 x 128 */ \
+    V(1, 3, 4, 2, 3, 3.54, 0.91)    /* 128 x 96 */ \
+    V(1, 4, 2, 2, 3, 3.83, 0.71)    /* 64 x 128 */ \
+    V(2, 2, 2, 2, 3, 3.66, 0.80)    /* 128 x 64 */ \
+    V(3, 2, 1, 4, 2, 5.47, 1.10)    /* 96 x 64 */ \
+    V(2, 3, 1, 4, 2, 5.31, 0.93)    /* 64 x 96 */ \
+    V(2, 2, 1, 4, 2, 4.03, 0.79)    /* 64 x 64 */ \
+    V(2, 1, 1, 4, 3, 3.18, 0.60)    /* 64 x 32 */ \
+    V(1, 2, 1, 4, 3, 2.72, 0.51)    /* 32 x 64 */ \
+    V(1, 1, 1, 8, 2, 3.00, 0.66)    /* 32 x 32 */
 
 // The cheapest tile's place in the list (-1: rows too long for every one).
 template <int F> static int tile_choice(int64_t rows, int64_t cols, int64_t batch, int cus)
 {
     int best = -1, i = 0;
     double best_us = 0;
-#define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) { \
+#define IFLOW_TILE_PRICE(RT, MB, WR, WK, STAGES, ROUND, STEP_US) { \
         constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES); \
         const int64_t wgs = ((rows + 32 * RT * WR - 1) / (32 * RT * WR)) * ((batch + 32 * MB - 1) / (32 * MB)); \
         const double rounds = (double)((wgs + cus - 1) / cus), steps = (double)tile_steps<WK, G>((int)(cols / 64), 0); \
-        const double us = START + rounds * (ROUND + steps * STEP_US); \
+        const double us = rounds * (ROUND + steps * STEP_US); \
         if (cols <= tile_max_cols(RT, MB) && (best < 0 || us < best_us)) { best = i; best_us = us; } \
         ++i; }
     IFLOW_TILES(IFLOW_TILE_PRICE)
@@ -524,7 +528,7 @@ template <int F>
 static hipError_t tile_launch(int tile, const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, hipStream_t s)
 {
     int i = 0;
-#define IFLOW_TILE_GO(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) \
+#define IFLOW_TILE_GO(RT, MB, WR, WK, STAGES, ROUND, STEP_US) \
     if (tile == i++) return tile_go<F, RT, MB, WR, WK, STAGES>(packed, rows, cols, X, batch, Y, s);
     IFLOW_TILES(IFLOW_TILE_GO)
 #undef IFLOW_TILE_GO
@@ -534,7 +538,7 @@ static hipError_t tile_launch(int tile, const void *packed, int64_t rows, int64_
 template <int F> static bool tile_shape(int tile, TileShape *shape)
 {
     int i = 0;
-#define IFLOW_TILE_SHAPE(RT, MB, WR, WK, STAGES, START, ROUND, STEP_US) \
+#define IFLOW_TILE_SHAPE(RT, MB, WR, WK, STAGES, ROUND, STEP_US) \
     if (tile == i++) { \
         constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES); \
         *shape = TileShape{32 * RT * WR, 32 * MB, WK, G, Parts<F, G>::BUFFERS, tile_max_cols(RT, MB)}; \

@@ -478,3 +478,22 @@ def test_tiles_reach_as_far_as_their_offsets(iflow):
             assert 2 * shape[1] * shape[5] <= 1 << 32 and min(96, shape[0]) * shape[5] <= 3 << 32
             tile += 1
         assert tile > 10
+
+
+def tile_of(iflow, fmt, rows, cols, batch, cus=256):
+    L = iflow.lib()
+    shape = (C.c_int64 * 6)()
+    tile = L.iflow_internal_qgemm_tile(C.c_int(fmt), C.c_int64(rows), C.c_int64(cols), C.c_int64(batch), C.c_int(cus))
+    assert tile >= 0 and L.iflow_internal_qgemm_tile_shape(C.c_int(fmt), C.c_int(tile), shape)
+    return int(shape[0]), int(shape[1]), int(shape[2])
+
+
+def test_short_rows_take_tiles_that_fit(iflow):
+    """Rows of a few chunks: a tile's own cost decides, not its steps.  Few rows and few vectors take a small tile, tall matrices one that reads each row once."""
+    for fmt in iflow.FORMATS.values():
+        for cols in (64, 128, 192, 256):
+            for rows, batch in [(33, 129), (64, 129), (33, 512), (64, 256), (100, 48)]:
+                tile = tile_of(iflow, fmt, rows, cols, batch)
+                assert tile[0] <= 64 and tile[1] <= 64, (fmt, rows, cols, batch, tile)
+            for batch in (33, 64):
+                assert tile_of(iflow, fmt, 131072, cols, batch)[:2] == (256, 128)

@@ -47,11 +47,13 @@ struct BlockAt {
 // ---- quantize: one lane per four consecutive weights, block/4 lanes per block ----------------------
 // Bound by memory: 4 bytes in and half a byte to nine eighths out per weight.  What kept it from that was arithmetic: five IEEE divisions and
 // a 64-bit division by the row length per lane.  Now a lane multiplies by the reciprocal of the stored scale and divides only
-// where the product lies so near to a rounding boundary that it could decide differently, and a workgroup has QUADS loads per lane in
-// flight.  11008 x 4096, us before -> after: 3.5-bit 62.5 -> 42.5 (4.8 TB/s), 8-bit 59.2 -> 43.0, 4-bit 52.4 -> 40.0, 2-bit 46.4 -> 35.5; a plain copy on
-// this card runs at 4.9 TB/s.
-constexpr int QUADS = 4;                                     // float4 loads per lane
-template <int F>
+// where the product lies so near to a rounding boundary that it could decide differently.  11008 x 4096, us before -> after: 3.5-bit
+// 61.3 -> 41.4 (4.4 TB/s read and written), 8-bit 49.8 -> 38.6, 4-bit (blocks of 32) 46.5 -> 37.5, 2-bit 46.0 -> 35.1.
+// QUADS: float4 loads per lane, all in flight at once.  Four where that leaves enough workgroups to fill the chip several times over, one
+// below, where more workgroups matter more than more loads in each (four / one, us: 0.5 million weights 3.7-4.0 / 2.7-2.8, 4 million 6.6-7.3 / 5.6-6.4,
+// 12 million 13.2-14.3 / 12.5-13.9; 16 million 15.8-17.2 / 16.3-17.5, 45 million 35.1-41.4 / 41.7-46.2).
+constexpr int64_t QUADS_MIN_WORKGROUPS = 3500;               // of four loads per lane: 14 million weights
+template <int F, int QUADS>
 __global__ __launch_bounds__(256) void quantize_kernel(const float4 *__restrict__ w, int64_t n_quads, int nbk,
                                                        uint8_t *__restrict__ packed, int64_t header_offset)
 {
@@ -265,8 +267,8 @@ __global__ __launch_bounds__(256) void read_kernel(const uint8_t *__restrict__ p
     }
 }
 
-template <int F>
-static hipError_t quantize_one(const float *w, int64_t rows, int64_t cols, void *packed, hipStream_t s)
+template <int F, int QUADS>
+static hipError_t quantize_go(const float *w, int64_t rows, int64_t cols, void *packed, hipStream_t s)
 {
     typedef Fmt<F> T;
     const int64_t n_quads = rows * cols / 4;
@@ -274,9 +276,15 @@ static hipError_t quantize_one(const float *w, int64_t rows, int64_t cols, void 
     const int64_t header_offset = rows * (cols / T::block) * (int64_t)T::code_bytes;
     const int64_t grid = (n_quads + 256 * QUADS - 1) / (256 * QUADS);
     if (grid > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(quantize_kernel<F>, dim3((unsigned)grid), dim3(256), 0, s,
+    hipLaunchKernelGGL((quantize_kernel<F, QUADS>), dim3((unsigned)grid), dim3(256), 0, s,
                        reinterpret_cast<const float4 *>(w), n_quads, nbk, static_cast<uint8_t *>(packed), header_offset);
     return hipGetLastError();
+}
+
+template <int F>
+static hipError_t quantize_one(const float *w, int64_t rows, int64_t cols, void *packed, hipStream_t s)
+{
+    return rows * cols / (256 * 4 * 4) >= QUADS_MIN_WORKGROUPS ? quantize_go<F, 4>(w, rows, cols, packed, s) : quantize_go<F, 1>(w, rows, cols, packed, s);
 }
 
 template <int F, bool LEVELS>

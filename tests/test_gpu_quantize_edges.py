@@ -66,3 +66,10 @@ def test_ranges_that_leave_fp16_and_fp32(gpu, orc, name):
     w[:, 8, 12] = nan
     w[:, 9, 13], w[:, 9, 14] = nan, inf
     check(gpu, orc, name, np.ascontiguousarray(w.reshape(3, -1)), "infinite and overflowing ranges")
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("rows,cols", [(3500, 4096), (3499, 4096), (57, 64 * 4097)])
+def test_one_and_four_loads_per_lane(gpu, orc, name, rows, cols):
+    """Both sides of the size (3500 workgroups of 4096 weights) from which a lane takes four times four weights, and ragged rows beyond it."""
+    check(gpu, orc, name, synth.weights(rows, cols, 0.02, synth.BASE_SEED + 5300 + rows), "loads per lane")

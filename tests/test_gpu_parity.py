@@ -155,8 +155,8 @@ def test_tall_and_thin(gpu, orc, name, batch):
     check_all(torch, iflow, orc, name, w, x, "tall-thin")
 
 
-# ---- a seeded sweep over shapes and batch sizes on both sides of every kernel-selection threshold (1 | 2 | 3..31 | 32..64 |
-#      65..; column counts that are and are not multiples of 64 for the 32-wide blocks) -----------------------------------------
+# ---- a seeded sweep over shapes and batch sizes on both sides of every kernel-selection threshold (1 | 2, for 8-bit formats 2..4 | up to 16 |
+#      17 and more; column counts that are and are not multiples of 64 for the 32-wide blocks) -----------------------------------
 def _sweep_cases():
     rng = np.random.default_rng(synth.BASE_SEED + 4242)
     batches = [1, 2, 3, 4, 5, 11, 12, 16, 17, 31, 32, 33, 64, 65, 130]
@@ -246,7 +246,7 @@ def test_odd_block_count_batches(gpu, orc, name, batch):
     check_all(torch, iflow, orc, name, w, x, "odd block count")
 
 
-# ---- large batches run on the matrix cores (128 x 64 tiles, 64-column chunks): ragged in every dimension ----
+# ---- 17 and more vectors run in tiles on the matrix cores (64-column chunks): ragged in every dimension ----
 @pytest.mark.parametrize("name", NAMES)
 @pytest.mark.parametrize("batch,rows,nchunks", [(32, 64, 1), (100, 200, 69), (512, 70, 3)])
 def test_large_batch_mfma(gpu, orc, name, batch, rows, nchunks):

@@ -73,3 +73,26 @@ def test_ranges_that_leave_fp16_and_fp32(gpu, orc, name):
 def test_one_and_four_loads_per_lane(gpu, orc, name, rows, cols):
     """Both sides of the size (3500 workgroups of 4096 weights) from which a lane takes four times four weights, and ragged rows beyond it."""
     check(gpu, orc, name, synth.weights(rows, cols, 0.02, synth.BASE_SEED + 5300 + rows), "loads per lane")
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_scales_on_fp16_ties(gpu, orc, name):
+    """The stored scale is (max - min) / L rounded to fp32 and then to fp16.  Ranges whose quotient lies exactly between two fp16 numbers: the corrected product the
+    kernel takes for the quotient is a hair off before its rounding to fp32, so a single rounding of it to fp16 would store the wrong neighbour of every other one (at
+    255, 63, 15 and 7 steps; 31, 10 and 3 come out exact)."""
+    _, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    block, top = iflow.format_block(fmt), iflow.format_levels(fmt) - 1
+    rng = np.random.default_rng(synth.BASE_SEED + 5400)
+    count = 16384
+    tie = (rng.integers(1024, 2048, count) * 2 + 1) * np.exp2(rng.integers(-14, 4, count) - 11.0)
+    span = (tie * top).astype(np.float32)                      # exact: 12 and at most 8 bits
+    inverse = np.float32(1) / np.float32(top)
+    product = span * inverse
+    exact = (span.astype(np.longdouble) - product.astype(np.longdouble) * top) * np.longdouble(inverse) + product.astype(np.longdouble)
+    even = tie.astype(np.float16).astype(np.float64)
+    assert top in (31, 10, 3) or (((exact < tie) & (even > tie)) | ((exact > tie) & (even < tie))).sum() > count // 5
+    w = np.zeros((count, block), np.float32)                   # minimum zero: the range is the maximum
+    w[:, 1] = span
+    w[:, 2:] = rng.random((count, block - 2), np.float32) * span[:, None]
+    check(gpu, orc, name, w.reshape(-1, 64 * block), "scales on fp16 ties")

@@ -14,8 +14,9 @@ constexpr int64_t IFLOW_SMALL_MFMA_MIN_BATCH = 3, IFLOW_SMALL_MFMA_MIN_BATCH_Q8 
 thread_local int g_last_hip_error = 0;
 
 // From this many vectors on the tiled matrix-core kernel is faster than passes of sixteen through the streaming one, at every size
-// measured (1024 x 1024 to 8192 x 8192, all formats: 17 vectors on 4096 x 4096, 3.5-bit, 8.2 us against 11.3 in two passes; at sixteen
-// and fewer one pass is, 6.1 against 8.3).
+// measured (ten shapes from 64 x 28672 and 1024 x 1024 to 28672 x 8192, 8192 x 28672 and 70000 x 4160 in five formats; us, 17 vectors, tiles / two passes: 4096 x
+// 4096, 3.5-bit 8.1 / 9.6, 28672 x 8192, 3.5-bit 48.7 / 55.7 and 8-bit 61.8 / 89.4, closest 11008 x 4096, 3.5-bit 13.9 / 14.8); at sixteen and
+// fewer one pass is (4096 x 4096, 3.5-bit 6.1 against 8.1).
 constexpr int64_t IFLOW_TILE_MIN_BATCH = 17;
 
 iflow_status_t device_status(hipError_t e)

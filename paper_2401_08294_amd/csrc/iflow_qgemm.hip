@@ -11,11 +11,13 @@
 //   - The operands of a k-step of 16 columns are read and decoded while the matrix instructions of the k-step before run.
 //   - Which lane holds which k of a chunk is free as long as both operands agree: lane half h takes columns 32 h .. 32 h + 31,
 //     so that a lane's weights are 32 consecutive ones of one row.
-// What bounds it: for large batches the power limit (a loop of nothing but these matrix instructions on random data runs at 1.5 to 1.8
-// PFLOP/s, 1.5 to 1.8 GHz) and the decode next to it, which is why the largest tile has 256 vectors per decoded weight; for small ones the
-// activations, which every workgroup reads from L2 (1 MB for 128 vectors of 4096 columns, about 100 KB of LDS to hold what is on its way).
-// Measured (before: 128 x 64 tiles with both operands decoded or copied into LDS, passes of sixteen below 32 vectors): 11008 x 4096 3.5-bit, 512
-// vectors 84.5 -> 55.5 us (832 TFLOP/s); 28672 x 8192 4-bit, 2000 vectors 1481 -> 845 us (1112 TFLOP/s); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.9 us.
+// What bounds it, by counters: at 2000 vectors (28672 x 8192, 4-bit) the matrix cores are busy 64 % of the cycles of a launch that runs at 1.4 GHz - the power
+// limit, a loop of nothing but these instructions on random data runs at 1.5 to 1.8 - next to a decode that issues 28 % of them, which is why
+// the largest tile has 256 vectors per decoded weight; at 512 (11008 x 4096, 3.5-bit) both are busy a third of the time, one wavefront per SIMD; at 33
+// (4096 x 11008, 8-bit) wavefronts wait for their copies.
+// Measured, us (before: 128 x 64 tiles with both operands decoded or copied into LDS, passes of sixteen below 32 vectors), one matrix again and again:
+// 11008 x 4096 3.5-bit, 512 vectors 84.4 -> 55.7 (830 TFLOP/s; over a ring of matrices beyond the caches 58 to 61); 28672 x 8192 4-bit, 2000 vectors 1491 -> 844 (1113
+// TFLOP/s; 833 to 890 by machine); 4096 x 11008 8-bit, 33 vectors 49.7 -> 17.4 (ring 23); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.0 (ring 9.6).
 #include "iflow_common.h"
 
 namespace iflow {
@@ -238,8 +240,8 @@ template <int F, int G> constexpr int tile_lds_bytes(int rt, int mb, int wr, int
 {
     return stages * wk * mb * 4096 + wr * wk * rt * Parts<F, G>::BUFFERS * Parts<F, G>::BYTES;
 }
-// Chunks fetched at once: 64 bytes of a row, or 128 where the 8-bit formats find room (28672 x 8192, 512 vectors 281 -> 259 us: a 64-byte
-// request fetches half a line from memory).
+// Chunks fetched at once: 64 bytes of a row, or 128 where the 8-bit formats find room (28672 x 8192, 512 vectors 281 -> 259 us, then 244 with eight
+// wavefronts instead of four: a 64-byte request fetches half a line from memory).
 template <int F> constexpr int tile_group(int rt, int mb, int wr, int wk, int stages)
 {
     typedef Parts<F> P;
@@ -478,7 +480,7 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     return hipGetLastError();
 }
 
-// The tiles in use and what a launch of each costs in microseconds: rounds * (round + steps * step), rounds = workgroups per compute unit, steps =
+// The tiles in use and what a launch of each costs in microseconds, for every format: rounds * (round + steps * step), rounds = workgroups per compute unit, steps =
 // chunks that one wavefront walks.  `step` is fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000 vectors,
 // `round` (start, first copies, sums and stores) is the median of what rows of 64 to 1024 columns take beyond their steps.  On 200 random products that
 // no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is 0.14 % slower than the best
@@ -486,7 +488,7 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 // 256 x 160 for nearly everything below 256 columns, 13 % slower than the best: 131072 x 64, 3.5-bit, 33 vectors 9.6 us, now 8.8; 33 x 256, 512 vectors 8.6, now 5.1.)
 // A workgroup too many for the last round costs up to half of a
 // launch, so sizes in between are worth having (with nine tiles 6.5 % slower than the best of 33 in the mean); eight wavefronts of 32 rows beat four of 64 where LDS holds
-// their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 259 -> 244; 4096 x 4096 x 512 32 -> 25).
+// their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 259 -> 244, in addition to the longer requests; 4096 x 4096 x 512 32 -> 25).
 // The choice depends on sizes, format and the number of compute units only, so a call always takes the same path on the same device.
 #define IFLOW_TILES(V) /* RT MB WR WK STAGES  round  step */ \
     V(1, 8, 8, 1, 2, 5.12, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \

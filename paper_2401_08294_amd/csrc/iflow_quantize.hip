@@ -48,7 +48,7 @@ struct BlockAt {
 // Bound by memory: 4 bytes in and half a byte to nine eighths out per weight.  What kept it from that was arithmetic: five IEEE divisions and
 // a 64-bit division by the row length per lane.  Now a lane multiplies by the reciprocal of the stored scale and divides only
 // where the product lies so near to a rounding boundary that it could decide differently.  11008 x 4096, us before -> after: 3.5-bit
-// 61.3 -> 41.4 (4.4 TB/s read and written), 8-bit 49.8 -> 38.6, 4-bit (blocks of 32) 46.5 -> 37.5, 2-bit 46.0 -> 35.1.
+// 61.3 -> 41.4 (4.9 TB/s read and written), 8-bit 49.8 -> 38.6, 4-bit (blocks of 32) 46.5 -> 37.5, 2-bit 46.0 -> 35.1.
 // QUADS: float4 loads per lane, all in flight at once.  Four where that leaves enough workgroups to fill the chip several times over, one
 // below, where more workgroups matter more than more loads in each (four / one, us: 0.5 million weights 3.7-4.0 / 2.7-2.8, 4 million 6.6-7.3 / 5.6-6.4,
 // 12 million 13.2-14.3 / 12.5-13.9; 16 million 15.8-17.2 / 16.3-17.5, 45 million 35.1-41.4 / 41.7-46.2).

@@ -59,7 +59,9 @@ struct SmallOps {
     float eps;
 };
 
-template <int F, int S, int XOP>
+// UPPER: more than eight vectors.  A kernel of its own for either case, because on a small matrix the second half's loads under a branch show (us, a
+// branch / a kernel for each: 1024 x 1024 4-bit, blocks of 32, 9 vectors 5.55 / 5.32, 8 vectors 5.15 / 4.80; 4096 x 11008 3.5-bit, 9 vectors 13.4 / 12.7).
+template <int F, int S, int XOP, bool UPPER>
 __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                 uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                 int64_t header_offset, int group0, int ngroups, const SmallOps ops)
@@ -69,6 +71,8 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     constexpr int HPL = 64 / T::block;                        // block headers per lane (1, or 2 for the 32-wide formats)
     constexpr int WA = Planes<KIND>::WA, WB = Planes<KIND>::WB;       // bit-plane formats: a lane's 64 weights take 2 WA + 2 WB words
     constexpr int NWORDS = kind_has_planes(KIND) ? 2 * WA + 2 * WB : KIND == KIND_Q8 ? 16 : 8;
+    // kernels that would keep some of the staging's and the sums' addresses in scratch memory all through the rounds
+    constexpr bool TIGHT = KIND == KIND_Q8 || XOP == IFLOW_X_RMS_GAIN || XOP == IFLOW_X_SILU_MUL;
     extern __shared__ __align__(16) uint8_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -213,20 +217,22 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     // activations of strip t: batch rows x the wavefront's 256 columns -> lane (j, g) holds row j, columns 64g .. 64g+63
     auto stage = [&](int t) {
         int ln = lane;
-        asm volatile("" : "+v"(ln));                          // (addresses worked out per strip: the registers are needed in the rounds)
+        if constexpr (TIGHT) asm volatile("" : "+v"(ln));     // (addresses worked out per strip: the registers are needed in the rounds)
         const int kb = t * 64 + wave * 4 + g;
         const bool live = kb < nbk64;                         // ragged last strip: dead lanes add nothing (their activations are zeroed)
         int c = (t * 64 + wave * 4) * 64 + (ln & 31) * 8;
         if (c >= cols) c = 0;                                 // columns past the end: any valid address, the values are masked below
-        const bool upper = batch > 8;                         // (uniform)
+        // (uniform; where a module's arithmetic comes between the loads and the turn a constant is no better: silu up to 7 % slower, rms with sixteen
+        // vectors up to 3 %)
+        const bool upper = XOP == IFLOW_X_SILU_MUL || (XOP == IFLOW_X_RMS_GAIN && UPPER) ? batch > 8 : UPPER;
         u32x4_t va[4], vb[4] = {};                             // load q: batch rows 2q and 2q+1 (vb: 8+2q, 9+2q), 512 bytes each, lane by lane
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             va[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(2 * q + (ln >> 5), batch - 1) * cols + c);
         if (upper)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            vb[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(8 + 2 * q + (ln >> 5), batch - 1) * cols + c);
+            for (int q = 0; q < 4; ++q)
+                vb[q] = *reinterpret_cast<const u32x4_t *>(X + (int64_t)min(8 + 2 * q + (ln >> 5), batch - 1) * cols + c);
         if constexpr (XOP == IFLOW_X_RMS_GAIN) {
             // the lane's eight columns of every vector it loaded: x^2 summed (columns past the end and dead column groups
             // were redirected to column 0: they do not count), then v = fp16(x g), an exact product rounded once
@@ -240,9 +246,11 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     sa = __builtin_amdgcn_fdot2(as_h2(xa[e]), as_h2(xa[e]), sa, false);
-                    sb = __builtin_amdgcn_fdot2(as_h2(xb[e]), as_h2(xb[e]), sb, false);
                     xa[e] = as_u32(as_h2(xa[e]) * as_h2(gw[e]));
-                    xb[e] = as_u32(as_h2(xb[e]) * as_h2(gw[e]));
+                    if constexpr (UPPER) {                    // (of zeros where there are no more than eight vectors)
+                        sb = __builtin_amdgcn_fdot2(as_h2(xb[e]), as_h2(xb[e]), sb, false);
+                        xb[e] = as_u32(as_h2(xb[e]) * as_h2(gw[e]));
+                    }
                 }
                 ssq[q] += counts ? sa : 0.f;
                 ssq[4 + q] += counts ? sb : 0.f;
@@ -321,7 +329,7 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     // wavefronts run freely.  1024 threads: round tid / 256 of the batch, vector tid / 16 % 16, row tid % 16 of the round's sixteen.
     auto finish = [&](int t, int r0, int slots, bool more) {
         int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));                         // (worked out here each time: the registers are needed in the rounds)
+        if constexpr (TIGHT) asm volatile("" : "+v"(tid));    // (worked out here each time: the registers are needed in the rounds)
         const int rl = tid >> 8, b = (tid >> 4) & 15, row16 = tid & 15;
         const int rr = (first + (r0 + rl) * (int)gridDim.x) * 16 + row16;
         const bool stores = rl < slots && rr < rows && b < batch && t + 1 == nstrips;
@@ -406,24 +414,24 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     }
 }
 
-template <int F, int S>
+template <int F, int S, bool UPPER>
 __global__ __launch_bounds__(1024) void gemm_small_kernel(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                           uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                           int64_t header_offset, int group0, int ngroups)
 {
-    gemm_small_body<F, S, -1>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, SmallOps{});
+    gemm_small_body<F, S, -1, UPPER>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, SmallOps{});
 }
 
-template <int F, int S, int XOP>
+template <int F, int S, int XOP, bool UPPER>
 __global__ __launch_bounds__(1024) void gemm_small_fused_kernel(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                                 uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                                 int64_t header_offset, int group0, int ngroups, const SmallOps ops)
 {
-    gemm_small_body<F, S, XOP>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, ops);
+    gemm_small_body<F, S, XOP, UPPER>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, ops);
 }
 
-template <int F, int XOP>
-static hipError_t small_launch(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
+template <int F, int XOP, bool UPPER>
+static hipError_t small_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
                                hipStream_t s)
 {
     typedef Fmt<F> T;
@@ -433,9 +441,9 @@ static hipError_t small_launch(const void *packed, int64_t rows, int64_t cols, c
     int cus = 0;
     hipError_t e0 = once_per_device(pd, &cus, [] {
         if constexpr (XOP < 0)
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_kernel<F, S>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_kernel<F, S, UPPER>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         else
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_fused_kernel<F, S, XOP>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_fused_kernel<F, S, XOP, UPPER>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (e0 != hipSuccess) return e0;
     const int nbk64 = (int)(cols / 64);
@@ -449,17 +457,25 @@ static hipError_t small_launch(const void *packed, int64_t rows, int64_t cols, c
         const int64_t g1 = g0 + per_launch < ngroups ? g0 + per_launch : ngroups;
         const int64_t grid = g1 - g0 < cus ? g1 - g0 : cus;
         if constexpr (XOP < 0)
-            hipLaunchKernelGGL((gemm_small_kernel<F, S>), dim3((unsigned)grid), dim3(1024), LDS, s,
+            hipLaunchKernelGGL((gemm_small_kernel<F, S, UPPER>), dim3((unsigned)grid), dim3(1024), LDS, s,
                                static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk64, nstrips, header_offset,
                                (int)g0, (int)g1);
         else
-            hipLaunchKernelGGL((gemm_small_fused_kernel<F, S, XOP>), dim3((unsigned)grid), dim3(1024), LDS, s,
+            hipLaunchKernelGGL((gemm_small_fused_kernel<F, S, XOP, UPPER>), dim3((unsigned)grid), dim3(1024), LDS, s,
                                static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk64, nstrips, header_offset,
                                (int)g0, (int)g1, ops);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int F, int XOP>
+static hipError_t small_launch(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
+                               hipStream_t s)
+{
+    if constexpr (XOP == IFLOW_X_SILU_MUL) return small_go<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s);
+    return batch > 8 ? small_go<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s) : small_go<F, XOP, false>(packed, rows, cols, X, batch, Y, ops, s);
 }
 
 hipError_t launch_qgemm_small(int format, const void *packed, int64_t rows, int64_t cols,

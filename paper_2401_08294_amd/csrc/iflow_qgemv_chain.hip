@@ -796,6 +796,17 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
         }
     };
 
+    // The lines of the plan that the requests will look up: the records of phases p and p + 1 and of four matrices from m on (all in bounds), read
+    // through the scalar cache while the wavefront has a wait in front of it anyway.  A segment change in the step loop is a chain of three to four
+    // dependent scalar loads, each a trip to L2 where nobody has read the line before.  Whole decode steps of the 7B shape at 1000 positions, us per
+    // layer, before -> after: 3.5-bit 34.0 -> 33.0, 4-bit 39.5 -> 38.9, 8-bit 51.9 -> 51.8; one phase ahead instead of two 0.2 to 0.3 less; in front
+    // of the attention phases too: 33.6.
+    auto plan_lines = [&](int p, int m) __attribute__((always_inline)) {
+        const int p0 = min(p, nphases - 1), p1 = min(p + 1, nphases - 1), last = hd->nmatrices - 1;
+        return a.ph[p0].first + a.ph[p1].first + a.ops[p0].x_op + a.ops[p1].x_op + a.mat[min(m, last)].rows + a.mat[min(m + 1, last)].rows +
+               a.mat[min(m + 2, last)].rows + a.mat[min(m + 3, last)].rows;
+    };
+
     // ---- activations of a phase into LDS, in decode order ---------------------------------------------------
     // Chunk c = (strip ts, block blk, quarter qd), qd fastest: 16 activations that feed decode slots 4qd..4qd+3 of
     // lane blk.  n[k] holds the pair (x[2k], x[2k+1]) of the chunk.
@@ -998,6 +1009,7 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                     }
                 }
             }
+            const int lines = plan_lines(p + 1, ph.first + ph.count);
             float res0 = 0.f, res1 = 0.f;
             int done = 0;                                      // pairs of rows summed so far
             // A tagged residual is read here for the first time, together with the phase's activations: its producer is an
@@ -1137,6 +1149,7 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                 if (lane == 0) sq_slot[wave] = wsum;
                 sumsq = 0.f;
             }
+            asm volatile("" ::"s"(lines));                     // (read, as far as the compiler knows: not needed before here)
             CHAIN_MARK(p, wave < 8 ? wave : 15);               // this wavefront's share of the activations is staged
             __syncthreads();
             if (wave == 0) CHAIN_MARK(p, 8);                   // all of them are

@@ -124,7 +124,7 @@ struct ChainHeader {
 // One decode step of grouped-query attention inside the launch (section "Grouped-query attention"; Section 5's Infer() runs
 // it between the q/k/v products and the output projection), head dimension 128, with the rotary position embedding of the
 // step's query and key and the step's append to the key/value cache (what iflow_rope_append and iflow_attn_decode do as
-// launches of their own).  It takes two phases.  Phase "part": workgroup (kv head j, range sp) rotates the group's queries,
+// launches of their own).  It takes two phases.  Phase "part": workgroup (kv head j, two heads of its group, range sp) rotates the queries,
 // walks its range of cached positions with a streaming softmax and leaves one partial state (maximum, sum, 128 weighted value
 // sums) per query head in the workspace, as 64-bit words (fp32 bits, launch tag); the workgroup whose range holds the step's
 // own position rotates the new key, uses it and the new value from registers and writes both into the caches.  Phase "merge":
@@ -304,19 +304,22 @@ __device__ __forceinline__ uint32_t chain_rope_pair(uint32_t own, uint32_t other
     return as_u32(rv);
 }
 
-// Phase "part" for R of the query heads of a key/value head's group, heads r0 .. r0 + R - 1 of the group (a group larger than
-// two heads takes several passes over its range).  lds: (4 * CHAIN_WAVES_ATTN) * 130 floats for the running states, and behind
+// Phase "part" of one item = (key/value head, R of the query heads of its group, range of positions).  A group's pairs of heads are
+// workgroups of their own, with as many ranges less: a workgroup walking its range once per pair took, us per layer of a whole step, 8 heads
+// on one key/value head, 410 positions, 8-bit 39.5, now 28.3; 32 on 8, 700 positions, 4-bit 41.6, now 36.7; 16 on 4, 1239 positions, 3.5-bit
+// 32.2, now 25.1 (pairs of one range read the same keys and values side by side, so from L2).  lds: (4 * CHAIN_WAVES_ATTN) * 130 floats for the running states, and behind
 // them CHAIN_ATTN_STAGE_BYTES for the step's rotated queries, rotated key and value.
 constexpr int CHAIN_ATTN_STATE_BYTES = 4 * CHAIN_WAVES_ATTN * 130 * 4, CHAIN_ATTN_STAGE_BYTES = 64 * 16;
 template <int R>
 __device__ __forceinline__ void chain_attn_part(const ChainAttn &at, uint32_t *ws, float *lds, const double2 *table, uint32_t tag, int position,
-                                                int wg, int wave, int lane, int r0, bool &failed, uint32_t *marks = nullptr)
+                                                int item, int wave, int lane, bool &failed, uint32_t *marks = nullptr)
 {
     const int group = at.n_heads / at.n_kv_heads;
     constexpr int NST = 4 * CHAIN_WAVES_ATTN;                       // (the LDS area holds up to this many states of 128 sums; R per wavefront are used)
     const int nsplit = at.nsplit;
-    if (wg >= at.n_kv_heads * nsplit) return;                  // (uniform over the workgroup)
-    const int j = wg / nsplit, sp = wg - j * nsplit;
+    const int pieces = R == 1 ? 1 : group / R;                 // of a group's heads
+    const int unit = item / nsplit, sp = item - unit * nsplit;
+    const int j = R == 1 ? unit : unit / pieces, r0 = R == 1 ? 0 : (unit - j * pieces) * R;       // heads r0 .. r0 + R - 1 of the group
     const int seq_len = position + 1;
     const int chunk = ((seq_len + nsplit - 1) / nsplit + 15) & ~15;
     const int t_begin = sp * chunk, t_end = min(seq_len, t_begin + chunk);     // may be empty
@@ -496,64 +499,76 @@ __device__ __forceinline__ void chain_attn_part(const ChainAttn &at, uint32_t *w
     __syncthreads();                                           // the states in LDS are no longer needed
 }
 
-// Phase "merge": a workgroup takes a contiguous piece of the n_heads * 128 outputs (head, component).  One thread per (range,
-// output) reads that range's partial state (re-reading until it carries the launch's tag) and leaves it in LDS - all ranges at
-// once, one memory latency - then one thread per output merges the ranges in order and publishes the output: the plain fp16
-// value and the tagged word a later phase stages from.  lds: nsplit * per_wg * 3 floats.
+// Phase "merge": a workgroup takes a contiguous piece of the n_heads * 128 outputs (head, component).  A lane reads one output's partial
+// state of one range (re-reading until it carries the launch's tag) - all ranges at once, one memory latency - and the ranges are merged
+// in a tree: across the lanes of a wavefront, then across the wavefronts through LDS.  One thread per output publishes it: the plain fp16
+// value and the tagged word a later phase stages from.  What bounds it is the trip of the partial states across the chip; one thread walking over
+// the ranges added up to 3 us to that, us per layer of a whole step, before -> after: 8 heads on one key/value head (64 ranges) 28.0 -> 22.8, 16
+// on 8 (32) 28.6 -> 26.4, 32 on 32 at the 7B shape (8) 33.3 -> 33.0.  lds: 3 floats per wavefront and output, 64 outputs at a time.
 __device__ __forceinline__ int chain_attn_merge_per_wg(int n_heads, int nwg)
 {
     return ((n_heads * 128 + nwg - 1) / nwg + 1) & ~1;       // (even, so that a workgroup writes whole pairs)
+}
+// (m, l, o) <- the merge of two states; a state that has seen no position has m = -inf, l = o = 0
+__device__ __forceinline__ void chain_attn_join(float &m, float &l, float &o, float m2, float l2, float o2)
+{
+    const float mx = fmaxf(m, m2);
+    const bool none = mx == -INFINITY;
+    const float f1 = none ? 1.0f : __builtin_amdgcn_exp2f(m - mx), f2 = none ? 1.0f : __builtin_amdgcn_exp2f(m2 - mx);
+    l = l * f1 + l2 * f2;
+    o = o * f1 + o2 * f2;
+    m = mx;
 }
 __device__ __forceinline__ void chain_attn_merge(const ChainAttn &at, uint32_t *ws, float *lds, uint32_t tag, int wg, int nwg, int tid, bool &failed)
 {
     const int total = at.n_heads * 128;
     const int per_wg = chain_attn_merge_per_wg(at.n_heads, nwg);
-    const int o_base = wg * per_wg, n_here = min(per_wg, total - o_base);
+    const int n_here = min(per_wg, total - wg * per_wg);
     if (n_here <= 0) return;                                   // (uniform over the workgroup)
     const uint64_t *parts = reinterpret_cast<const uint64_t *>(ws + at.part_word);
-    const int nsplit = at.nsplit;
-    for (int idx = tid; idx < nsplit * n_here; idx += 64 * CHAIN_WAVES_ATTN) {
-        const int i = idx / n_here, ol = idx - i * n_here, o = o_base + ol;
-        const uint64_t *src = parts + ((int64_t)(o >> 7) * nsplit + i) * 130;
-        uint64_t wo, wm, wl;
-        int budget = failed ? 1 : CHAIN_POLL_BUDGET;
-        for (;;) {
-            wo = __hip_atomic_load(src + (o & 127), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wm = __hip_atomic_load(src + 128, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            wl = __hip_atomic_load(src + 129, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)(wo >> 32) == tag && (uint32_t)(wm >> 32) == tag && (uint32_t)(wl >> 32) == tag) break;
-            if (--budget <= 0) {
-                failed = true;
-                __hip_atomic_store(ws + CHAIN_WS_ERROR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(CHAIN_POLL_SLEEP);
-        }
-        float *dst = lds + (i * per_wg + ol) * 3;
-        dst[0] = __builtin_bit_cast(float, (uint32_t)wo);
-        dst[1] = __builtin_bit_cast(float, (uint32_t)wm);
-        dst[2] = __builtin_bit_cast(float, (uint32_t)wl);
-    }
-    __syncthreads();
-    if (tid < n_here) {
+    const int nsplit = at.nsplit, lane = tid & 63, wave = tid >> 6;
+#pragma unroll 1
+    for (int c0 = 0; c0 < n_here; c0 += 64) {
+        const int o_base = wg * per_wg + c0, n = min(64, n_here - c0);
+        const int width = n <= 1 ? 0 : 32 - __builtin_clz(n - 1);                 // outputs side by side in a wavefront: 2^width >= n
+        const int per_wave = 64 >> width;                      // ranges of a wavefront
+        const int ol = lane & ((1 << width) - 1), o = o_base + min(ol, n - 1);
         float M = -INFINITY, L = 0.f, O = 0.f;
-        for (int i = 0; i < nsplit; ++i) {
-            const float *st = lds + (i * per_wg + tid) * 3;
-            const float oi = st[0], mi = st[1], li = st[2];
-            const float m_new = fmaxf(M, mi);
-            if (m_new != -INFINITY) {                          // (ranges in order: the first non-empty one sets the maximum)
-                const float keep = __builtin_amdgcn_exp2f(M - m_new), f = __builtin_amdgcn_exp2f(mi - m_new);
-                L = L * keep + li * f;
-                O = O * keep + oi * f;
-                M = m_new;
+        for (int i = wave * per_wave + (lane >> width); i < nsplit; i += CHAIN_WAVES_ATTN * per_wave) {
+            const uint64_t *src = parts + ((int64_t)(o >> 7) * nsplit + i) * 130;
+            uint64_t wo, wm, wl;
+            int budget = failed ? 1 : CHAIN_POLL_BUDGET;
+            for (;;) {
+                wo = __hip_atomic_load(src + (o & 127), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                wm = __hip_atomic_load(src + 128, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                wl = __hip_atomic_load(src + 129, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((uint32_t)(wo >> 32) == tag && (uint32_t)(wm >> 32) == tag && (uint32_t)(wl >> 32) == tag) break;
+                if (--budget <= 0) {
+                    failed = true;
+                    __hip_atomic_store(ws + CHAIN_WS_ERROR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(CHAIN_POLL_SLEEP);
             }
+            chain_attn_join(M, L, O, __builtin_bit_cast(float, (uint32_t)wm), __builtin_bit_cast(float, (uint32_t)wl),
+                            __builtin_bit_cast(float, (uint32_t)wo));
         }
-        const int o = o_base + tid;
-        const uint32_t h = as_u16((half_t)(O / L));
-        *global_ptr<uint16_t>(at.out + o) = (uint16_t)h;
-        __hip_atomic_store(ws + at.out_tag_word + chain_tag_word(o), h | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int d = 1 << width; d < 64; d *= 2) chain_attn_join(M, L, O, __shfl_xor(M, d), __shfl_xor(L, d), __shfl_xor(O, d));
+        float *mine = lds + (wave * 64 + ol) * 3;
+        if (lane < n) { mine[0] = M; mine[1] = L; mine[2] = O; }
+        __syncthreads();
+        if (tid < n) {                                         // (lane tid of wavefront 0: its own state is the first)
+            const int waves = min(CHAIN_WAVES_ATTN, (nsplit + per_wave - 1) / per_wave);
+            for (int w = 1; w < waves; ++w) {
+                const float *st = lds + (w * 64 + tid) * 3;
+                chain_attn_join(M, L, O, st[0], st[1], st[2]);
+            }
+            const uint32_t h = as_u16((half_t)(O / L));
+            *global_ptr<uint16_t>(at.out + o_base + tid) = (uint16_t)h;
+            __hip_atomic_store(ws + at.out_tag_word + chain_tag_word(o_base + tid), h | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();                                       // the states in LDS are no longer needed
     }
-    __syncthreads();                                           // the states in LDS are no longer needed
 }
 
 // ATTN: the fused variant that also knows the two attention phases (a launch without them runs the code without them: the
@@ -964,11 +979,11 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                 uint32_t *const marks = nullptr;
 #endif
                 if (group == 1) {
-                    chain_attn_part<1>(at, ws, scratch, rope_table, tag, position, wg, wave, lane, 0, failed, marks);
-                } else {                                       // (even by the plan's check)
+                    if (wg < at.n_heads * at.nsplit) chain_attn_part<1>(at, ws, scratch, rope_table, tag, position, wg, wave, lane, failed, marks);
+                } else {                                       // (even by the plan's check; more pairs than workgroups: several passes)
 #pragma unroll 1
-                    for (int r0 = 0; r0 < group; r0 += 2)
-                        chain_attn_part<2>(at, ws, scratch, rope_table, tag, position, wg, wave, lane, r0, failed);
+                    for (int item = wg; item < (at.n_heads / 2) * at.nsplit; item += (int)gridDim.x)
+                        chain_attn_part<2>(at, ws, scratch, rope_table, tag, position, item, wave, lane, failed, marks);
                 }
                 CHAIN_MARK(p, 3 + (wave == 0 ? 0 : 8));           // (wavefront 0: slot 3) the partial states are written
                 chain_attn_merge(at, ws, scratch, tag, wg, (int)gridDim.x, tid, failed);
@@ -1323,17 +1338,22 @@ size_t chain_plan_bytes(int nphases, int nmatrices, int nattn)
            (size_t)nattn * sizeof(ChainAttn);
 }
 
-// position ranges per key/value head of an attention inside the launch: about one workgroup per (head, range)
-static int chain_attn_splits(int n_kv_heads, int grid)
+// position ranges of an attention inside the launch: about one workgroup per (unit, range), a unit being a pair of query heads (one where
+// every query head has its own key/value head)
+static int chain_attn_ranges(int units, int grid)
 {
-    const int n = grid / n_kv_heads;
+    const int n = grid / units;
     return n < 1 ? 1 : n > 64 ? 64 : n;
+}
+static int chain_attn_splits(int n_heads, int n_kv_heads, int grid)
+{
+    return chain_attn_ranges(n_heads == n_kv_heads ? n_heads : (n_heads + 1) / 2, grid);
 }
 
 // the partial states of one attention: 64-bit words [head][range][130]
 size_t chain_attn_workspace_bytes(int n_heads, int n_kv_heads, int grid)
 {
-    return (size_t)n_heads * chain_attn_splits(n_kv_heads, grid) * 130 * 8;
+    return (size_t)n_heads * chain_attn_splits(n_heads, n_kv_heads, grid) * 130 * 8;
 }
 
 // Dynamic LDS of a launch: the staged activations of the widest phase (+ the shares of sum x^2) or the attention's running
@@ -1446,11 +1466,12 @@ bool chain_build_plan(const ChainSpec &c, int grid, std::vector<uint8_t> &out)
                 at.v_tag_word = as.v_src >= 0 ? mats[as.v_src].tag_word : 0;
                 at.k_cache = as.k_cache; at.v_cache = as.v_cache; at.out = c.y[m];
                 at.out_tag_word = mats[m].tag_word;
-                at.n_heads = as.n_heads; at.n_kv_heads = as.n_kv_heads; at.nsplit = chain_attn_splits(as.n_kv_heads, grid);
-                if (as.n_kv_heads * at.nsplit > grid) return false;
-                // the second half's LDS: a state per (range, output of the workgroup); one thread per output
-                const int per_wg = ((as.n_heads * 128 + grid - 1) / grid + 1) & ~1;
-                if (per_wg > 64 * CHAIN_WAVES_ATTN || at.nsplit * per_wg * 3 > 4 * CHAIN_WAVES_ATTN * 130) return false;
+                at.n_heads = as.n_heads; at.n_kv_heads = as.n_kv_heads; at.nsplit = chain_attn_splits(as.n_heads, as.n_kv_heads, grid);
+                // what a plan takes: a state per (range, output of the workgroup) for the most ranges there can be, a workgroup per key/value
+                // head and range, within the states' LDS; one thread per output
+                const int per_wg = ((as.n_heads * 128 + grid - 1) / grid + 1) & ~1, ranges = chain_attn_ranges(as.n_kv_heads, grid);
+                if (as.n_kv_heads * ranges > grid) return false;
+                if (per_wg > 64 * CHAIN_WAVES_ATTN || ranges * per_wg * 3 > 4 * CHAIN_WAVES_ATTN * 130) return false;
                 const int group = as.n_heads / as.n_kv_heads;
                 if (as.n_heads % as.n_kv_heads != 0 || (group != 1 && (group & 1))) return false;
                 at.max_seq = as.max_seq; at.pairing = as.pairing;

@@ -120,6 +120,9 @@ class Stack:
     ("Q8_B32", 4, 2, 1408, 1),
     ("Q6_B64", 4, 2, 1408, 1),        # a bit-plane format
     ("Q3_B32", 4, 4, 704, 0),
+    ("Q4_B32", 8, 1, 704, 1),         # all heads on one key/value head: four workgroups per range
+    ("Q3H_B64", 6, 1, 704, 0),        # ... and pairs of heads that do not divide the grid
+    ("Q5_B64", 12, 2, 704, 1),        # six heads per key/value head
 ])
 def test_decode_steps_of_a_small_stack_stage_by_stage(gpu, orc, name, n_heads, n_kv, ffn, pairing):
     torch, iflow = gpu

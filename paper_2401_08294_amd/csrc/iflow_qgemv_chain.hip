@@ -202,11 +202,12 @@ struct ChainWalk {
 #endif
 constexpr int CHAIN_SETS = IFLOW_CHAIN_SETS;
 // Register sets (steps of weights in flight) per wavefront: a step of the 3.5-bit format is 4 KB (two rows of a 2 KB
-// strip), a step of the 4- and 8-bit formats 2 KB, of the bit-plane formats 0.75 to 1.75 KB.  The counts are the fastest
-// measured on 7B-shaped layers (eight layers in one launch, us per layer with 2 / 3 / 4 sets: Q4_B64 34.3 / 35.5 / 30.7,
-// Q8_B64 46.9 / 44.2 / 44.3, Q6_B64 44.2 / 45.2 / 47.4, Q5_B64 43.5 / 35.4 / 46.5, Q3_B32 42.7 / 43.8 / 35.6, Q2_B32 23.5 / 34.9 /
-// 36.0; the padding of a phase's steps to whole rounds is part of what they measure).  IFLOW_CHAIN_SETS_OTHER overrides
-// them all (measurement builds).
+// strip), a step of the 4- and 8-bit formats 2 KB, of the bit-plane formats 0.75 to 1.75 KB.  Measured with 2 / 3 / 4 sets, us per layer of
+// bare products of the 7B shape and of whole decode steps with 32 key/value heads (7B shape, 1000 positions) and with 4 (8 heads, feed-forward 2944): 8-bit,
+// padded steps, 48.8 / 45.9 / 45.9, 52.9 / 51.5 / 51.6, 23.1 / 23.4 / 24.3; 4-bit, padded, 26.1 / 27.4 / 27.4, 36.3 / 37.7 / 39.1, 24.3 / 25.3 / 26.3; 5-bit,
+// not padded, 34.3 / 35.8 / 35.9, 45.2 / 45.6 / 46.4, 25.9 / 25.8 / 26.2, and 2-, 3- and 6-bit alike: the more sets, the more weights queue in
+// front of a phase's activations.  (Three and four sets were ahead while a phase's words were requested one after the other, each wait taking the
+// weights in front of it along.)  IFLOW_CHAIN_SETS_OTHER overrides them all (measurement builds).
 constexpr int chain_sets(int format, bool attn = false)
 {
 #ifdef IFLOW_CHAIN_SETS_ATTN
@@ -215,7 +216,7 @@ constexpr int chain_sets(int format, bool attn = false)
 #ifdef IFLOW_CHAIN_SETS_OTHER
     return format == IFLOW_Q3H_B64 ? CHAIN_SETS : IFLOW_CHAIN_SETS_OTHER;
 #else
-    return format == IFLOW_Q3H_B64 ? CHAIN_SETS : (format == IFLOW_Q6_B64 || format == IFLOW_Q2_B32) ? 2 : format == IFLOW_Q5_B64 ? 3 : 4;
+    return format == IFLOW_Q8_B32 || format == IFLOW_Q8_B64 ? 3 : 2;
 #endif
 }
 
@@ -644,10 +645,11 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
     // PAD: a wavefront's steps per phase are padded to a multiple of S with empty steps, so that every phase starts at set 0
     // and the step loop is S steps unrolled once.  Without it every set always holds a step that will be used, a phase
     // starts at whatever set the sequence has reached, and the step exists in more copies (below).  Which is faster is
-    // measured, per format: with two sets of 4 KB (3.5-bit) no padding is 3.5 % faster on 7B-shaped layers; with four sets
-    // of 2 KB (4- and 8-bit) padding is 4-7 % faster - the empty sets at the head of a short phase are weights that are not
-    // queued in front of the reads of the phase's activations.
-    constexpr bool PAD = !Q3H;
+    // measured, per format (us per layer, padded / not; bare products of the 7B shape, whole decode steps of it with 32 key/value heads): 3.5-bit not (3.5 %
+    // on bare products), 4-bit padded 26.1 / 26.8 and 36.3 / 37.3, 8-bit padded 45.9 / 48.6 and 51.5 / 52.9, 6-bit 36.7 / 36.8 and 47.6 / 46.3, 5-bit 34.8 /
+    // 34.3 and 45.7 / 45.2, 3-bit 33.2 / 32.3 and 44.8 / 44.3, 2-bit 23.8 / 23.6 and 35.5 / 35.1 - an empty set at the head of a short phase is weights that
+    // are not queued in front of the reads of the phase's activations, and a step less in flight.
+    constexpr bool PAD = KIND == KIND_Q4 || KIND == KIND_Q8;
     ChainWalk q = {-1, 0, 0, 0};
     const uint8_t *q_wptr = reinterpret_cast<const uint8_t *>(ws);     // weights of the step under the cursor
     int q_lt = 0, q_last = 0;                                  // its strip; the last strip of a row

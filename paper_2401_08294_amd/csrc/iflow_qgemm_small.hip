@@ -286,13 +286,12 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             };
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                gate(va[q], 2 * q + (ln >> 5));
-                if (upper) gate(vb[q], 8 + 2 * q + (ln >> 5));
+                // (uniform: the gate is most of a strip's work - two vectors, 4096 x 11008 4-bit 17.8 -> 11.2 us, nine, 1077 x 10432 8-bit 25.7 -> 19.9)
+                if (2 * q < batch) gate(va[q], 2 * q + (ln >> 5));
+                if (upper && 8 + 2 * q < batch) gate(vb[q], 8 + 2 * q + (ln >> 5));
             }
         }
         uint32_t n[32];
-#pragma unroll
-        for (int q = 0; q < 32; ++q) n[q] = 0u;
         auto turn = [&](const u32x4_t (&v)[4], bool mine) {     // eight batch rows through the staging rows
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -300,19 +299,26 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if (mine) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const u32x4_t u = *reinterpret_cast<const u32x4_t *>(xst + (i & 7) * SMALL_XROW + g * 128 + q * 16);
-                n[4 * q] = mine ? u.x : n[4 * q]; n[4 * q + 1] = mine ? u.y : n[4 * q + 1];
-                n[4 * q + 2] = mine ? u.z : n[4 * q + 2]; n[4 * q + 3] = mine ? u.w : n[4 * q + 3];
+                for (int q = 0; q < 8; ++q) {
+                    const u32x4_t u = *reinterpret_cast<const u32x4_t *>(xst + (i & 7) * SMALL_XROW + g * 128 + q * 16);
+                    n[4 * q] = u.x; n[4 * q + 1] = u.y; n[4 * q + 2] = u.z; n[4 * q + 3] = u.w;
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();                  // the next turn overwrites the staging rows
         };
-        turn(va, i < 8);
+        // (Up to eight vectors: lanes 8 .. 15 of a group hold the first eight again, their columns of the result are not stored.  A lane reads the half that
+        // is its own, instead of both with a select per register, and the zeros for dead column groups are made only where there are some: 190 -> 90
+        // vector instructions a strip next to 150 to 220 of a step's decode; us, before -> after: 4096 x 4096 4-bit, 8 vectors 4.8 -> 4.3, 4096 x 11008 8-bit 13.9
+        // -> 13.4, 11008 x 4096 3.5-bit with rms and residual 11.1 -> 10.8, 1627 x 17280 6-bit 15.8 -> 15.0.  Requesting the next strip's activations a strip
+        // ahead gave nothing at up to eight vectors and spilled at sixteen: the wavefronts of a SIMD fill each other's waits.)
+        turn(va, !upper || i < 8);
         if (upper) turn(vb, i >= 8);
         // MFMA B operands: the eight activations of step w.  Q3H's decoder yields weights in the order (4s, 4s+2, 4s+1, 4s+3).
         const uint32_t keep = live ? 0xFFFFFFFFu : 0u;
+        const bool ragged = t * 64 + wave * 4 + 4 > nbk64;     // (uniform: some of the wavefront's column groups are dead)
 #pragma unroll
         for (int w = 0; w < 8; ++w) {
             uint32_t v[4];
@@ -322,8 +328,14 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
                 v[2 * hs] = KIND == KIND_Q3H ? __builtin_amdgcn_perm(a1, a0, 0x05040100u) : a0;        // (x[4s], x[4s+2])
                 v[2 * hs + 1] = KIND == KIND_Q3H ? __builtin_amdgcn_perm(a1, a0, 0x07060302u) : a1;    // (x[4s+1], x[4s+3])
             }
-            xq[w] = __builtin_bit_cast(half8_t, (u32x4_t){v[0] & keep, v[1] & keep, v[2] & keep, v[3] & keep});
+            xq[w] = __builtin_bit_cast(half8_t, (u32x4_t){v[0], v[1], v[2], v[3]});
         }
+        if (ragged)
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const u32x4_t v = __builtin_bit_cast(u32x4_t, xq[w]);
+                xq[w] = __builtin_bit_cast(half8_t, (u32x4_t){v.x & keep, v.y & keep, v.z & keep, v.w & keep});
+            }
     };
     // The sums over the wavefronts, in a fixed order, once per batch of rounds (`slots` of them, from round r0 of strip t on): between two of these the
     // wavefronts run freely.  1024 threads: round tid / 256 of the batch, vector tid / 16 % 16, row tid % 16 of the round's sixteen.

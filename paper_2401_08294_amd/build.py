@@ -4,10 +4,12 @@ from __future__ import annotations
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libiflow.so")
+NATIVE = os.path.join(HERE, "_native.so")                   # the Python extension (csrc/iflow_py.cpp); it binds the library's functions at run time
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=off: the quantizer's arithmetic must not be fused (fused multiply-adds are written out
@@ -32,21 +34,28 @@ def _run(cmd):
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + err)
+        raise RuntimeError("the compiler failed:\n" + " ".join(cmd) + "\n" + err)
     return err
+
+
+def build_native() -> str:
+    return _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-cast-function-type",
+                 "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "iflow_py.cpp"), "-o", NATIVE])
 
 
 def build_lib(verbose: bool = False) -> str:
     """Compile every HIP source into paper_2401_08294_amd/libiflow.so (always recompiles): one object per source, the
-    sources side by side on up to eight host threads, then one link."""
+    sources side by side on up to eight host threads, then one link; and the Python extension beside it."""
     from concurrent.futures import ThreadPoolExecutor
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     compile_flags = [f for f in FLAGS if f != "-shared"]
     srcs = sources()
     objs = [os.path.join(objdir, os.path.basename(s)[:-4] + ".o") for s in srcs]
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as pool:
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as pool:
+        native = pool.submit(build_native)
         errs = list(pool.map(lambda so: _run([HIPCC] + compile_flags + ["-c", so[0], "-o", so[1]]), zip(srcs, objs)))
+        errs.append(native.result())
     errs.append(_run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB]))
     if verbose:
         for e in errs:

@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libiflow.so, with the same names as the C ABI in include/iflow.h.
+"""Thin binding over libiflow.so, with the same names as the C ABI in include/iflow.h: ctypes, and for the calls that a decode step makes over and
+over a small extension (csrc/iflow_py.cpp) that hands the same arguments to the same functions.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  PyTorch is used
 by callers for device memory and streams; tensors are passed as `tensor.data_ptr()` and the stream as
@@ -52,15 +53,28 @@ class IflowError(RuntimeError):
 
 
 _lib = None
+_native = None                 # the extension, bound to the library's functions
+# Enqueueing from Python, us, ctypes / here: a product with one vector 4.4 / 3.7, the attention's two launches 7.1 / 6.1, a decoder layer's six calls (seven
+# launches) 35.0 / 24.6 - of which 2.3 a launch are the launch itself.
+_NATIVE_CALLS = ("quantize", "dequant", "qgemv", "qgemm", "qgemv_fused", "qgemv_gated", "qgemm_fused", "attn_decode", "rope_append")
+
+
+def _calls():
+    lib()
+    return _native
 
 
 def lib():
     """Load libiflow.so (once).  Raises if it is missing: the product path has no fallback."""
-    global _lib
+    global _lib, _native
     if _lib is None:
+        build = "build it with __graft_entry__.build() or `python -m paper_2401_08294_amd.build`"
         if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
-                               "or `python -m paper_2401_08294_amd.build`")
+            raise RuntimeError(f"{LIB_PATH} is missing: {build}")
+        try:
+            from . import _native as native
+        except ImportError as e:
+            raise RuntimeError(f"the extension beside {LIB_PATH} is missing or does not load ({e}): {build}") from e
         # PyTorch ships its own HIP runtime; import it first so that the library binds to that same
         # runtime (two runtimes in one process do not share devices, streams or memory).
         import torch  # noqa: F401
@@ -102,6 +116,8 @@ def lib():
         L.iflow_decode_stack_sizes.argtypes = [C.POINTER(DecodeStack), C.POINTER(sz), C.POINTER(sz), C.POINTER(sz)]
         L.iflow_decode_stack_plan.argtypes = [C.POINTER(DecodeStack), p, sz, p, sz, p, C.POINTER(Chain)]
         L.iflow_decode_stack_launch.argtypes = [C.POINTER(Chain), i64, p]
+        native.bind(*[C.cast(getattr(L, "iflow_" + name), p).value for name in _NATIVE_CALLS])
+        _native = native
         _lib = L
     return _lib
 
@@ -173,19 +189,19 @@ def packed_bytes(fmt: int, rows: int, cols: int) -> int:
 
 def quantize(fmt: int, w, rows: int, cols: int, packed, packed_capacity: int, stream=None) -> None:
     """w: fp32 [rows][cols] device tensor; packed: uint8 device tensor of at least packed_bytes()."""
-    _check(lib().iflow_quantize(fmt, _ptr(w), rows, cols, _ptr(packed), packed_capacity, _stream(stream)), "iflow_quantize")
+    _check((_native or _calls()).quantize(fmt, w, rows, cols, packed, packed_capacity, _stream(stream)), "iflow_quantize")
 
 
 def dequant(fmt: int, packed, rows: int, cols: int, w16, stream=None) -> None:
-    _check(lib().iflow_dequant(fmt, _ptr(packed), rows, cols, _ptr(w16), _stream(stream)), "iflow_dequant")
+    _check((_native or _calls()).dequant(fmt, packed, rows, cols, w16, _stream(stream)), "iflow_dequant")
 
 
 def qgemv(fmt: int, packed, rows: int, cols: int, x, y, stream=None) -> None:
-    _check(lib().iflow_qgemv(fmt, _ptr(packed), rows, cols, _ptr(x), _ptr(y), _stream(stream)), "iflow_qgemv")
+    _check((_native or _calls()).qgemv(fmt, packed, rows, cols, x, y, _stream(stream)), "iflow_qgemv")
 
 
 def qgemm(fmt: int, packed, rows: int, cols: int, X, batch: int, Y, stream=None) -> None:
-    _check(lib().iflow_qgemm(fmt, _ptr(packed), rows, cols, _ptr(X), batch, _ptr(Y), _stream(stream)), "iflow_qgemm")
+    _check((_native or _calls()).qgemm(fmt, packed, rows, cols, X, batch, Y, _stream(stream)), "iflow_qgemm")
 
 
 def unpack_logical(fmt: int, packed, rows: int, cols: int, levels, scale16, offset16, stream=None) -> None:
@@ -223,31 +239,22 @@ def qgemv_fused(fmt: int, packed_list, rows_list, cols: int, x, y_list, x_op: in
                 residual_list=None, stream=None) -> None:
     """qgemv_multi with rms normalization (aux = gains) or the silu-gated input (aux = second factor) in front of the
     product and an optional residual per matrix behind it, in the same launch."""
-    n = len(packed_list)
-    pk = (C.c_void_p * n)(*[_ptr(t) for t in packed_list])
-    ys = (C.c_void_p * n)(*[_ptr(t) for t in y_list])
-    rs = (C.c_int64 * n)(*[int(r) for r in rows_list])
-    res = None
-    if residual_list is not None:
-        res = (C.c_void_p * n)(*[(_ptr(t) if t is not None else None) for t in residual_list])
-    _check(lib().iflow_qgemv_fused(fmt, n, pk, rs, cols, _ptr(x), x_op, _ptr(aux) if aux is not None else None, eps, res, ys,
-                                   _stream(stream)), "iflow_qgemv_fused")
+    _check((_native or _calls()).qgemv_fused(fmt, packed_list, rows_list, cols, x, y_list, x_op, aux, eps, residual_list, _stream(stream)),
+           "iflow_qgemv_fused")
 
 
 def qgemm_fused(fmt: int, packed, rows: int, cols: int, X, batch: int, Y, x_op: int = X_PLAIN, aux=None, eps: float = 0.0,
                 residual=None, stream=None) -> None:
     """qgemv_fused for 1..16 activation vectors X [batch][cols] -> Y [batch][rows]: rms normalization (aux = gains [cols]) or the
     silu-gated input (aux [batch][cols]) in front of the product, an optional residual [batch][rows] behind it."""
-    _check(lib().iflow_qgemm_fused(fmt, _ptr(packed), rows, cols, _ptr(X), batch, x_op, _ptr(aux) if aux is not None else None, eps,
-                                   _ptr(residual) if residual is not None else None, _ptr(Y), _stream(stream)), "iflow_qgemm_fused")
+    _check((_native or _calls()).qgemm_fused(fmt, packed, rows, cols, X, batch, Y, x_op, aux, eps, residual, _stream(stream)), "iflow_qgemm_fused")
 
 
 def qgemv_gated(fmt: int, packed_gate, packed_up, rows: int, cols: int, x, y, x_op: int = X_PLAIN, aux=None, eps: float = 0.0,
                 stream=None) -> None:
     """y = silu(c W_gate' v) * (c W_up' v): a gated feed-forward's two first projections and its gate in one launch
     (v, c: x itself and 1, or the rms-normalized x with gains `aux`)."""
-    _check(lib().iflow_qgemv_gated(fmt, _ptr(packed_gate), _ptr(packed_up), rows, cols, _ptr(x), x_op,
-                                   _ptr(aux) if aux is not None else None, eps, _ptr(y), _stream(stream)), "iflow_qgemv_gated")
+    _check((_native or _calls()).qgemv_gated(fmt, packed_gate, packed_up, rows, cols, x, y, x_op, aux, eps, _stream(stream)), "iflow_qgemv_gated")
 
 
 def attn_decode_workspace_bytes(n_heads: int) -> int:
@@ -259,8 +266,8 @@ def attn_decode_workspace_bytes(n_heads: int) -> int:
 def attn_decode(q, k_cache, v_cache, n_heads: int, n_kv_heads: int, head_dim: int, seq_len: int, max_seq: int, scale: float, out,
                 workspace, workspace_bytes: int, stream=None) -> None:
     """One decode step of grouped-query attention over an fp16 key/value cache [n_kv_heads][max_seq][head_dim]."""
-    _check(lib().iflow_attn_decode(_ptr(q), _ptr(k_cache), _ptr(v_cache), n_heads, n_kv_heads, head_dim, seq_len, max_seq, scale,
-                                   _ptr(out), _ptr(workspace), workspace_bytes, _stream(stream)), "iflow_attn_decode")
+    _check((_native or _calls()).attn_decode(q, k_cache, v_cache, n_heads, n_kv_heads, head_dim, seq_len, max_seq, scale, out, workspace, workspace_bytes,
+                                             _stream(stream)), "iflow_attn_decode")
 
 
 def attn_decode_static(q, k_cache, v_cache, n_heads: int, n_kv_heads: int, head_dim: int, seq_len: int, max_seq: int, scale: float,
@@ -274,8 +281,8 @@ def rope_append(q, k_new, v_new, n_heads: int, n_kv_heads: int, head_dim: int, p
                 pair_mode: int, k_cache, v_cache, stream=None) -> None:
     """Rotary position embedding of one decode step: q rotated in place, rotated k_new and v_new written to row `position`
     of the caches [n_kv_heads][max_seq][head_dim]."""
-    _check(lib().iflow_rope_append(_ptr(q), _ptr(k_new), _ptr(v_new), n_heads, n_kv_heads, head_dim, position, max_seq, base,
-                                   pair_mode, _ptr(k_cache), _ptr(v_cache), _stream(stream)), "iflow_rope_append")
+    _check((_native or _calls()).rope_append(q, k_new, v_new, n_heads, n_kv_heads, head_dim, position, max_seq, base, pair_mode, k_cache, v_cache,
+                                             _stream(stream)), "iflow_rope_append")
 
 
 def qgemv_chain_workspace_bytes(rows_list) -> int:

@@ -458,6 +458,69 @@ def test_forked_child_asks_the_runtime_again(monkeypatch):
     assert iflow._stream(None) == 1234                         # the parent keeps its own
 
 
+def test_extension_hands_every_argument_to_its_place(iflow):
+    """The calls that go through the Python extension: with recording functions bound in the library's place, every argument arrives where the C ABI
+    has it (prototypes: the ctypes ones), addresses come from integers, None and data_ptr(), the status comes back; what does not fit raises."""
+    L, native, seen = iflow.lib(), iflow._native, {}
+
+    class Tensor:
+        def __init__(self, address):
+            self.address = address
+
+        def data_ptr(self):
+            return self.address
+
+    def recorder(name):
+        def record(*args):
+            seen[name] = args
+            return iflow.ERR_SHAPE
+        return C.CFUNCTYPE(C.c_int, *getattr(L, "iflow_" + name).argtypes)(record)
+    fakes = [recorder(name) for name in iflow._NATIVE_CALLS]
+    real = [C.cast(getattr(L, "iflow_" + name), C.c_void_p).value for name in iflow._NATIVE_CALLS]
+    big = (1 << 63) + 16                                       # (an address above the signed range)
+    native.bind(*[C.cast(f, C.c_void_p).value for f in fakes])
+    try:
+        def call(f, *args, **kw):
+            with pytest.raises(iflow.IflowError) as info:
+                f(*args, **kw)
+            assert info.value.status == iflow.ERR_SHAPE
+        call(iflow.quantize, 1, Tensor(2), 3 << 40, 4, 5, 6, stream=7)
+        assert seen["quantize"] == (1, 2, 3 << 40, 4, 5, 6, 7)
+        call(iflow.dequant, 1, big, 3, 4, None, stream=7)
+        assert seen["dequant"] == (1, big, 3, 4, None, 7)
+        call(iflow.qgemv, 1, Tensor(big), 3, 4, 5, Tensor(6), stream=7)
+        assert seen["qgemv"] == (1, big, 3, 4, 5, 6, 7)
+        call(iflow.qgemm, 1, 2, 3, 4, 5, 6, 7, stream=8)
+        assert seen["qgemm"] == (1, 2, 3, 4, 5, 6, 7, 8)
+        call(iflow.qgemm_fused, 1, 2, 3, 4, 5, 6, 7, 8, Tensor(9), 0.5, None, stream=11)
+        assert seen["qgemm_fused"] == (1, 2, 3, 4, 5, 6, 8, 9, 0.5, None, 7, 11)
+        call(iflow.qgemv_gated, 1, 2, 3, 4, 5, 6, 7, 8, None, 0.5, stream=11)
+        assert seen["qgemv_gated"] == (1, 2, 3, 4, 5, 6, 8, None, 0.5, 7, 11)
+        call(iflow.attn_decode, 1, 2, 3, 4, 5, 6, 7, 8, 0.5, 10, 11, 12, stream=13)
+        assert seen["attn_decode"] == (1, 2, 3, 4, 5, 6, 7, 8, 0.5, 10, 11, 12, 13)
+        call(iflow.rope_append, 1, 2, 3, 4, 5, 6, 7, 8, 0.5, 10, 11, 12, stream=13)
+        assert seen["rope_append"] == (1, 2, 3, 4, 5, 6, 7, 8, 0.5, 10, 11, 12, 13)
+        call(iflow.qgemv_fused, 1, [2, Tensor(3)], (4, 5), 6, 7, [8, 9], 10, 11, 0.5, [None, Tensor(12)], stream=13)
+        fmt, n, packed, rows, cols, x, op, aux, eps, res, y, stream = seen["qgemv_fused"]
+        assert (fmt, n, cols, x, op, aux, eps, stream) == (1, 2, 6, 7, 10, 11, 0.5, 13)
+        # (the arrays are gone with the call: their contents are checked by every product on the device; here, that there are some)
+        assert packed and rows and res and y
+        call(iflow.qgemv_fused, 1, [2], [4], 6, 7, [8], stream=13)
+        assert not seen["qgemv_fused"][9]                      # no residuals
+        seen.clear()
+        for wrong in (lambda: iflow.qgemv(1, "packed", 3, 4, 5, 6, stream=7), lambda: iflow.qgemv(1, 2, 3.5, 4, 5, 6, stream=7),
+                      lambda: iflow.qgemv_fused(1, [2, 3], [4], 6, 7, [8, 9], stream=13), lambda: iflow.qgemv_fused(1, [2] * 65, [4] * 65, 6, 7, [8] * 65, stream=13),
+                      lambda: iflow.qgemv_fused(1, [2], [4], 6, 7, [8], residual_list=[], stream=13)):
+            with pytest.raises((TypeError, ValueError, AttributeError)):
+                wrong()
+        assert not seen                                        # ... and nothing was called
+    finally:
+        native.bind(*real)
+    with pytest.raises(iflow.IflowError) as info:
+        iflow.qgemv(4, None, 8, 64, 0x10000, 0x10000, stream=0)
+    assert info.value.status == iflow.ERR_NULL
+
+
 def test_tiles_reach_as_far_as_their_offsets(iflow):
     """17 and more vectors take the tiled product up to 2^26 columns, and never a tile whose byte offsets would leave 32 bits: of its vectors' activations, or of
     a wavefront's (at most 96) rows of at most one byte a weight."""

@@ -268,10 +268,16 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     constexpr int SLICE = BM * 128, STEP = WK * SLICE;         // bytes of one chunk's activations; of the WK chunks of a step
     constexpr int NX = (4 * MB + WR - 1) / WR;                 // 1 KB pieces of its group's chunk a wavefront copies per step
     constexpr int NG = RT * (P::q3h ? 2 * P::NA : P::NA + P::NB + P::NH);      // a wavefront's requests per group of G chunks
+    // With two stages a step waits for what was requested one step ago.  Where a group lasts two steps its request goes out behind that step's
+    // activations, so that the wait for them leaves it one step more: these bytes come from memory, the activations from L2.  (us, before -> after: 28672 x
+    // 8192 4-bit, 2000 vectors 889 -> 874, 1024 471 -> 457, 8-bit, 1000 508 -> 493; 14336 x 8192 6-bit, 1500 423 -> 413; 5000 x 3008 4-bit, 1300 62.8 -> 58.8
+    // with the same tile.  Not with groups of four steps - 3.5-bit, 11008 x 4096, 2048 vectors 201 -> 207 - nor without a barrier: 4096 x 11008 8-bit, 33 vectors
+    // 17.4 -> 17.7.)
+    constexpr bool XFIRST = STAGES == 2 && G == 2 && WR > 1;
     // what may still be on its way when a step's activations have to be there: the activations of the STAGES - 2 steps after it and
-    // the groups requested among them
-    constexpr int AHEAD = STAGES - 2, SURE = AHEAD * NX + AHEAD / G * NG;
-    static_assert(SURE + NG < 64 && (P::BUFFERS - 1) * G >= STAGES - 1, "the wait counter's range; a group is there when its steps come");
+    // the groups requested among them (XFIRST: behind them)
+    constexpr int AHEAD = STAGES - 2, SINCE = AHEAD + XFIRST, SURE = AHEAD * NX + SINCE / G * NG;
+    static_assert(SURE + NG < 64 && (P::BUFFERS - 1) * G >= STAGES - 1 + XFIRST, "the wait counter's range; a group is there when its steps come");
     extern __shared__ __align__(16) uint8_t smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -342,8 +348,9 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     wait_requests<(STAGES - 2) * NX>();
     if constexpr (WR > 1) __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if constexpr (XFIRST) request_x(STAGES - 1, STAGES - 1);
     request_w(P::BUFFERS - 1, P::BUFFERS - 1);
-    request_x(STAGES - 1, STAGES - 1);
+    if constexpr (!XFIRST) request_x(STAGES - 1, STAGES - 1);
     read_w(0, 0);
     read_x(0, 0, af[0]);
 #pragma unroll
@@ -359,17 +366,18 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
             if (ks < 3) {
                 read_x(stage, ks + 1, af[(ks + 1) & 1]);
             } else {
-                if (G > 1 && AHEAD % G != 0 && c < AHEAD % G) wait_requests<SURE + NG>();   // a group was requested since
+                if (G > 1 && SINCE % G != 0 && c < SINCE % G) wait_requests<SURE + NG>();   // a group was requested since
                 else wait_requests<SURE>();                    // step + 1's are there; and the wavefront's reads of this stage are done
                 if constexpr (WR > 1) __builtin_amdgcn_s_barrier();   // ... everybody's (a group of one wavefront copies what it reads)
                 asm volatile("" ::: "memory");
+                if constexpr (XFIRST) request_x(step + STAGES, stage);
                 if (G == 1 || ++c == G) {                      // the group is used up
                     c = 0; ++group;
                     const int used = buf;
                     buf = buf == P::BUFFERS - 1 ? 0 : buf + 1;
                     request_w(group + P::BUFFERS - 1, used);
                 }
-                request_x(step + STAGES, stage);
+                if constexpr (!XFIRST) request_x(step + STAGES, stage);
                 read_w(c, buf);
                 read_x(next, 0, af[0]);
             }

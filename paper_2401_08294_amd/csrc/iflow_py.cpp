@@ -12,7 +12,7 @@
 
 namespace {
 
-constexpr Py_ssize_t MAX_ARRAY = 64;                           // matrices of one call (the library takes 8)
+constexpr Py_ssize_t MAX_ARRAY = 16;                           // matrices of one call that are handed on (the library takes 8 and refuses more by their count)
 
 decltype(&iflow_quantize) p_quantize;
 decltype(&iflow_dequant) p_dequant;
@@ -51,20 +51,23 @@ struct Args {
         if (o && !address(o, &p)) bad = true;
         return static_cast<T *>(p);
     }
+    // whole numbers as ctypes takes them: what has __index__, its low bits (a capacity of 2^64 - 1 is one)
+    static bool whole(PyObject *o, int64_t *out)
+    {
+        PyObject *v = PyNumber_Index(o);
+        if (!v) return false;
+        *out = (int64_t)PyLong_AsUnsignedLongLongMask(v);
+        Py_DECREF(v);
+        return true;
+    }
     int64_t num()
     {
         PyObject *o = next();
-        if (!o) return 0;
-        const long long v = PyLong_AsLongLong(o);
-        if (v == -1 && PyErr_Occurred()) bad = true;
+        int64_t v = 0;
+        if (o && !whole(o, &v)) bad = true;
         return v;
     }
-    int word()
-    {
-        const int64_t v = num();
-        if (!bad && v != (int)v) { PyErr_SetString(PyExc_OverflowError, "an argument does not fit 32 bits"); bad = true; }
-        return (int)v;
-    }
+    int word() { return (int)num(); }
     float real()
     {
         PyObject *o = next();
@@ -73,7 +76,7 @@ struct Args {
         if (v == -1.0 && PyErr_Occurred()) bad = true;
         return (float)v;
     }
-    // a list or tuple of addresses or of whole numbers; its length, or -1 for None
+    // a list of addresses or of whole numbers, its first MAX_ARRAY entries; its length, or -1 for None
     template <typename Put> Py_ssize_t each(Put put)
     {
         PyObject *o = next();
@@ -81,8 +84,7 @@ struct Args {
         PyObject *seq = PySequence_Fast(o, "a list is wanted");
         if (!seq) { bad = true; return -1; }
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-        if (n > MAX_ARRAY) { PyErr_SetString(PyExc_ValueError, "too many matrices in one call"); bad = true; }
-        for (Py_ssize_t i = 0; i < n && !bad; ++i)
+        for (Py_ssize_t i = 0; i < n && i < MAX_ARRAY && !bad; ++i)
             if (!put(i, PySequence_Fast_GET_ITEM(seq, i))) bad = true;
         Py_DECREF(seq);
         return n;
@@ -101,9 +103,9 @@ struct Args {
         return each([&](Py_ssize_t i, PyObject *o) {
             PyObject *v = PyNumber_Long(o);                    // int(o)
             if (!v) return false;
-            out[i] = PyLong_AsLongLong(v);
+            const bool ok = whole(v, &out[i]);
             Py_DECREF(v);
-            return !(out[i] == -1 && PyErr_Occurred());
+            return ok;
         });
     }
 };
@@ -170,10 +172,11 @@ PyObject *qgemv_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     Args a(args, nargs, 11);
     const int fmt = a.word();
-    const void *packed[MAX_ARRAY];
-    int64_t rows[MAX_ARRAY];
-    uint16_t *y[MAX_ARRAY];
-    const uint16_t *residual[MAX_ARRAY];
+    // (what a shorter list leaves out is null or zero: no residual, or refused by the library)
+    const void *packed[MAX_ARRAY] = {};
+    int64_t rows[MAX_ARRAY] = {};
+    uint16_t *y[MAX_ARRAY] = {};
+    const uint16_t *residual[MAX_ARRAY] = {};
     const Py_ssize_t n = a.addresses(packed), nr = a.numbers(rows);
     const int64_t cols = a.num();
     const uint16_t *x = a.ptr<const uint16_t>();
@@ -183,10 +186,8 @@ PyObject *qgemv_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const float eps = a.real();
     const Py_ssize_t nres = a.addresses(residual);
     void *stream = a.ptr<void>();
-    if (!a.bad && (n < 0 || nr != n || ny != n || (nres >= 0 && nres != n))) {
-        PyErr_SetString(PyExc_ValueError, "the lists of matrices, rows, outputs and residuals have different lengths");
-        return nullptr;
-    }
+    if (!a.bad && (n < 0 || nr < 0 || ny < 0)) { PyErr_SetString(PyExc_TypeError, "lists of matrices, rows and outputs are wanted"); return nullptr; }
+    if (!a.bad && (nr > n || ny > n || nres > n)) { PyErr_SetString(PyExc_ValueError, "more rows, outputs or residuals than matrices"); return nullptr; }
     return run(a, [&] {
         return p_qgemv_fused((iflow_format_t)fmt, (int)n, packed, rows, cols, x, (iflow_x_op_t)x_op, aux, eps, nres < 0 ? nullptr : residual, y, stream);
     });

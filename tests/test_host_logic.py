@@ -509,13 +509,24 @@ def test_extension_hands_every_argument_to_its_place(iflow):
         assert not seen["qgemv_fused"][9]                      # no residuals
         seen.clear()
         for wrong in (lambda: iflow.qgemv(1, "packed", 3, 4, 5, 6, stream=7), lambda: iflow.qgemv(1, 2, 3.5, 4, 5, 6, stream=7),
-                      lambda: iflow.qgemv_fused(1, [2, 3], [4], 6, 7, [8, 9], stream=13), lambda: iflow.qgemv_fused(1, [2] * 65, [4] * 65, 6, 7, [8] * 65, stream=13),
-                      lambda: iflow.qgemv_fused(1, [2], [4], 6, 7, [8], residual_list=[], stream=13)):
+                      lambda: iflow.qgemv_fused(1, [2], [4, 4], 6, 7, [8], stream=13), lambda: iflow.qgemv_fused(1, [2], [4], 6, 7, [8, 8], stream=13),
+                      lambda: iflow.qgemv_fused(1, [2], [4], 6, 7, [8], residual_list=[1, 2], stream=13), lambda: iflow.qgemv_fused(1, None, [4], 6, 7, [8], stream=13)):
             with pytest.raises((TypeError, ValueError, AttributeError)):
                 wrong()
         assert not seen                                        # ... and nothing was called
+        # whole numbers wrap as ctypes' do, numpy's are some too
+        call(iflow.quantize, (1 << 32) + 1, 2, np.int64(3), 4, 5, 2 ** 64 - 1, stream=7)
+        assert seen["quantize"] == (1, 2, 3, 4, 5, 2 ** 64 - 1, 7)
     finally:
         native.bind(*real)
+    # the library's own answers to lists that are too long or too short (a short list of residuals leaves the other matrices without: below,
+    # the second matrix is refused for its alignment, so nothing is launched)
+    at = 0x10000
+    for status, packed, rows, y, residual in ((iflow.ERR_SHAPE, [at] * 65, [8] * 65, [at] * 65, None), (iflow.ERR_SHAPE, [at] * 2, [8], [at, 2 * at], None),
+                                              (iflow.ERR_NULL, [at] * 2, [8] * 2, [3 * at], None), (iflow.ERR_ALIGN, [at, at + 1], [8] * 2, [3 * at, 4 * at], [5 * at])):
+        with pytest.raises(iflow.IflowError) as info:
+            iflow.qgemv_fused(4, packed, rows, 64, 2 * at, y, residual_list=residual, stream=0)
+        assert info.value.status == status
     with pytest.raises(iflow.IflowError) as info:
         iflow.qgemv(4, None, 8, 64, 0x10000, 0x10000, stream=0)
     assert info.value.status == iflow.ERR_NULL

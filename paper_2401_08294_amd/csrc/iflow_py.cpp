@@ -81,11 +81,11 @@ struct Args {
     {
         PyObject *o = next();
         if (!o || o == Py_None) return -1;
-        PyObject *seq = PySequence_Fast(o, "a list is wanted");
+        PyObject *seq = PySequence_Tuple(o);                   // (a copy that holds its entries: data_ptr or another thread may change the list meanwhile)
         if (!seq) { bad = true; return -1; }
-        const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
+        const Py_ssize_t n = PyTuple_GET_SIZE(seq);
         for (Py_ssize_t i = 0; i < n && i < MAX_ARRAY && !bad; ++i)
-            if (!put(i, PySequence_Fast_GET_ITEM(seq, i))) bad = true;
+            if (!put(i, PyTuple_GET_ITEM(seq, i))) bad = true;
         Py_DECREF(seq);
         return n;
     }

@@ -532,6 +532,24 @@ def test_extension_hands_every_argument_to_its_place(iflow):
     assert info.value.status == iflow.ERR_NULL
 
 
+def test_extension_holds_the_lists_it_walks(iflow):
+    """A list whose entries' data_ptr empties it (and drops the entries) while the call reads it: the entries that were there are read."""
+    class Emptying:
+        def __init__(self, entries):
+            self.entries = entries
+
+        def data_ptr(self):
+            del self.entries[:]
+            return 0x10000
+    packed, y = [], []
+    packed.extend([Emptying(packed)] + [Emptying(packed) for _ in range(3)])
+    y.extend([Emptying(y) for _ in range(4)])
+    with pytest.raises(iflow.IflowError) as info:
+        iflow.qgemv_fused(4, packed, [8] * 4, 64, 0x20001, y, stream=0)
+    assert info.value.status == iflow.ERR_ALIGN                # (x: every other address is aligned)
+    assert not packed and not y
+
+
 def test_tiles_reach_as_far_as_their_offsets(iflow):
     """17 and more vectors take the tiled product up to 2^26 columns, and never a tile whose byte offsets would leave 32 bits: of its vectors' activations, or of
     a wavefront's (at most 96) rows of at most one byte a weight."""

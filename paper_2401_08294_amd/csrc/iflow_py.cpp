@@ -4,7 +4,9 @@
 // three-matrix call of a decoder layer 4, next to the 2.3 of the launch itself.  Here an address is one method call (data_ptr) and an array lives
 // on the stack.  Measured, us to enqueue, ctypes -> here: a product with one vector 4.4 -> 3.7, a decoder layer's six calls 35.0 -> 24.6.
 // The functions are the library's own, bound by address (bind), so the library is loaded once and in one place.  An address is an integer, None
-// (null) or an object with data_ptr(); a call returns the library's status and runs without the interpreter's lock, as a ctypes call does.
+// (null) or an object with data_ptr(), a number what has __index__ or __float__, matrices and outputs are lists or tuples; a call returns the library's
+// status and runs without the interpreter's lock, as a ctypes call does.  A call with anything else among its arguments (ctypes' own numbers, an iterator,
+// a text) is handed on as it is to the function that otherwise() was given, which takes or refuses it.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -23,26 +25,25 @@ decltype(&iflow_qgemv_gated) p_qgemv_gated;
 decltype(&iflow_qgemm_fused) p_qgemm_fused;
 decltype(&iflow_attn_decode) p_attn_decode;
 decltype(&iflow_rope_append) p_rope_append;
-PyObject *s_data_ptr;
+PyObject *s_data_ptr, *general;                                // general(name, arguments ...): the call that takes every form of argument
 
-// One call's arguments in order; the first that does not fit leaves a Python exception and turns the rest into zeros.
+// One call's arguments in order; the first that does not fit ends the reading (bad; perhaps a Python exception) and turns the rest into zeros.
 struct Args {
-    PyObject *const *at;
-    Py_ssize_t left;
+    const char *name;
+    PyObject *const *first, *const *at;
+    Py_ssize_t count;
     bool bad = false;
-    Args(PyObject *const *args, Py_ssize_t nargs, Py_ssize_t want) : at(args), left(nargs)
-    {
-        if (nargs != want) { PyErr_Format(PyExc_TypeError, "%zd arguments, got %zd", want, nargs); bad = true; }
-    }
+    Args(const char *call, PyObject *const *args, Py_ssize_t nargs, Py_ssize_t want) : name(call), first(args), at(args), count(nargs) { bad = nargs != want; }
     PyObject *next() { return bad ? nullptr : *at++; }
     static bool address(PyObject *o, void **out)
     {
         if (o == Py_None) { *out = nullptr; return true; }
         PyObject *v = PyLong_Check(o) ? Py_NewRef(o) : PyObject_CallMethodNoArgs(o, s_data_ptr);
         if (!v) return false;
-        *out = reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(v));
+        const bool number = PyLong_Check(v);
+        if (number) *out = reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(v));
         Py_DECREF(v);
-        return !(*out == reinterpret_cast<void *>(~0ull) && PyErr_Occurred());
+        return number;
     }
     template <typename T> T *ptr()
     {
@@ -50,6 +51,14 @@ struct Args {
         void *p = nullptr;
         if (o && !address(o, &p)) bad = true;
         return static_cast<T *>(p);
+    }
+    // a stream's handle: a number already
+    void *handle()
+    {
+        PyObject *o = next();
+        void *p = nullptr;
+        if (o && !((o == Py_None || PyLong_Check(o)) && address(o, &p))) bad = true;
+        return p;
     }
     // whole numbers as ctypes takes them: what has __index__, its low bits (a capacity of 2^64 - 1 is one)
     static bool whole(PyObject *o, int64_t *out)
@@ -81,7 +90,7 @@ struct Args {
     {
         PyObject *o = next();
         if (!o || o == Py_None) return -1;
-        PyObject *seq = PySequence_Tuple(o);                   // (a copy that holds its entries: data_ptr or another thread may change the list meanwhile)
+        PyObject *seq = PyList_Check(o) || PyTuple_Check(o) ? PySequence_Tuple(o) : nullptr;      // (a copy that holds its entries: data_ptr or another thread may change the list meanwhile)
         if (!seq) { bad = true; return -1; }
         const Py_ssize_t n = PyTuple_GET_SIZE(seq);
         for (Py_ssize_t i = 0; i < n && i < MAX_ARRAY && !bad; ++i)
@@ -110,9 +119,28 @@ struct Args {
     }
 };
 
+// A call whose arguments do not fit here, as it came: what data_ptr, __index__ or __float__ raised is raised again there, or not.  (An interrupt goes up.)
+PyObject *hand_on(const Args &a)
+{
+    if (PyErr_Occurred()) {
+        if (!PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
+        PyErr_Clear();
+    }
+    if (!general) { PyErr_SetString(PyExc_RuntimeError, "not bound"); return nullptr; }
+    PyObject *args = PyTuple_New(a.count + 1), *name = PyUnicode_FromString(a.name), *result = nullptr;
+    if (args && name) {
+        PyTuple_SET_ITEM(args, 0, Py_NewRef(name));
+        for (Py_ssize_t i = 0; i < a.count; ++i) PyTuple_SET_ITEM(args, i + 1, Py_NewRef(a.first[i]));
+        result = PyObject_Call(general, args, nullptr);
+    }
+    Py_XDECREF(args);
+    Py_XDECREF(name);
+    return result;
+}
+
 template <typename Call> PyObject *run(const Args &a, Call call)
 {
-    if (a.bad) return nullptr;
+    if (a.bad) return hand_on(a);
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = (int)call();
@@ -122,55 +150,55 @@ template <typename Call> PyObject *run(const Args &a, Call call)
 
 PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 7);
+    Args a("quantize", args, nargs, 7);
     const int fmt = a.word();
     const float *w = a.ptr<const float>();
     const int64_t rows = a.num(), cols = a.num();
     void *packed = a.ptr<void>();
     const int64_t capacity = a.num();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_quantize((iflow_format_t)fmt, w, rows, cols, packed, (size_t)capacity, stream); });
 }
 
 PyObject *dequant(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 6);
+    Args a("dequant", args, nargs, 6);
     const int fmt = a.word();
     const void *packed = a.ptr<const void>();
     const int64_t rows = a.num(), cols = a.num();
     uint16_t *w16 = a.ptr<uint16_t>();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_dequant((iflow_format_t)fmt, packed, rows, cols, w16, stream); });
 }
 
 PyObject *qgemv(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 7);
+    Args a("qgemv", args, nargs, 7);
     const int fmt = a.word();
     const void *packed = a.ptr<const void>();
     const int64_t rows = a.num(), cols = a.num();
     const uint16_t *x = a.ptr<const uint16_t>();
     uint16_t *y = a.ptr<uint16_t>();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_qgemv((iflow_format_t)fmt, packed, rows, cols, x, y, stream); });
 }
 
 PyObject *qgemm(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 8);
+    Args a("qgemm", args, nargs, 8);
     const int fmt = a.word();
     const void *packed = a.ptr<const void>();
     const int64_t rows = a.num(), cols = a.num();
     const uint16_t *x = a.ptr<const uint16_t>();
     const int64_t batch = a.num();
     uint16_t *y = a.ptr<uint16_t>();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_qgemm((iflow_format_t)fmt, packed, rows, cols, x, batch, y, stream); });
 }
 
 PyObject *qgemv_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 11);
+    Args a("qgemv_fused", args, nargs, 11);
     const int fmt = a.word();
     // (what a shorter list leaves out is null or zero: no residual, or refused by the library)
     const void *packed[MAX_ARRAY] = {};
@@ -185,9 +213,8 @@ PyObject *qgemv_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const uint16_t *aux = a.ptr<const uint16_t>();
     const float eps = a.real();
     const Py_ssize_t nres = a.addresses(residual);
-    void *stream = a.ptr<void>();
-    if (!a.bad && (n < 0 || nr < 0 || ny < 0)) { PyErr_SetString(PyExc_TypeError, "lists of matrices, rows and outputs are wanted"); return nullptr; }
-    if (!a.bad && (nr > n || ny > n || nres > n)) { PyErr_SetString(PyExc_ValueError, "more rows, outputs or residuals than matrices"); return nullptr; }
+    void *stream = a.handle();
+    if (n < 0 || nr < 0 || ny < 0 || nr > n || ny > n || nres > n) a.bad = true;
     return run(a, [&] {
         return p_qgemv_fused((iflow_format_t)fmt, (int)n, packed, rows, cols, x, (iflow_x_op_t)x_op, aux, eps, nres < 0 ? nullptr : residual, y, stream);
     });
@@ -195,7 +222,7 @@ PyObject *qgemv_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 
 PyObject *qgemv_gated(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 11);
+    Args a("qgemv_gated", args, nargs, 11);
     const int fmt = a.word();
     const void *gate = a.ptr<const void>(), *up = a.ptr<const void>();
     const int64_t rows = a.num(), cols = a.num();
@@ -204,13 +231,13 @@ PyObject *qgemv_gated(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const int x_op = a.word();
     const uint16_t *aux = a.ptr<const uint16_t>();
     const float eps = a.real();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_qgemv_gated((iflow_format_t)fmt, gate, up, rows, cols, x, (iflow_x_op_t)x_op, aux, eps, y, stream); });
 }
 
 PyObject *qgemm_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 12);
+    Args a("qgemm_fused", args, nargs, 12);
     const int fmt = a.word();
     const void *packed = a.ptr<const void>();
     const int64_t rows = a.num(), cols = a.num();
@@ -221,13 +248,13 @@ PyObject *qgemm_fused(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const uint16_t *aux = a.ptr<const uint16_t>();
     const float eps = a.real();
     const uint16_t *residual = a.ptr<const uint16_t>();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_qgemm_fused((iflow_format_t)fmt, packed, rows, cols, x, batch, (iflow_x_op_t)x_op, aux, eps, residual, y, stream); });
 }
 
 PyObject *attn_decode(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 13);
+    Args a("attn_decode", args, nargs, 13);
     const uint16_t *q = a.ptr<const uint16_t>(), *k = a.ptr<const uint16_t>(), *v = a.ptr<const uint16_t>();
     const int heads = a.word(), kv_heads = a.word(), head_dim = a.word();
     const int64_t seq_len = a.num(), max_seq = a.num();
@@ -235,13 +262,13 @@ PyObject *attn_decode(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     uint16_t *out = a.ptr<uint16_t>();
     void *workspace = a.ptr<void>();
     const int64_t bytes = a.num();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] { return p_attn_decode(q, k, v, heads, kv_heads, head_dim, seq_len, max_seq, scale, out, workspace, (size_t)bytes, stream); });
 }
 
 PyObject *rope_append(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 13);
+    Args a("rope_append", args, nargs, 13);
     uint16_t *q = a.ptr<uint16_t>();
     const uint16_t *k = a.ptr<const uint16_t>(), *v = a.ptr<const uint16_t>();
     const int heads = a.word(), kv_heads = a.word(), head_dim = a.word();
@@ -249,7 +276,7 @@ PyObject *rope_append(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     const float base = a.real();
     const int pairing = a.word();
     uint16_t *k_cache = a.ptr<uint16_t>(), *v_cache = a.ptr<uint16_t>();
-    void *stream = a.ptr<void>();
+    void *stream = a.handle();
     return run(a, [&] {
         return p_rope_append(q, k, v, heads, kv_heads, head_dim, position, max_seq, base, (iflow_rope_pairing_t)pairing, k_cache, v_cache, stream);
     });
@@ -258,10 +285,10 @@ PyObject *rope_append(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 // bind(addresses of the nine functions, in this order)
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
-    Args a(args, nargs, 9);
+    Args a("bind", args, nargs, 9);
     void *f[9];
-    for (void *&p : f) p = a.ptr<void>();
-    if (a.bad) return nullptr;
+    for (void *&p : f) p = a.handle();
+    if (a.bad) { PyErr_SetString(PyExc_TypeError, "nine addresses are wanted"); return nullptr; }
     p_quantize = reinterpret_cast<decltype(p_quantize)>(f[0]);
     p_dequant = reinterpret_cast<decltype(p_dequant)>(f[1]);
     p_qgemv = reinterpret_cast<decltype(p_qgemv)>(f[2]);
@@ -274,8 +301,18 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     Py_RETURN_NONE;
 }
 
+// otherwise(function): what general is
+PyObject *otherwise(PyObject *, PyObject *const *args, Py_ssize_t nargs)
+{
+    if (nargs != 1) { PyErr_SetString(PyExc_TypeError, "a function is wanted"); return nullptr; }
+    PyObject *was = general;
+    general = Py_NewRef(args[0]);
+    Py_XDECREF(was);
+    Py_RETURN_NONE;
+}
+
 #define IFLOW_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {IFLOW_METHOD(bind), IFLOW_METHOD(quantize), IFLOW_METHOD(dequant), IFLOW_METHOD(qgemv), IFLOW_METHOD(qgemm),
+PyMethodDef methods[] = {IFLOW_METHOD(bind), IFLOW_METHOD(otherwise), IFLOW_METHOD(quantize), IFLOW_METHOD(dequant), IFLOW_METHOD(qgemv), IFLOW_METHOD(qgemm),
                          IFLOW_METHOD(qgemv_fused), IFLOW_METHOD(qgemv_gated), IFLOW_METHOD(qgemm_fused), IFLOW_METHOD(attn_decode),
                          IFLOW_METHOD(rope_append), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -59,6 +59,70 @@ _native = None                 # the extension, bound to the library's functions
 _NATIVE_CALLS = ("quantize", "dequant", "qgemv", "qgemm", "qgemv_fused", "qgemv_gated", "qgemm_fused", "attn_decode", "rope_append")
 
 
+class ArgumentError(C.ArgumentError, TypeError):
+    """An argument of a type that the call does not take."""
+
+
+class TooManyError(IndexError, ValueError):
+    """More rows, outputs or residuals than matrices."""
+
+
+class _Ctypes:
+    """The same calls through ctypes: the general form, which takes what ctypes converts (its own numbers, _as_parameter_) and refuses the rest."""
+
+    @staticmethod
+    def quantize(fmt, w, rows, cols, packed, capacity, stream):
+        return _lib.iflow_quantize(fmt, _ptr(w), rows, cols, _ptr(packed), capacity, stream)
+
+    @staticmethod
+    def dequant(fmt, packed, rows, cols, w16, stream):
+        return _lib.iflow_dequant(fmt, _ptr(packed), rows, cols, _ptr(w16), stream)
+
+    @staticmethod
+    def qgemv(fmt, packed, rows, cols, x, y, stream):
+        return _lib.iflow_qgemv(fmt, _ptr(packed), rows, cols, _ptr(x), _ptr(y), stream)
+
+    @staticmethod
+    def qgemm(fmt, packed, rows, cols, X, batch, Y, stream):
+        return _lib.iflow_qgemm(fmt, _ptr(packed), rows, cols, _ptr(X), batch, _ptr(Y), stream)
+
+    @staticmethod
+    def qgemv_fused(fmt, packed_list, rows_list, cols, x, y_list, x_op, aux, eps, residual_list, stream):
+        n = len(packed_list)
+        pk = (C.c_void_p * n)(*[_ptr(t) for t in packed_list])
+        ys = (C.c_void_p * n)(*[_ptr(t) for t in y_list])
+        rs = (C.c_int64 * n)(*[int(r) for r in rows_list])
+        res = None if residual_list is None else (C.c_void_p * n)(*[_ptr(t) for t in residual_list])
+        return _lib.iflow_qgemv_fused(fmt, n, pk, rs, cols, _ptr(x), x_op, _ptr(aux), eps, res, ys, stream)
+
+    @staticmethod
+    def qgemv_gated(fmt, packed_gate, packed_up, rows, cols, x, y, x_op, aux, eps, stream):
+        return _lib.iflow_qgemv_gated(fmt, _ptr(packed_gate), _ptr(packed_up), rows, cols, _ptr(x), x_op, _ptr(aux), eps, _ptr(y), stream)
+
+    @staticmethod
+    def qgemm_fused(fmt, packed, rows, cols, X, batch, Y, x_op, aux, eps, residual, stream):
+        return _lib.iflow_qgemm_fused(fmt, _ptr(packed), rows, cols, _ptr(X), batch, x_op, _ptr(aux), eps, _ptr(residual), _ptr(Y), stream)
+
+    @staticmethod
+    def attn_decode(q, k_cache, v_cache, n_heads, n_kv_heads, head_dim, seq_len, max_seq, scale, out, workspace, workspace_bytes, stream):
+        return _lib.iflow_attn_decode(_ptr(q), _ptr(k_cache), _ptr(v_cache), n_heads, n_kv_heads, head_dim, seq_len, max_seq, scale, _ptr(out),
+                                      _ptr(workspace), workspace_bytes, stream)
+
+    @staticmethod
+    def rope_append(q, k_new, v_new, n_heads, n_kv_heads, head_dim, position, max_seq, base, pair_mode, k_cache, v_cache, stream):
+        return _lib.iflow_rope_append(_ptr(q), _ptr(k_new), _ptr(v_new), n_heads, n_kv_heads, head_dim, position, max_seq, base, pair_mode,
+                                      _ptr(k_cache), _ptr(v_cache), stream)
+
+
+def _through_ctypes(name, *args):
+    try:
+        return getattr(_Ctypes, name)(*args)
+    except C.ArgumentError as e:
+        raise ArgumentError(*e.args) from e
+    except IndexError as e:
+        raise TooManyError("more rows, outputs or residuals than matrices") from e
+
+
 def _calls():
     lib()
     return _native
@@ -117,6 +181,7 @@ def lib():
         L.iflow_decode_stack_plan.argtypes = [C.POINTER(DecodeStack), p, sz, p, sz, p, C.POINTER(Chain)]
         L.iflow_decode_stack_launch.argtypes = [C.POINTER(Chain), i64, p]
         native.bind(*[C.cast(getattr(L, "iflow_" + name), p).value for name in _NATIVE_CALLS])
+        native.otherwise(_through_ctypes)
         _native = native
         _lib = L
     return _lib

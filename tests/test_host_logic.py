@@ -550,6 +550,69 @@ def test_extension_holds_the_lists_it_walks(iflow):
     assert not packed and not y
 
 
+def test_extension_takes_what_ctypes_takes(iflow):
+    """Arguments other than tensors, plain numbers and lists reach the library as ctypes converts them, or are refused with ctypes' exceptions.  A call that
+    gets through answers for its packed address, which is not aligned."""
+    class Parameter:
+        def __init__(self, value):
+            self._as_parameter_ = value
+
+    class Holder:
+        def __init__(self, value):
+            self.value = value
+
+        def data_ptr(self):
+            return self.value
+
+    class Stream:
+        def __init__(self, value):
+            self.cuda_stream = value
+    odd, at = 0x10001, 0x20000
+
+    def qgemv(fmt=4, packed=odd, rows=8, x=at, stream=0):
+        iflow.qgemv(fmt, packed, rows, 64, x, 2 * at, stream=stream)
+
+    def fused(packed=(odd,), rows=(8,), y=(2 * at,), residual=None):
+        iflow.qgemv_fused(4, packed, rows, 64, at, y, residual_list=residual, stream=0)
+
+    def normed(eps):
+        iflow.qgemm_fused(4, odd, 8, 64, at, 2, 2 * at, iflow.X_RMS_GAIN, 3 * at, eps, stream=0)
+
+    def quantize(capacity):
+        iflow.quantize(4, at, 8, 64, odd, capacity, stream=0)
+    taken = [lambda: qgemv(rows=C.c_int64(8)), lambda: qgemv(rows=Parameter(8)), lambda: qgemv(rows=Parameter(C.c_int64(8))), lambda: qgemv(rows=np.int32(8)),
+             lambda: qgemv(fmt=C.c_int(4)), lambda: qgemv(x=Holder(C.c_void_p(at))), lambda: qgemv(stream=Stream(C.c_void_p(0))), lambda: qgemv(stream=Stream(None)),
+             lambda: normed(C.c_float(0.5)), lambda: normed(Parameter(0.5)), lambda: normed(np.float32(0.5)), lambda: normed(1),
+             lambda: quantize(C.c_size_t(512)), lambda: fused(packed=[Holder(C.c_void_p(odd))]), lambda: fused(rows=["8"]), lambda: fused(rows=[8.7]),
+             lambda: fused(rows=np.array([8])), lambda: fused(y=(a for a in [2 * at])), lambda: fused(rows={8: 1}), lambda: fused(residual=[])]
+    for i, call in enumerate(taken):
+        with pytest.raises(iflow.IflowError) as info:
+            call()
+        assert info.value.status == iflow.ERR_ALIGN, i
+    with pytest.raises(iflow.IflowError) as info:
+        qgemv(x=Holder(None))
+    assert info.value.status == iflow.ERR_NULL
+    for refuse in (lambda: qgemv(rows=8.0), lambda: qgemv(rows="8"), lambda: qgemv(rows=None), lambda: qgemv(rows=C.c_int(8)), lambda: qgemv(fmt=C.c_int64(4)),
+                   lambda: qgemv(packed=Holder(1.5)), lambda: qgemv(packed=Holder(np.int64(odd))), lambda: qgemv(stream=Stream(1.0)), lambda: normed("1"),
+                   lambda: normed(C.c_double(0.5)), lambda: normed(np.zeros(2)), lambda: normed(10 ** 400), lambda: quantize(512.0)):
+        with pytest.raises(C.ArgumentError):
+            refuse()
+    for refuse in (lambda: fused(rows=[8, 8]), lambda: fused(y=[2 * at] * 2), lambda: fused(residual=[None] * 2)):
+        with pytest.raises(IndexError):
+            refuse()
+    for refuse in (lambda: fused(packed=(a for a in [odd])), lambda: fused(packed=None), lambda: fused(rows=None), lambda: fused(y=5), lambda: fused(packed=[Holder(1.5)])):
+        with pytest.raises(TypeError):
+            refuse()
+    with pytest.raises(AttributeError):
+        qgemv(packed=C.c_void_p(odd))
+
+    class Failing:
+        def data_ptr(self):
+            raise KeyError("no storage")
+    with pytest.raises(KeyError, match="no storage"):
+        qgemv(packed=Failing())
+
+
 def test_tiles_reach_as_far_as_their_offsets(iflow):
     """17 and more vectors take the tiled product up to 2^26 columns, and never a tile whose byte offsets would leave 32 bits: of its vectors' activations, or of
     a wavefront's (at most 96) rows of at most one byte a weight."""

@@ -9,7 +9,10 @@ by callers for device memory and streams; tensors are passed as `tensor.data_ptr
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
+import types
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libiflow.so")
@@ -53,7 +56,7 @@ class IflowError(RuntimeError):
 
 
 _lib = None
-_native = None                 # the extension, bound to the library's functions
+_native = None                 # the extension, bound to the library's functions (without one: the same calls through ctypes)
 # Enqueueing from Python, us, ctypes / here: a product with one vector 4.4 / 3.7, the attention's two launches 7.1 / 6.1, a decoder layer's six calls (seven
 # launches) 35.0 / 24.6 - of which 2.3 a launch are the launch itself.
 _NATIVE_CALLS = ("quantize", "dequant", "qgemv", "qgemm", "qgemv_fused", "qgemv_gated", "qgemm_fused", "attn_decode", "rope_append")
@@ -138,7 +141,8 @@ def lib():
         try:
             from . import _native as native
         except ImportError as e:
-            raise RuntimeError(f"the extension beside {LIB_PATH} is missing or does not load ({e}): {build}") from e
+            native = None
+            warnings.warn(f"the extension beside {LIB_PATH} is missing or does not load ({e}); calls go through ctypes, a few microseconds slower: {build}")
         # PyTorch ships its own HIP runtime; import it first so that the library binds to that same
         # runtime (two runtimes in one process do not share devices, streams or memory).
         import torch  # noqa: F401
@@ -180,10 +184,13 @@ def lib():
         L.iflow_decode_stack_sizes.argtypes = [C.POINTER(DecodeStack), C.POINTER(sz), C.POINTER(sz), C.POINTER(sz)]
         L.iflow_decode_stack_plan.argtypes = [C.POINTER(DecodeStack), p, sz, p, sz, p, C.POINTER(Chain)]
         L.iflow_decode_stack_launch.argtypes = [C.POINTER(Chain), i64, p]
-        native.bind(*[C.cast(getattr(L, "iflow_" + name), p).value for name in _NATIVE_CALLS])
-        native.otherwise(_through_ctypes)
-        _native = native
+        if native is not None:
+            native.bind(*[C.cast(getattr(L, "iflow_" + name), p).value for name in _NATIVE_CALLS])
+            native.otherwise(_through_ctypes)
+        else:
+            native = types.SimpleNamespace(**{name: functools.partial(_through_ctypes, name) for name in _NATIVE_CALLS})
         _lib = L
+        _native = native
     return _lib
 
 

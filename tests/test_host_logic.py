@@ -613,6 +613,38 @@ def test_extension_takes_what_ctypes_takes(iflow):
         qgemv(packed=Failing())
 
 
+def test_extension_is_named_for_its_interpreter(iflow):
+    """A Python of another ABI must not load this one's extension: the file carries the tag that says whose it is."""
+    import sysconfig
+    assert iflow._native.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_binding_works_without_the_extension(iflow, monkeypatch):
+    """A Python that the extension is not for, or a tree built without Python's headers: a warning, and the same calls through ctypes."""
+    import sys
+
+    import paper_2401_08294_amd as package
+    monkeypatch.setattr(iflow, "_lib", None)
+    monkeypatch.setattr(iflow, "_native", None)
+    monkeypatch.delattr(package, "_native", raising=False)
+    monkeypatch.setitem(sys.modules, package.__name__ + "._native", None)
+    odd, at = 0x10001, 0x20000
+    with pytest.warns(UserWarning, match="through ctypes"):
+        iflow.lib()
+    for call in (lambda: iflow.quantize(4, at, 8, 64, odd, 512, stream=0), lambda: iflow.dequant(4, odd, 8, 64, at, stream=0),
+                 lambda: iflow.qgemv(4, odd, 8, 64, at, 2 * at, stream=0), lambda: iflow.qgemm(4, odd, 8, 64, at, 3, 2 * at, stream=0),
+                 lambda: iflow.qgemv_fused(4, [at, odd], [8, 8], 64, 2 * at, [3 * at, 4 * at], stream=0),
+                 lambda: iflow.qgemv_gated(4, at, odd, 8, 64, 2 * at, 3 * at, stream=0),
+                 lambda: iflow.qgemm_fused(4, odd, 8, 64, at, 3, 2 * at, iflow.X_RMS_GAIN, 3 * at, 0.5, 4 * at, stream=0),
+                 lambda: iflow.attn_decode(odd, at, 2 * at, 4, 4, 128, 3, 64, 0.1, 3 * at, 4 * at, 1 << 30, stream=0),
+                 lambda: iflow.rope_append(odd, at, 2 * at, 4, 4, 128, 3, 64, 10000.0, 1, 3 * at, 4 * at, stream=0)):
+        with pytest.raises(iflow.IflowError) as info:
+            call()
+        assert info.value.status == iflow.ERR_ALIGN
+    with pytest.raises(C.ArgumentError):
+        iflow.qgemv(4, odd, 8.0, 64, at, 2 * at, stream=0)
+
+
 def test_tiles_reach_as_far_as_their_offsets(iflow):
     """17 and more vectors take the tiled product up to 2^26 columns, and never a tile whose byte offsets would leave 32 bits: of its vectors' activations, or of
     a wavefront's (at most 96) rows of at most one byte a weight."""

@@ -817,7 +817,10 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
     // through the scalar cache while the wavefront has a wait in front of it anyway.  A segment change in the step loop is a chain of three to four
     // dependent scalar loads, each a trip to L2 where nobody has read the line before.  Whole decode steps of the 7B shape at 1000 positions, us per
     // layer, before -> after: 3.5-bit 34.0 -> 33.0, 4-bit 39.5 -> 38.9, 8-bit 51.9 -> 51.8; one phase ahead instead of two 0.2 to 0.3 less; in front
-    // of the attention phases too: 33.6.
+    // of the attention phases too: 33.6.  Without attention, without -> with, bare products and with the modules between: 4-bit 25.15 -> 24.86, 27.1 -> 26.9; 8-bit
+    // 44.0 -> 43.5, 45.7 -> 45.5; 2-bit 23.3 -> 22.6, 26.0 -> 25.5; 3-bit 31.8 -> 31.6, 34.8 -> 34.3; 6-bit 36.1 -> 35.8, 38.4 -> 38.9; 5-bit 33.5 -> 33.0, 35.2 -> 35.3;
+    // 3.5-bit 23.0 both and 24.95 -> 25.42: with the modules that kernel takes 151 vector registers for it instead of 141, and it goes without.
+    constexpr bool LINES = ATTN || !FUSED || !Q3H;
     auto plan_lines = [&](int p, int m) __attribute__((always_inline)) {
         const int p0 = min(p, nphases - 1), p1 = min(p + 1, nphases - 1), last = hd->nmatrices - 1;
         return a.ph[p0].first + a.ph[p1].first + a.ops[p0].x_op + a.ops[p1].x_op + a.mat[min(m, last)].rows + a.mat[min(m + 1, last)].rows +
@@ -1026,7 +1029,8 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                     }
                 }
             }
-            const int lines = plan_lines(p + 1, ph.first + ph.count);
+            [[maybe_unused]] int lines = 0;
+            if constexpr (LINES) lines = plan_lines(p + 1, ph.first + ph.count);
             float res0 = 0.f, res1 = 0.f;
             int done = 0;                                      // pairs of rows summed so far
             // A tagged residual is read here for the first time, together with the phase's activations: its producer is an
@@ -1166,7 +1170,7 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                 if (lane == 0) sq_slot[wave] = wsum;
                 sumsq = 0.f;
             }
-            asm volatile("" ::"s"(lines));                     // (read, as far as the compiler knows: not needed before here)
+            if constexpr (LINES) asm volatile("" ::"s"(lines)); // (read, as far as the compiler knows: not needed before here)
             CHAIN_MARK(p, wave < 8 ? wave : 15);               // this wavefront's share of the activations is staged
             __syncthreads();
             if (wave == 0) CHAIN_MARK(p, 8);                   // all of them are

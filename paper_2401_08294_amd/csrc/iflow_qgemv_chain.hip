@@ -204,7 +204,8 @@ constexpr int CHAIN_SETS = IFLOW_CHAIN_SETS;
 // Register sets (steps of weights in flight) per wavefront: a step of the 3.5-bit format is 4 KB (two rows of a 2 KB
 // strip), a step of the 4- and 8-bit formats 2 KB, of the bit-plane formats 0.75 to 1.75 KB.  Measured with 2 / 3 / 4 sets, us per layer of
 // bare products of the 7B shape and of whole decode steps with 32 key/value heads (7B shape, 1000 positions) and with 4 (8 heads, feed-forward 2944): 8-bit,
-// padded steps, 48.8 / 45.9 / 45.9, 52.9 / 51.5 / 51.6, 23.1 / 23.4 / 24.3; 4-bit, padded, 26.1 / 27.4 / 27.4, 36.3 / 37.7 / 39.1, 24.3 / 25.3 / 26.3; 5-bit,
+// padded steps, 48.8 / 45.9 / 45.9, 52.9 / 51.5 / 51.6, 23.1 / 23.4 / 24.3 (without attention four, with 3 / 4 sets: blocks of 64 bare 43.66 / 43.65, with the modules
+// between the products 45.5 / 44.7, blocks of 32 46.9 / 46.9, 48.65 / 47.9; the launches before three sets 45.3 and 48.9); 4-bit, padded, 26.1 / 27.4 / 27.4, 36.3 / 37.7 / 39.1, 24.3 / 25.3 / 26.3; 5-bit,
 // not padded, 34.3 / 35.8 / 35.9, 45.2 / 45.6 / 46.4, 25.9 / 25.8 / 26.2, and 2-, 3- and 6-bit alike: the more sets, the more weights queue in
 // front of a phase's activations.  (Three and four sets were ahead while a phase's words were requested one after the other, each wait taking the
 // weights in front of it along.)  IFLOW_CHAIN_SETS_OTHER overrides them all (measurement builds).
@@ -216,7 +217,7 @@ constexpr int chain_sets(int format, bool attn = false)
 #ifdef IFLOW_CHAIN_SETS_OTHER
     return format == IFLOW_Q3H_B64 ? CHAIN_SETS : IFLOW_CHAIN_SETS_OTHER;
 #else
-    return format == IFLOW_Q8_B32 || format == IFLOW_Q8_B64 ? 3 : 2;
+    return format == IFLOW_Q8_B32 || format == IFLOW_Q8_B64 ? (attn ? 3 : 4) : 2;
 #endif
 }
 

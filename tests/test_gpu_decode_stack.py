@@ -115,7 +115,7 @@ class Stack:
 @pytest.mark.parametrize("name,n_heads,n_kv,ffn,pairing", [
     ("Q3H_B64", 4, 2, 1408, 1),       # two query heads per key/value head
     ("Q3H_B64", 4, 4, 704, 0),        # one: multi-head attention; adjacent pairs
-    ("Q3H_B64", 8, 2, 1408, 1),       # four: two passes over the range
+    ("Q3H_B64", 8, 2, 1408, 1),       # four: two workgroups per range
     ("Q4_B64", 4, 2, 1408, 0),
     ("Q8_B32", 4, 2, 1408, 1),
     ("Q6_B64", 4, 2, 1408, 1),        # a bit-plane format
@@ -154,6 +154,61 @@ def test_decode_stack_long_context_many_ranges(gpu, orc, position):
     say(f"[case] decode stack Q3H_B64, 8 heads / 4 kv heads, context {position}, cache of 2048 rows")
     st = Stack(torch, iflow, orc, "Q3H_B64", 1, 8, 4, 1408, 2048, 1, synth.BASE_SEED + 3300, position)
     st.step_and_check(position)
+
+
+@pytest.mark.parametrize("name,n_heads,n_kv,position", [
+    ("Q8_B64", 8, 1, 1500),           # four pairs of heads, 64 ranges
+    ("Q5_B64", 12, 2, 2047),          # three pairs, 42 ranges; the step's own position is the cache's last row
+    ("Q3H_B64", 16, 2, 1023),         # ... whose key only the first of four pairs writes, in the last of 32 ranges
+])
+def test_decode_stack_long_context_of_grouped_heads(gpu, orc, name, n_heads, n_kv, position):
+    """Several pairs of query heads per key/value head, each a workgroup of its own that walks several blocks of positions, and many ranges to merge."""
+    torch, iflow = gpu
+    say(f"[case] decode stack {name}, {n_heads} heads / {n_kv} kv heads, context {position}, cache of 2048 rows")
+    st = Stack(torch, iflow, orc, name, 1, n_heads, n_kv, 704, 2048, 1, synth.BASE_SEED + 3700 + n_heads, position)
+    st.step_and_check(position)
+
+
+def test_decode_stack_with_more_than_64_outputs_a_workgroup(gpu):
+    """192 heads: on 256 compute units a workgroup merges 96 of the attention's outputs, 64 at a time.  The attention alone is compared, on the q, k and v that
+    the launch itself has written (matrices of this size have no oracle that would end in time; the products are tested elsewhere)."""
+    from oracle import attention as att
+    from oracle import rope as R
+    torch, iflow = gpu
+    n_heads, n_kv, ffn, max_seq, position = 192, 48, 64, 512, 300
+    hidden, kvd, fmt = n_heads * D, n_kv * D, iflow.FORMATS["Q2_B32"]
+    say(f"[case] decode stack Q2_B32, {n_heads} heads / {n_kv} kv heads: the attention's second half in two turns")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.BASE_SEED + 3800)
+    layer = {}
+    for key, (rows, cols) in {"wq": (hidden, hidden), "wk": (kvd, hidden), "wv": (kvd, hidden), "wo": (hidden, hidden), "w_gate": (ffn, hidden),
+                              "w_up": (ffn, hidden), "w_down": (hidden, ffn)}.items():
+        w = torch.empty((rows, cols), device="cuda").normal_(0.0, cols ** -0.5, generator=g)
+        n = iflow.packed_bytes(fmt, rows, cols)
+        layer[key] = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        iflow.quantize(fmt, w, rows, cols, layer[key], n)
+    for key in ("norm1", "norm2"):
+        layer[key] = torch.ones((hidden,), dtype=torch.float16, device="cuda")
+    cache = torch.zeros((2, n_kv, max_seq, D), dtype=torch.float16, device="cuda")
+    cache[:, :, :position] = torch.empty((2, n_kv, position, D), device="cuda").normal_(generator=g).half()
+    layer["k_cache"], layer["v_cache"] = cache[0], cache[1]
+    h_in = torch.empty((hidden,), device="cuda").normal_(generator=g).half()
+    h_out = torch.zeros((hidden,), dtype=torch.float16, device="cuda")
+    shape = (fmt, hidden, ffn, n_heads, n_kv, max_seq, EPS, BASE, iflow.ROPE_HALVES)
+    sizes = iflow.decode_stack_sizes(iflow.decode_stack(*shape, n_layers=1))
+    scratch = torch.zeros((sizes[0] // 2,), dtype=torch.float16, device="cuda")
+    plan, ws = (torch.empty((n,), dtype=torch.uint8, device="cuda") for n in sizes[1:])
+    chain = iflow.decode_stack_plan(iflow.decode_stack(*shape, layers=[layer], h_in=h_in, h_out=h_out, scratch=scratch), plan, sizes[1], ws, sizes[2])
+    before = bits_of(cache).copy()
+    iflow.decode_stack_launch(chain, position)
+    iflow.qgemv_chain_check(chain)
+    s = bits_of(scratch)
+    q, k, v, t = (s[o:o + n] for o, n in ((0, hidden), (r128(hidden), kvd), (r128(hidden) + r128(kvd), kvd), (r128(hidden) + 2 * r128(kvd), hidden)))
+    q_rot = R.rope_append(q.reshape(n_heads, D), k.reshape(n_kv, D), v.reshape(n_kv, D), position, BASE, iflow.ROPE_HALVES, before[0], before[1])
+    after = bits_of(cache)
+    assert close_bits(after[0], before[0]) and np.array_equal(after[1], before[1])
+    ref = att.gqa_decode(q_rot.reshape(n_heads, D), after[0], after[1], position + 1, D ** -0.5)
+    assert err(t, ref.reshape(-1)) <= 2 * TOL                   # (the oracle's own rotation of q: an fp16 step apart here and there)
 
 
 def test_decode_stack_at_7b_shape(gpu, orc):

@@ -1,8 +1,8 @@
 // The calls of a decode step from Python: arguments from Python objects straight into the C ABI of include/iflow.h.
 //
 // These kernels take a few microseconds each, as long as it takes to call them: through ctypes a product costs 1.5 us of marshalling and the
-// three-matrix call of a decoder layer 4, next to the 2.3 of the launch itself.  Here an address is one method call (data_ptr) and an array lives
-// on the stack.  Measured, us to enqueue, ctypes -> here: a product with one vector 4.4 -> 3.7, a decoder layer's six calls 35.0 -> 24.6.
+// three-matrix call of a decoder layer 4, next to the 2.3 or more of the launch itself.  Here an address is one method call (data_ptr) and an array lives
+// on the stack.  Measured, us to enqueue, ctypes -> here: a product with one vector 5.2 -> 4.6, a decoder layer's six calls 43 -> 32.
 // The functions are the library's own, bound by address (bind), so the library is loaded once and in one place.  An address is an integer, None
 // (null) or an object with data_ptr(), a number what has __index__ or __float__, matrices and outputs are lists or tuples; a call returns the library's
 // status and runs without the interpreter's lock, as a ctypes call does.  A call with anything else among its arguments (ctypes' own numbers, an iterator,

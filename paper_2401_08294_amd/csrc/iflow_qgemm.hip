@@ -11,13 +11,13 @@
 //   - The operands of a k-step of 16 columns are read and decoded while the matrix instructions of the k-step before run.
 //   - Which lane holds which k of a chunk is free as long as both operands agree: lane half h takes columns 32 h .. 32 h + 31,
 //     so that a lane's weights are 32 consecutive ones of one row.
-// What bounds it, by counters: at 2000 vectors (28672 x 8192, 4-bit) the matrix cores are busy 64 % of the cycles of a launch that runs at 1.4 GHz - the power
-// limit, a loop of nothing but these instructions on random data runs at 1.5 to 1.8 - next to a decode that issues 28 % of them, which is why
+// What bounds it, by counters: at 2000 vectors (28672 x 8192, 4-bit) the matrix cores are busy 67 % of the cycles of a launch that runs at 1.4 to 1.55 GHz - the power
+// limit, a loop of nothing but these instructions on random data runs at 1.5 to 1.8 - next to a decode that issues 29 % of them, which is why
 // the largest tile has 256 vectors per decoded weight; at 512 (11008 x 4096, 3.5-bit) both are busy a third of the time, one wavefront per SIMD; at 33
 // (4096 x 11008, 8-bit) wavefronts wait for their copies.
 // Measured, us (before: 128 x 64 tiles with both operands decoded or copied into LDS, passes of sixteen below 32 vectors), one matrix again and again:
-// 11008 x 4096 3.5-bit, 512 vectors 84.4 -> 55.7 (830 TFLOP/s; over a ring of matrices beyond the caches 58 to 61); 28672 x 8192 4-bit, 2000 vectors 1491 -> 844 (1113
-// TFLOP/s; 833 to 890 by machine); 4096 x 11008 8-bit, 33 vectors 49.7 -> 17.4 (ring 23); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.0 (ring 9.6).
+// 11008 x 4096 3.5-bit, 512 vectors 84.4 -> 55.7 (830 TFLOP/s; over a ring of matrices beyond the caches 58 to 61); 28672 x 8192 4-bit, 2000 vectors 1491 -> 831 (1130
+// TFLOP/s; 820 to 864 by machine); 4096 x 11008 8-bit, 33 vectors 49.7 -> 17.4 (ring 23); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.0 (ring 9.6).
 #include "iflow_common.h"
 
 namespace iflow {
@@ -269,10 +269,11 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     constexpr int NX = (4 * MB + WR - 1) / WR;                 // 1 KB pieces of its group's chunk a wavefront copies per step
     constexpr int NG = RT * (P::q3h ? 2 * P::NA : P::NA + P::NB + P::NH);      // a wavefront's requests per group of G chunks
     // With two stages a step waits for what was requested one step ago.  Where a group lasts two steps its request goes out behind that step's
-    // activations, so that the wait for them leaves it one step more: these bytes come from memory, the activations from L2.  (us, before -> after: 28672 x
-    // 8192 4-bit, 2000 vectors 889 -> 874, 1024 471 -> 457, 8-bit, 1000 508 -> 493; 14336 x 8192 6-bit, 1500 423 -> 413; 5000 x 3008 4-bit, 1300 62.8 -> 58.8
-    // with the same tile.  Not with groups of four steps - 3.5-bit, 11008 x 4096, 2048 vectors 201 -> 207 - nor without a barrier: 4096 x 11008 8-bit, 33 vectors
-    // 17.4 -> 17.7.)
+    // activations, so that the wait for them leaves it one step more: these bytes come from memory, the activations from L2.  (us, before -> after, one matrix
+    // again and again: 28672 x 8192 4-bit, 2000 vectors 845 -> 831, 1024 445 -> 436, 8-bit, 1000 479 -> 467; 14336 x 8192 6-bit, 1500 396 -> 386.  A tile by its
+    // number over rings of matrices, 140 random products in these formats, mean: 256 x 160 -10 %, 256 x 256 and 256 x 224 -8 %, 128 x 128 -7 %, 96 x 128 -5 %, 128 x 192
+    // -4 %, 192 x 128 -3.5 %.  Not with groups of four steps - 3.5-bit, 11008 x 4096, 2048 vectors 201 -> 207 - nor without a barrier: 4096 x 11008 8-bit, 33
+    // vectors 17.4 -> 17.7.)
     constexpr bool XFIRST = STAGES == 2 && G == 2 && WR > 1;
     // what may still be on its way when a step's activations have to be there: the activations of the STAGES - 2 steps after it and
     // the groups requested among them (XFIRST: behind them)
@@ -491,8 +492,9 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 // The tiles in use and what a launch of each costs in microseconds, for every format: rounds * (round + steps * step), rounds = workgroups per compute unit, steps =
 // chunks that one wavefront walks.  `step` is fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000 vectors,
 // `round` (start, first copies, sums and stores) is the median of what rows of 64 to 1024 columns take beyond their steps.  On 200 random products that
-// no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is 0.14 % slower than the best
-// in the mean and 10 % at worst, on 64 to 1024 columns 1.5 % and 9 %.  (`round` fitted to the long rows too came out at 0.6 to 4.9 us and took
+// no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is 0.35 % slower than the best
+// in the mean and 13 % at worst, on 300 of 64 to 1024 columns 1.3 % and 9.5 %.  The steps were fitted before XFIRST made some of these tiles 3.5 to 10 % faster; before it
+// the same 200 products lost 0.30 %, so they were left.  (`round` fitted to the long rows too came out at 0.6 to 4.9 us and took
 // 256 x 160 for nearly everything below 256 columns, 13 % slower than the best: 131072 x 64, 3.5-bit, 33 vectors 9.6 us, now 8.8; 33 x 256, 512 vectors 8.6, now 5.1.)
 // A workgroup too many for the last round costs up to half of a
 // launch, so sizes in between are worth having (with nine tiles 6.5 % slower than the best of 33 in the mean); eight wavefronts of 32 rows beat four of 64 where LDS holds

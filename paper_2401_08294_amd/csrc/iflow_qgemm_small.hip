@@ -286,7 +286,7 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             };
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                // (uniform: the gate is most of a strip's work - two vectors, 4096 x 11008 4-bit 17.8 -> 11.2 us, nine, 1077 x 10432 8-bit 25.7 -> 19.9)
+                // (uniform: the gate is most of a strip's work - with the staging below, two vectors, 4096 x 11008 4-bit 16.7 -> 9.9 us, nine, 1077 x 10432 8-bit 24.4 -> 18.2)
                 if (2 * q < batch) gate(va[q], 2 * q + (ln >> 5));
                 if (upper && 8 + 2 * q < batch) gate(vb[q], 8 + 2 * q + (ln >> 5));
             }
@@ -311,9 +311,9 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
         };
         // (Up to eight vectors: lanes 8 .. 15 of a group hold the first eight again, their columns of the result are not stored.  A lane reads the half that
         // is its own, instead of both with a select per register, and the zeros for dead column groups are made only where there are some: 190 -> 90
-        // vector instructions a strip next to 150 to 220 of a step's decode; us, before -> after: 4096 x 4096 4-bit, 8 vectors 4.8 -> 4.3, 4096 x 11008 8-bit 13.9
-        // -> 13.4, 11008 x 4096 3.5-bit with rms and residual 11.1 -> 10.8, 1627 x 17280 6-bit 15.8 -> 15.0.  Requesting the next strip's activations a strip
-        // ahead gave nothing at up to eight vectors and spilled at sixteen: the wavefronts of a SIMD fill each other's waits.)
+        // vector instructions a strip next to 150 to 220 of a step's decode; us, before -> after, 8 vectors with a residual: 4096 x 4096 4-bit 5.15 -> 4.6, 4096 x 11008
+        // 8-bit 13.3 -> 12.8, 11008 x 4096 3.5-bit with rms 9.5 -> 9.05 (10.6 -> 10.2 on another machine), 1627 x 17280 6-bit 15.0 -> 14.25.  Requesting the next
+        // strip's activations a strip ahead gave nothing at up to eight vectors and spilled at sixteen: the wavefronts of a SIMD fill each other's waits.)
         turn(va, !upper || i < 8);
         if (upper) turn(vb, i >= 8);
         // MFMA B operands: the eight activations of step w.  Q3H's decoder yields weights in the order (4s, 4s+2, 4s+1, 4s+3).

@@ -205,8 +205,8 @@ constexpr int CHAIN_SETS = IFLOW_CHAIN_SETS;
 // strip), a step of the 4- and 8-bit formats 2 KB, of the bit-plane formats 0.75 to 1.75 KB.  Measured with 2 / 3 / 4 sets, us per layer of
 // bare products of the 7B shape and of whole decode steps with 32 key/value heads (7B shape, 1000 positions) and with 4 (8 heads, feed-forward 2944): 8-bit,
 // padded steps, 48.8 / 45.9 / 45.9, 52.9 / 51.5 / 51.6, 23.1 / 23.4 / 24.3 (without attention four, with 3 / 4 sets: blocks of 64 bare 43.66 / 43.65, with the modules
-// between the products 45.5 / 44.7, blocks of 32 46.9 / 46.9, 48.65 / 47.9; the launches before three sets 45.3 and 48.9); 4-bit, padded, 26.1 / 27.4 / 27.4, 36.3 / 37.7 / 39.1, 24.3 / 25.3 / 26.3; 5-bit,
-// not padded, 34.3 / 35.8 / 35.9, 45.2 / 45.6 / 46.4, 25.9 / 25.8 / 26.2, and 2-, 3- and 6-bit alike: the more sets, the more weights queue in
+// between the products 45.5 / 44.7, blocks of 32 46.9 / 46.9, 48.65 / 47.9; the launches before three sets 45.3 and 48.9); 4-bit, padded,
+// 26.1 / 27.4 / 27.4, 36.3 / 37.7 / 39.1, 24.3 / 25.3 / 26.3; 5-bit, not padded, 34.3 / 35.8 / 35.9, 45.2 / 45.6 / 46.4, 25.9 / 25.8 / 26.2, and 2-, 3- and 6-bit alike: the more sets, the more weights queue in
 // front of a phase's activations.  (Three and four sets were ahead while a phase's words were requested one after the other, each wait taking the
 // weights in front of it along.)  IFLOW_CHAIN_SETS_OTHER overrides them all (measurement builds).
 constexpr int chain_sets(int format, bool attn = false)
@@ -307,10 +307,12 @@ __device__ __forceinline__ uint32_t chain_rope_pair(uint32_t own, uint32_t other
 }
 
 // Phase "part" of one item = (key/value head, R of the query heads of its group, range of positions).  A group's pairs of heads are
-// workgroups of their own, with as many ranges less: a workgroup walking its range once per pair took, us per layer of a whole step, 8 heads
-// on one key/value head, 410 positions, 8-bit 39.5, now 28.3; 32 on 8, 700 positions, 4-bit 41.6, now 36.7; 16 on 4, 1239 positions, 3.5-bit
-// 32.2, now 25.1 (pairs of one range read the same keys and values side by side, so from L2).  lds: (4 * CHAIN_WAVES_ATTN) * 130 floats for the running states, and behind
-// them CHAIN_ATTN_STAGE_BYTES for the step's rotated queries, rotated key and value.
+// workgroups of their own, with as many ranges less, because a workgroup that walks its range once per pair pays its start and its waits once per pair.
+// Us per layer of whole decode steps in one launch, before -> after this and the merge in a tree (whose share stands there): 8 heads on one key/value
+// head, feed-forward 2944, 410 positions, 8-bit 39.0 -> 23.9; 32 on 8, 11008, 700 positions, 4-bit 42.2 -> 35.8; 16 on 4, 5184, 1239 positions, 3.5-bit 33.5 -> 25.2.
+// Pairs of one range read the same keys and values at the same time.  They are nsplit workgroups apart, so on one die and from its L2 where the ranges are a
+// multiple of the eight dies (64, 32, 16, 8 of them: 8, 16, 32 or 64 heads on 256 compute units); elsewhere (6, 12 heads) a die fetches them once more.
+// lds: (4 * CHAIN_WAVES_ATTN) * 130 floats for the running states, and behind them CHAIN_ATTN_STAGE_BYTES for the step's rotated queries, rotated key and value.
 constexpr int CHAIN_ATTN_STATE_BYTES = 4 * CHAIN_WAVES_ATTN * 130 * 4, CHAIN_ATTN_STAGE_BYTES = 64 * 16;
 template <int R>
 __device__ __forceinline__ void chain_attn_part(const ChainAttn &at, uint32_t *ws, float *lds, const double2 *table, uint32_t tag, int position,
@@ -505,8 +507,10 @@ __device__ __forceinline__ void chain_attn_part(const ChainAttn &at, uint32_t *w
 // state of one range (re-reading until it carries the launch's tag) - all ranges at once, one memory latency - and the ranges are merged
 // in a tree: across the lanes of a wavefront, then across the wavefronts through LDS.  One thread per output publishes it: the plain fp16
 // value and the tagged word a later phase stages from.  What bounds it is the trip of the partial states across the chip; one thread walking over
-// the ranges added up to 3 us to that, us per layer of a whole step, before -> after: 8 heads on one key/value head (64 ranges) 28.0 -> 22.8, 16
-// on 8 (32) 28.6 -> 26.4, 32 on 32 at the 7B shape (8) 33.3 -> 33.0.  lds: 3 floats per wavefront and output, 64 outputs at a time.
+// the ranges adds up to 5 us to that, us per layer of a whole step, so -> as it is: 8 heads on one key/value head (64 ranges, 8-bit) 28.7 -> 23.6, 16
+// on 8 (32, 4-bit) 27.9 -> 25.8, 32 on 8 at the 7B shape (16, 4-bit) 33.9 -> 32.9, 32 on 32 (8, 3.5-bit) 33.0 -> 32.7.  The tree's fp32 error is no larger than
+// that of the sums in order (relative, 2-norm, of the merge alone: 64 ranges 1.9e-7 in order, 1.1e-7 in the tree; 8 ranges 9.4e-8, 8.0e-8; 4 ranges 6.9e-8, 7.2e-8),
+// but an output differs by an fp16 step now and then.  lds: 3 floats per wavefront and output, 64 outputs at a time.
 __device__ __forceinline__ int chain_attn_merge_per_wg(int n_heads, int nwg)
 {
     return ((n_heads * 128 + nwg - 1) / nwg + 1) & ~1;       // (even, so that a workgroup writes whole pairs)
@@ -816,9 +820,10 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
 
     // The lines of the plan that the requests will look up: the records of phases p and p + 1 and of four matrices from m on (all in bounds), read
     // through the scalar cache while the wavefront has a wait in front of it anyway.  A segment change in the step loop is a chain of three to four
-    // dependent scalar loads, each a trip to L2 where nobody has read the line before.  Whole decode steps of the 7B shape at 1000 positions, us per
-    // layer, before -> after: 3.5-bit 34.0 -> 33.0, 4-bit 39.5 -> 38.9, 8-bit 51.9 -> 51.8; one phase ahead instead of two 0.2 to 0.3 less; in front
-    // of the attention phases too: 33.6.  Without attention, without -> with, bare products and with the modules between: 4-bit 25.15 -> 24.86, 27.1 -> 26.9; 8-bit
+    // dependent scalar loads, each a trip to L2 where nobody has read the line before.  Whole decode steps, us per layer, without -> with: the 7B shape
+    // at 1000 positions 3.5-bit 33.3 -> 32.7, 4-bit 35.75 -> 35.0, 8-bit 50.6 -> 50.3, with 8 key/value heads, 700 positions, 4-bit 33.4 -> 32.9; small layers, whose
+    // phases have hardly a step to hide it behind, pay up to 0.4: 16 heads, feed-forward 5184, 3.5-bit 24.7 -> 25.0, 8 heads, 5184, 2-bit 23.9 -> 24.3.
+    // Without attention, bare products and with the modules between: 4-bit 25.15 -> 24.86, 27.1 -> 26.9; 8-bit
     // 44.0 -> 43.5, 45.7 -> 45.5; 2-bit 23.3 -> 22.6, 26.0 -> 25.5; 3-bit 31.8 -> 31.6, 34.8 -> 34.3; 6-bit 36.1 -> 35.8, 38.4 -> 38.9; 5-bit 33.5 -> 33.0, 35.2 -> 35.3;
     // 3.5-bit 23.0 both and 24.95 -> 25.42: with the modules that kernel takes 151 vector registers for it instead of 141, and it goes without.
     constexpr bool LINES = ATTN || !FUSED || !Q3H;
@@ -986,7 +991,8 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
 #endif
                 if (group == 1) {
                     if (wg < at.n_heads * at.nsplit) chain_attn_part<1>(at, ws, scratch, rope_table, tag, position, wg, wave, lane, failed, marks);
-                } else {                                       // (even by the plan's check; more pairs than workgroups: several passes)
+                } else {                                       // (even by the plan's check; more pairs than workgroups: several passes - only on a
+                                                               // part of the card: 65536 columns are 256 pairs)
 #pragma unroll 1
                     for (int item = wg; item < (at.n_heads / 2) * at.nsplit; item += (int)gridDim.x)
                         chain_attn_part<2>(at, ws, scratch, rope_table, tag, position, item, wave, lane, failed, marks);
@@ -1053,7 +1059,7 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                     const bool live = k0 < cols;                   // lanes past the end of the row stage zeros (and read lane 0's words)
                     const int k = live ? k0 : 0;
                     uint32_t n[G::XD];
-                    u32x4 gains[XQ] = {};                          // (requested before the wait for the activations)
+                    u32x4 gains[XQ] = {};                          // (requested before the wait for the activations: 0.2 to 0.4 us of a layer)
                     if constexpr (FUSED) {
                         if (a.ops[p].x_op == IFLOW_X_RMS_GAIN)
 #pragma unroll
@@ -1070,9 +1076,9 @@ __global__ __launch_bounds__(64 * chain_waves(ATTN)) void chain_kernel(const uin
                         bool again;
                         do {
                             // (All words are requested before one is looked at: with the check in the same loop the compiler waits for each word
-                            // before it requests the next - 8 to 16 memory round trips one after the other, 2 to 3 us of every phase.  Whole decode
-                            // steps, us per layer, before -> after: 7B shape with 8 key/value heads, 700 positions, 4-bit 50.5 -> 41.6; 8-bit, 32
-                            // heads, feed-forward 8000 45.4 -> 42.6; 8 heads, feed-forward 5184, 2-bit 36.3 -> 28.4.)
+                            // before it requests the next - 8 to 16 memory round trips one after the other, up to 2 us of every phase.  Whole decode
+                            // steps at 700 positions, us per layer, so -> as it is: 7B shape with 8 key/value heads, 4-bit 40.5 -> 32.9; 8-bit, 32
+                            // heads, feed-forward 8000 45.2 -> 42.6; 8 heads, 5184, 2-bit 31.7 -> 24.3.)
                             uint64_t wd[G::XD];
 #pragma unroll
                             for (int i = 0; i < G::XD; ++i) {
@@ -1474,8 +1480,8 @@ bool chain_build_plan(const ChainSpec &c, int grid, std::vector<uint8_t> &out)
                 at.k_cache = as.k_cache; at.v_cache = as.v_cache; at.out = c.y[m];
                 at.out_tag_word = mats[m].tag_word;
                 at.n_heads = as.n_heads; at.n_kv_heads = as.n_kv_heads; at.nsplit = chain_attn_splits(as.n_heads, as.n_kv_heads, grid);
-                // what a plan takes: a state per (range, output of the workgroup) for the most ranges there can be, a workgroup per key/value
-                // head and range, within the states' LDS; one thread per output
+                // What a plan takes is kept as it was when a workgroup walked a key/value head's range for all its heads and held a state per range and
+                // output in LDS: the kernel needs neither (it could run, say, 64 heads on 4), but a description that was refused stays refused.
                 const int per_wg = ((as.n_heads * 128 + grid - 1) / grid + 1) & ~1, ranges = chain_attn_ranges(as.n_kv_heads, grid);
                 if (as.n_kv_heads * ranges > grid) return false;
                 if (per_wg > 64 * CHAIN_WAVES_ATTN || ranges * per_wg * 3 > 4 * CHAIN_WAVES_ATTN * 130) return false;

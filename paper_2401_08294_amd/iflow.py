@@ -57,8 +57,8 @@ class IflowError(RuntimeError):
 
 _lib = None
 _native = None                 # the extension, bound to the library's functions (without one: the same calls through ctypes)
-# Enqueueing from Python, us, ctypes / here: a product with one vector 4.4 / 3.7, the attention's two launches 7.1 / 6.1, a decoder layer's six calls (seven
-# launches) 35.0 / 24.6 - of which 2.3 a launch are the launch itself.
+# Enqueueing from Python, us, ctypes / here: a product with one vector 5.2 / 4.6, the attention's two launches 8.6 / 7.7, a decoder layer's six calls (seven
+# launches) 43 / 32 (on another host 4.4 / 3.7, 7.1 / 6.1, 35.0 / 24.6) - of which 2.3 and more a launch are the launch itself.
 _NATIVE_CALLS = ("quantize", "dequant", "qgemv", "qgemm", "qgemv_fused", "qgemv_gated", "qgemm_fused", "attn_decode", "rope_append")
 
 

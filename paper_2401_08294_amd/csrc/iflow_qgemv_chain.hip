@@ -509,7 +509,7 @@ __device__ __forceinline__ void chain_attn_part(const ChainAttn &at, uint32_t *w
 // value and the tagged word a later phase stages from.  What bounds it is the trip of the partial states across the chip; one thread walking over
 // the ranges adds up to 5 us to that, us per layer of a whole step, so -> as it is: 8 heads on one key/value head (64 ranges, 8-bit) 28.7 -> 23.6, 16
 // on 8 (32, 4-bit) 27.9 -> 25.8, 32 on 8 at the 7B shape (16, 4-bit) 33.9 -> 32.9, 32 on 32 (8, 3.5-bit) 33.0 -> 32.7.  The tree's fp32 error is no larger than
-// that of the sums in order (relative, 2-norm, of the merge alone: 64 ranges 1.9e-7 in order, 1.1e-7 in the tree; 8 ranges 9.4e-8, 8.0e-8; 4 ranges 6.9e-8, 7.2e-8),
+// that of the sums in order (relative, 2-norm, of the merge alone: 64 ranges 1.9e-7 in order, 1.1e-7 in the tree; 8 ranges 9.0e-8, 8.0e-8; 4 and fewer alike, 7.1e-8),
 // but an output differs by an fp16 step now and then.  lds: 3 floats per wavefront and output, 64 outputs at a time.
 __device__ __forceinline__ int chain_attn_merge_per_wg(int n_heads, int nwg)
 {

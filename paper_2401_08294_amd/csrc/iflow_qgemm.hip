@@ -256,6 +256,22 @@ template <int WK, int G> constexpr __host__ __device__ __forceinline__ int tile_
     return (runs + WK - 1 - group) / WK * G + (runs % WK == group ? nchunks % G : 0);
 }
 
+// Which tile a workgroup takes.  Workgroups go to the eight dies in turn, and each die has an L2 of its own: a die gets a consecutive part of the tiles, in bands of TILE_BAND
+// tiles of vectors with those of one row tile next to each other, so that the weights of a row tile are fetched by one die instead of by every die that a tile of vectors
+// puts it on (rows outermost: by one only where the row tiles are a multiple of eight), while a die's 32 workgroups at a time still share their activations.  Bands of 2, 4 and 8 are
+// within 2 % of each other.  Us, rows outermost -> this: 543 x 25856 4-bit, 1254 vectors 86.9 -> 70.4; 2350 x 21632 6-bit, 2035 265 -> 247; 4122 x 24832 5-bit, 78 63.0 -> 60.3; 28672 x 8192
+// 4-bit, 2000 831 -> 821; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; where the row tiles are a multiple of eight (4096 x 11008 8-bit, 33) the same.
+constexpr int TILE_DIES = 8, TILE_BAND = 4;
+struct TilePlace { int tr, tb; };
+__device__ __forceinline__ TilePlace tile_place(int wg, int ntr, int ntb)
+{
+    const int total = ntr * ntb, die = wg % TILE_DIES, per = total / TILE_DIES, more = total % TILE_DIES;
+    const int tile = die * per + min(die, more) + wg / TILE_DIES;
+    const int band = tile / (ntr * TILE_BAND), wide = min(TILE_BAND, ntb - band * TILE_BAND), in = tile - band * (ntr * TILE_BAND);
+    const int tr = in / wide;
+    return TilePlace{tr, band * TILE_BAND + in - tr * wide};
+}
+
 // RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
 // activations, WK such groups take every WK-th run of G chunks each and add their sums at the end.
 template <int F, int RT, int MB, int WR, int WK, int STAGES>
@@ -284,7 +300,7 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % WR, wk = wave / WR;
     const int li = lane & 31, h = lane >> 5;
-    const int tr = blockIdx.x % ntr, tb = blockIdx.x / ntr;
+    const auto [tr, tb] = tile_place((int)blockIdx.x, ntr, ntb);
     const int n0 = (tr * WR + wr) * (32 * RT), m0 = tb * BM;
     // Run q of G chunks (the last one may be shorter) belongs to wavefront group q % WK.  A group stops at its own last chunk: nothing is
     // multiplied that the product does not have (weights of zero against the last activations again would turn an infinity there into a NaN),

@@ -102,6 +102,37 @@ def test_each_tile_by_number(gpu, name):
             assert err <= 6e-4, f"tile {tile}: {rows} x {cols}, {batch} vectors: {err:.2e}"
 
 
+# row tiles x tiles of vectors: fewer than the dies, one more and one less than a multiple of them, one band of vectors, a whole second one and a short one
+PLACES = [(1, 1), (3, 2), (7, 1), (1, 9), (5, 3), (9, 4), (11, 5), (8, 8), (3, 11), (17, 13)]
+
+
+@pytest.mark.parametrize("ntr,ntb", PLACES)
+def test_every_place(gpu, ntr, ntb):
+    """Every tile of the product is some workgroup's, whatever the counts: each output is written, by the smallest tile, with the last row tile and the last vectors ragged.
+    Bound: as above, one fp16 rounding and sums of 64 products."""
+    torch, iflow = gpu
+    fmt = iflow.FORMATS["Q4_B64"]
+    shapes = tile_shapes(iflow, fmt)
+    tile = min(range(len(shapes)), key=lambda i: shapes[i][0] * shapes[i][1])
+    rows, batch, cols = (ntr - 1) * shapes[tile][0] + 5, (ntb - 1) * shapes[tile][1] + 3, 64
+    say(f"[case] places {ntr} x {ntb}: rows={rows} batch={batch}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(synth.BASE_SEED + 4900 + 16 * ntr + ntb)
+    w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+    x = torch.empty((batch, cols), device="cuda").normal_(generator=g).half()
+    n = iflow.packed_bytes(fmt, rows, cols)
+    packed = torch.empty((n,), dtype=torch.uint8, device="cuda")
+    iflow.quantize(fmt, w, rows, cols, packed, n)
+    w16 = torch.empty((rows, cols), dtype=torch.float16, device="cuda")
+    iflow.dequant(fmt, packed, rows, cols, w16)
+    y = torch.full((batch, rows), float("nan"), dtype=torch.float16, device="cuda")
+    with_tile(torch, iflow, fmt, tile, packed, rows, cols, x, batch, y)
+    torch.cuda.synchronize()
+    ref = x.double() @ w16.double().T.contiguous()
+    err = ((y.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean().sqrt())).max().item()
+    assert err <= 6e-4, f"{rows} x {cols}, {batch} vectors: {err:.2e}"
+
+
 @pytest.mark.parametrize("name", NAMES)
 def test_infinity_in_the_last_columns(gpu, name):
     """An infinite activation in the last 64 columns makes its vector's outputs infinite (NaN only against a weight of zero), whatever kernel

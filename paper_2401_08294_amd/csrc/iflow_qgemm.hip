@@ -515,6 +515,10 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 // A workgroup too many for the last round costs up to half of a
 // launch, so sizes in between are worth having (with nine tiles 6.5 % slower than the best of 33 in the mean); eight wavefronts of 32 rows beat four of 64 where LDS holds
 // their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 259 -> 244, in addition to the longer requests; 4096 x 4096 x 512 32 -> 25).
+// 192 x 128 and 128 x 64 were four wavefronts of 96 and 64 rows: twelve and eight of 32, three and two per SIMD instead of one, read the activations from LDS three times and twice
+// as often and are faster all the same (300 random products of all formats, tile against tile: 192 x 128 15 % in the mean, never slower, 128 x 64 10 %; 11008 x 4096, 512 vectors 52.1 -> 50.0 us in
+// 3.5-bit, 55.3 -> 49.2 in 2-bit, 58.1 -> 54.7 in 8-bit, 20112 x 5184 4-bit, 237 vectors 68.2 -> 60.9).  Not so where a wavefront has its vectors to itself (64 x 64 as eight
+// wavefronts of 32 rows 2 to 8 % slower than four of 64).
 // The choice depends on sizes, format and the number of compute units only, so a call always takes the same path on the same device.
 #define IFLOW_TILES(V) /* RT MB WR WK STAGES  round  step */ \
     V(1, 8, 8, 1, 2, 5.12, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \
@@ -523,11 +527,11 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     V(1, 5, 8, 1, 2, 3.71, 1.12)    /* 256 x 160 */ \
     V(1, 4, 8, 1, 3, 3.59, 0.93)    /* 256 x 128 */ \
     V(1, 4, 4, 2, 2, 3.39, 1.11)    /* 128 x 128 */ \
-    V(3, 4, 2, 2, 2, 6.05, 1.65)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
+    V(1, 4, 6, 2, 2, 4.50, 1.55)    /* 192 x 128 (11008 rows x 512 vectors: 232 workgroups) */ \
     V(1, 4, 3, 2, 2, 3.61, 1.00)    /* 96 x 128 */ \
     V(1, 3, 4, 2, 3, 3.54, 0.91)    /* 128 x 96 */ \
     V(1, 4, 2, 2, 3, 3.83, 0.71)    /* 64 x 128 */ \
-    V(2, 2, 2, 2, 3, 3.66, 0.80)    /* 128 x 64 */ \
+    V(1, 2, 4, 2, 2, 3.30, 0.71)    /* 128 x 64 */ \
     V(3, 2, 1, 4, 2, 5.47, 1.10)    /* 96 x 64 */ \
     V(2, 3, 1, 4, 2, 5.31, 0.93)    /* 64 x 96 */ \
     V(2, 2, 1, 4, 2, 4.03, 0.79)    /* 64 x 64 */ \

@@ -7,13 +7,13 @@
 // contiguous 16-byte-per-lane reads, everything else in registers.
 //   - The cache is [kv head][position][128] fp16, so the positions of a head are one contiguous stream.  A workgroup
 //     (four wavefronts) takes one kv head and one contiguous range of positions (a "split"); the grid is
-//     kv heads x splits, a few workgroups per compute unit.
+//     kv heads x splits, about one workgroup per compute unit.
 //   - A wavefront walks its range in blocks of sixteen positions.  Sixteen lanes share a position (8 of the 128
 //     components each), so one load instruction covers four consecutive positions = 1 KB; the four lane groups of a
 //     wavefront keep separate running softmax states (maximum, sum, 128-component weighted value sum) for their
 //     positions.  The block after the current one is already requested while a block is processed.
 //   - All query heads of a group are served from the same loaded keys and values: one or two heads by the kernel
-//     described here, on the vector units; four or eight by attn_decode_mfma_kernel further down, on the matrix cores.
+//     described here, on the vector units; more by attn_decode_mfma_kernel further down, on the matrix cores.
 //   - Softmax is computed the streaming way: per block one rescale of the running sums to the new maximum, then
 //     exp2 of the (pre-scaled) score differences.  fp32 throughout; the output is rounded to fp16 once.
 //   - A workgroup merges its sixteen states through LDS and writes one state per (head, split) to the caller's
@@ -35,6 +35,21 @@ constexpr int ATT_MAX_SPLITS = 64;
 
 typedef uint32_t att_u32x4 __attribute__((ext_vector_type(4)));
 
+// One head's keys or values of a workgroup's positions, as a buffer that ends with them: blocks are requested ahead without a branch (behind one the compiler waits
+// for everything), and what lies past the end arrives as zeros without a request to memory.  (With the last position requested again in
+// their place, 32/32 heads, 64 positions took 2.78 us and 32/8 heads 3.77.)
+struct AttRange {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ AttRange(const uint16_t *first, int positions, int d)
+    {
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(first), 0, (int)((uint32_t)positions * (2u * (uint32_t)d)), 0x00027000);
+    }
+    __device__ __forceinline__ att_u32x4 load(uint32_t byte) const       // (2: nontemporal)
+    {
+        return __builtin_bit_cast(att_u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte, 0, 2));
+    }
+};
+
 template <int R>
 __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ kc,
                                                                      const uint16_t *__restrict__ vc, uint16_t *__restrict__ out,
@@ -48,8 +63,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
     const int gq = lane >> 4, dseg = lane & 15;               // position inside a tile; which 8 of the 128 components
     const int j = blockIdx.x / nsplit, sp = blockIdx.x - j * nsplit;
     const int t_begin = sp * chunk, t_end = min(seq_len, t_begin + chunk);      // t_begin < seq_len by construction
-    const uint16_t *kh = kc + (int64_t)j * head_stride + dseg * 8;
-    const uint16_t *vh = vc + (int64_t)j * head_stride + dseg * 8;
+    const AttRange keys(kc + (int64_t)j * head_stride + (int64_t)t_begin * ATT_D, t_end - t_begin, ATT_D);
+    const AttRange values(vc + (int64_t)j * head_stride + (int64_t)t_begin * ATT_D, t_end - t_begin, ATT_D);
 
     // the group's queries: lane holds components 8 dseg .. 8 dseg + 7 of each
     half2_t qr[R][4];
@@ -66,13 +81,13 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
         for (int e = 0; e < 8; ++e) acc[r][e] = 0.f;
     }
 
-    // positions past the range are loaded from the range's last position (in bounds) and their scores set to -inf
+    // positions past the range are zeros and their scores set to -inf
     auto load_block = [&](att_u32x4 (&kt)[ATT_TILES], att_u32x4 (&vt)[ATT_TILES], int p0) {
 #pragma unroll
         for (int t = 0; t < ATT_TILES; ++t) {
-            const int64_t pos = min(p0 + t * 4 + gq, t_end - 1);
-            kt[t] = __builtin_nontemporal_load(reinterpret_cast<const att_u32x4 *>(kh + pos * ATT_D));
-            vt[t] = __builtin_nontemporal_load(reinterpret_cast<const att_u32x4 *>(vh + pos * ATT_D));
+            const uint32_t byte = (uint32_t)(p0 - t_begin) * (2 * ATT_D) + lane * 16 + t * 1024;
+            kt[t] = keys.load(byte);
+            vt[t] = values.load(byte);
         }
     };
     auto process_block = [&](const att_u32x4 (&kt)[ATT_TILES], const att_u32x4 (&vt)[ATT_TILES], int p0) {
@@ -168,28 +183,54 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
     }
 }
 
-// ---- groups of four or eight query heads per kv head: scores and weighted sums on the matrix cores --------------------
+// ---- three or more query heads per kv head, or 64 components: scores and weighted sums on the matrix cores -------------
 // With eight heads per loaded key the vector units bind (about 46 instructions per position in the kernel above).  But a
-// block of sixteen positions against a group of heads is two small dense contractions:
-//   S[position][head]  = sum_k K[position][k] Q[head][k]            16 x 128 x (16 heads, 4 or 8 of them real)
+// block of 32 positions against a group of heads is two small dense contractions:
+//   S[position][head]  = sum_k K[position][k] Q[head][k]            2 x 16 x 128 x (16 heads, up to RMAX of them real)
 //   O[head][component] = sum_position P[position][head] V[position][component]
-// and v_mfma_f32_16x16x16_f16 does each in eight instructions per block.  Operand layouts of that instruction, lane =
-// i + 16 g: A: lane holds A[i][4g..4g+3]; B: lane holds B[4g..4g+3][i]; C/D: lane holds D[4g..4g+3][i].
-//   - Scores: A = keys (row = position), B = queries (column = head).  A lane loads its position's keys in four 16-byte
-//     pieces K[position][32u + 8g .. +8]; each piece feeds two instructions, so instruction (u, h) sums over the
-//     components 32u + 8g + 4h + e - any order of k will do as long as the queries are loaded the same way.
-//   - The result D[position 4g+e][head i] is, read the other way round, P^T[head i][positions 4g..4g+3]: exactly an A
-//     operand of the second contraction (row = head, k = position).  So the probabilities never move between lanes.
-//   - The second contraction wants B = values with k = position, i.e. four values of ONE component from four
-//     consecutive positions per lane, while the cache holds a position's 128 components together.  The wavefront's
-//     16 x 128 value tile therefore crosses LDS: written as loaded (16-byte pieces), read back by columns (rows 272 bytes
-//     apart, which puts the four lane groups on different banks).
-//   - Streaming softmax per head in the lanes that hold that head's column of S; the rescale factors of heads 4g..4g+3
-//     are fetched across lanes for the accumulators, which are laid out by (head, component).
+// and v_mfma_f32_16x16x32_f16 does the first in eight instructions per block and the second in sixteen, with the probabilities as two fp16 numbers each (as one,
+// their rounding adds half as much again to the error of the output's own).  Operand layouts of that instruction, lane =
+// i + 16 g: A: lane holds A[i][8g..8g+7]; B: lane holds B[8g..8g+7][i]; C/D: lane holds D[4g..4g+3][i].
+//   - A load instruction takes 1 KB of consecutive positions (a lane has 16 bytes of one), as in the kernel above; the tile of 32 keys crosses
+//     LDS, then the tile of values in the same place.  (Loaded straight into operand layout, an instruction takes 64 bytes of each of
+//     sixteen positions.)
+//   - Scores: A = keys (row = position), B = queries (column = head).  A lane reads its position's pieces K[position][32u + 8g .. +8]: one
+//     operand each.
+//   - The results D[position 4g+e][head i] of the block's two halves are, read the other way round, P^T[head i][positions
+//     4g..4g+3 of each half]: exactly an A operand of the second contraction (row = head, k = position, in that order).  So the
+//     probabilities never move between lanes.
+//   - The second contraction wants B = values with k = position, i.e. values of ONE component from 2 x 4 consecutive positions
+//     per lane, while the cache holds a position's components together: the tile is read by columns with the transposing read (ds_read_b64_tr_b16: of the 16
+//     lanes of a group, lane s asks for four components of row s / 4 and lane l gets component l of all four rows; rows 2 D + 16
+//     bytes apart, which spreads a read's sixteen rows evenly over the banks).
+//   - Streaming softmax per head in the lanes that hold that head's column of S.  The sums are kept relative to a reference that only
+//     follows, to 2^-ATT_BELOW of a block's maximum, when a block exceeds it by more than 2^ATT_LAG: a probability is then at most that
+//     large, which fp16 holds as well as one below 1, and the accumulators, which are laid out by (head, component) and need the
+//     factors from other lanes, are left alone in nearly every block.
+// What bounds it: memory at long contexts (64/8 heads, 16001 positions: 65 MB in 13.0 us with the merge's launch, 2.5 of it), and before that the loads of a compute unit.
+// Us (64/8 heads, graph replay) of blocks of sixteen positions, 64-byte pieces and two-byte column reads / 32 positions and the transposing read / and loads of
+// 1 KB / and nothing requested past a range's end: 16001 positions 16.9 / 16.9 / 13.9 / 13.0, 8000 11.2 / 11.6 / 10.3 / 9.5, 128 in one range 5.1 / 5.9 / 5.2 / 4.5.
 // RMAX (4, 8 or 16) is the number of query heads a workgroup serves from one pass over its keys and values: a group of up
 // to RMAX heads takes one pass, a larger group (the paper's multi-query models: every head shares one key/value head) is
 // cut into pieces of RMAX heads along the grid's second dimension.  D (64 or 128) is the head dimension: D / 32 pieces of
 // 16 bytes per lane and position, D / 16 column groups of the weighted sum.
+constexpr int ATT_BLOCK = 32;                                 // positions per wavefront and block
+constexpr float ATT_BELOW = 7.f, ATT_LAG = 15.f;              // in units of log2
+
+typedef _Float16 att_half4 __attribute__((ext_vector_type(4)));
+typedef _Float16 att_half8 __attribute__((ext_vector_type(8)));
+typedef float att_float4 __attribute__((ext_vector_type(4)));
+typedef short att_short4 __attribute__((ext_vector_type(4)));
+
+// the maximum over the four lanes i, i + 16, i + 32, i + 48
+__device__ __forceinline__ float max_of_rows(float x)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    x = fmaxf(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+}
+
 template <int RMAX, int D>
 __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ kc,
                                                                           const uint16_t *__restrict__ vc, uint16_t *__restrict__ out,
@@ -198,12 +239,12 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
                                                                           float scale_log2e)
 {
     static_assert((RMAX == 4 || RMAX == 8 || RMAX == 16) && (D == 64 || D == 128), "group piece and head dimension");
-    typedef _Float16 half4v __attribute__((ext_vector_type(4)));
-    typedef float float4v __attribute__((ext_vector_type(4)));
     constexpr int NU = D / 32, NC = D / 16;
-    constexpr int VROW = 2 * D + 16;                          // bytes between rows of the staged value tile (a multiple of 16)
-    __shared__ __align__(16) uint8_t s_v[ATT_WAVES][16 * VROW];
-    __shared__ float s_o[ATT_WAVES][RMAX][D];
+    constexpr int LANES = D / 8, LOADS = ATT_BLOCK * LANES / 64;      // lanes per position in a load; loads per block
+    constexpr int VROW = 2 * D + 16;                          // bytes between rows of the staged tile: an odd number of 16-byte slots
+    // a wavefront's tile of keys, then values, and, once its last block is done, its weighted sums [RMAX][D] for the merge
+    constexpr int WAVE_BYTES = ATT_BLOCK * VROW > RMAX * D * 4 ? ATT_BLOCK * VROW : RMAX * D * 4;
+    __shared__ __align__(16) uint8_t s_wave[ATT_WAVES][WAVE_BYTES];
     __shared__ float s_m[ATT_WAVES][16], s_l[ATT_WAVES][16];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -211,91 +252,102 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
     const int j = blockIdx.x / nsplit, sp = blockIdx.x - j * nsplit;
     const int r0 = blockIdx.y * RMAX, rr = min(RMAX, group - r0);     // this workgroup's heads of the group: r0 .. r0 + rr - 1
     const int t_begin = sp * chunk, t_end = min(seq_len, t_begin + chunk);
-    const uint16_t *kh = kc + (int64_t)j * head_stride + g * 8;
-    const uint16_t *vh = vc + (int64_t)j * head_stride + g * 8;
+    const AttRange keys(kc + (int64_t)j * head_stride + (int64_t)t_begin * D, t_end - t_begin, D);
+    const AttRange values(vc + (int64_t)j * head_stride + (int64_t)t_begin * D, t_end - t_begin, D);
 
-    // queries as B operands: lane (head li, g) holds Q[head][32u + 8g + 4h + e]; heads past the piece are zero
-    half4v qb[2 * NU];
+    // queries as B operands: lane (head li, g) holds Q[head][32u + 8g .. +8]; heads past the piece are zero
+    att_half8 qb[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-        att_u32x4 v = {0u, 0u, 0u, 0u};
-        if (li < rr) v = *reinterpret_cast<const att_u32x4 *>(q + (int64_t)(j * group + r0 + li) * D + 32 * u + 8 * g);
-        qb[2 * u] = __builtin_bit_cast(half4v, make_uint2(v.x, v.y));
-        qb[2 * u + 1] = __builtin_bit_cast(half4v, make_uint2(v.z, v.w));
+        const att_u32x4 v = *reinterpret_cast<const att_u32x4 *>(q + (int64_t)(j * group + r0 + min(li, rr - 1)) * D + 32 * u + 8 * g);
+        qb[u] = __builtin_bit_cast(att_half8, li < rr ? v : (att_u32x4){0u, 0u, 0u, 0u});
     }
-    float m = -INFINITY, l = 0.f;                             // of head li (the maximum is the same in the four lanes of a head)
-    float4v oacc[NC];                                         // oacc[c][e] = O[head 4g+e][16c + li]
+    float m = -INFINITY, l = 0.f;                             // of head li (the reference is the same in the four lanes of a head)
+    att_float4 oacc[NC];                                      // oacc[c][e] = O[head 4g+e][16c + li]
 #pragma unroll
-    for (int c = 0; c < NC; ++c) oacc[c] = (float4v){0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < NC; ++c) oacc[c] = (att_float4){0.f, 0.f, 0.f, 0.f};
 
-    auto load_block = [&](att_u32x4 (&kt)[NU], att_u32x4 (&vt)[NU], int p0) {
-        const int64_t pos = min(p0 + li, t_end - 1);          // past the range: its last position, masked below
+    auto load_block = [&](att_u32x4 (&kt)[LOADS], att_u32x4 (&vt)[LOADS], int p0) {      // (past the range: zeros, scores masked below)
+        const uint32_t byte = (uint32_t)(p0 - t_begin) * (2 * D) + lane * 16;
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            kt[u] = __builtin_nontemporal_load(reinterpret_cast<const att_u32x4 *>(kh + pos * D + 32 * u));
-            vt[u] = __builtin_nontemporal_load(reinterpret_cast<const att_u32x4 *>(vh + pos * D + 32 * u));
-        }
+        for (int t = 0; t < LOADS; ++t) kt[t] = keys.load(byte + t * 1024);
+#pragma unroll
+        for (int t = 0; t < LOADS; ++t) vt[t] = values.load(byte + t * 1024);
     };
-    uint8_t *myv = s_v[wave];
-    auto process_block = [&](const att_u32x4 (&kt)[NU], const att_u32x4 (&vt)[NU], int p0) {
-        // values -> LDS as loaded: row = position li, bytes 64u + 16g
-#pragma unroll
-        for (int u = 0; u < NU; ++u) *reinterpret_cast<att_u32x4 *>(myv + li * VROW + 64 * u + 16 * g) = vt[u];
-        // scores
-        float4v sacc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const half4v a0 = __builtin_bit_cast(half4v, make_uint2(kt[u].x, kt[u].y));
-            const half4v a1 = __builtin_bit_cast(half4v, make_uint2(kt[u].z, kt[u].w));
-            sacc = __builtin_amdgcn_mfma_f32_16x16x16f16(a0, qb[2 * u], sacc, 0, 0, 0);
-            sacc = __builtin_amdgcn_mfma_f32_16x16x16f16(a1, qb[2 * u + 1], sacc, 0, 0, 0);
-        }
-        float sc[4], bm = -INFINITY;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {                         // position p0 + 4g + e, head li
-            sc[e] = (p0 + 4 * g + e < t_end) ? sacc[e] * scale_log2e : -INFINITY;
-            bm = fmaxf(bm, sc[e]);
-        }
-        bm = fmaxf(bm, __shfl_xor(bm, 16));                   // the head's maximum over the block's sixteen positions
-        bm = fmaxf(bm, __shfl_xor(bm, 32));
-        const float m_new = fmaxf(m, bm);
-        const float alpha = (m_new == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);
-        const float base = (m_new == -INFINITY) ? 0.f : m_new;
-        float p[4];
-        l *= alpha;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { p[e] = __builtin_amdgcn_exp2f(sc[e] - base); l += p[e]; }
-        m = m_new;
-        const half4v pa = {(_Float16)p[0], (_Float16)p[1], (_Float16)p[2], (_Float16)p[3]};
-        // The accumulators hold heads 4g .. 4g+3: their rescale factors live in lanes 4g .. 4g+3.  Only when some head's
-        // maximum has moved (after the first blocks of a range it rarely does): the accumulators sit in the matrix
-        // cores' own registers, and rescaling them means moving all 32 out and back.
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-            float al[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * g + e);
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) oacc[c][e] *= al[e];
-        }
-        // weighted sums: B = values by columns from LDS (the wavefront's own tile: LDS operations of a wavefront are served in order)
+    uint8_t *myv = s_wave[wave];
+    const uint8_t *column = myv + (4 * g + (li >> 2)) * VROW + 8 * (li & 3);  // what this lane asks for in a transposing read
+    uint8_t *placed = myv + lane / LANES * VROW + 16 * (lane % LANES);        // where its part of a load goes
+    auto turn = [] {                                          // (the wavefront's own tile: its LDS operations are served in order)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto process_block = [&](const att_u32x4 (&kt)[LOADS], const att_u32x4 (&vt)[LOADS], int p0) {
+        // keys through the tile into operands: lane (position li of a half, g) takes the pieces 32u + 8g
+#pragma unroll
+        for (int t = 0; t < LOADS; ++t) *reinterpret_cast<att_u32x4 *>(placed + t * (64 / LANES) * VROW) = kt[t];
+        turn();
+        att_float4 sacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const att_half8 a = *reinterpret_cast<const att_half8 *>(myv + (16 * h + li) * VROW + 64 * u + 16 * g);
+                sacc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qb[u], sacc[h], 0, 0, 0);
+            }
+        turn();
+        // values into the same tile
+#pragma unroll
+        for (int t = 0; t < LOADS; ++t) *reinterpret_cast<att_u32x4 *>(placed + t * (64 / LANES) * VROW) = vt[t];
+        float sc[8], bm = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {                         // position p0 + 16 (e / 4) + 4g + e % 4, head li
+            sc[e] = (p0 + 16 * (e >> 2) + 4 * g + (e & 3) < t_end) ? sacc[e >> 2][e & 3] * scale_log2e : -INFINITY;
+            bm = fmaxf(bm, sc[e]);
+        }
+        bm = max_of_rows(bm);                                 // the head's maximum over the block
+        const bool follow = bm > m + ATT_LAG;                 // (the first block with a score above -inf: always)
+        if (__builtin_amdgcn_ballot_w64(follow) != 0) {
+            const float alpha = follow ? __builtin_amdgcn_exp2f(m - (bm - ATT_BELOW)) : 1.0f;         // exp2(-inf) = 0: nothing summed yet
+            const bool first = __builtin_amdgcn_ballot_w64(m != -INFINITY) == 0;
+            l *= alpha;
+            m = follow ? bm - ATT_BELOW : m;
+            if (!first) {                                     // the accumulators hold heads 4g .. 4g+3: their factors live in lanes 4g .. 4g+3
+                float al[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) al[e] = __shfl(alpha, 4 * g + e);
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) oacc[c][e] *= al[e];
+            }
+        }
+        const float base = (m == -INFINITY) ? 0.f : m;        // (a head that has seen nothing above -inf: no -inf - -inf)
+        att_half8 pa, pr;                                     // the probabilities as fp16, and what that leaves of them
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p = __builtin_amdgcn_exp2f(sc[e] - base);                     // exp2(-inf) = 0 for masked positions
+            l += p;
+            pa[e] = (_Float16)(p * (1.f - 0x1p-10f));         // less than p, so that the rest is positive: against an infinite value both parts are the same infinity
+            pr[e] = (_Float16)(p - (float)pa[e]);
+        }
+        // weighted sums: B = values by columns
+        turn();
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const uint16_t *col = reinterpret_cast<const uint16_t *>(myv + (4 * g) * VROW) + 16 * c + li;
-            const half4v vb = {as_h(col[0]), as_h(col[VROW / 2]), as_h(col[2 * (VROW / 2)]), as_h(col[3 * (VROW / 2)])};
-            oacc[c] = __builtin_amdgcn_mfma_f32_16x16x16f16(pa, vb, oacc[c], 0, 0, 0);
+            typedef __attribute__((address_space(3))) att_short4 lds_short4;
+            const att_short4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(column + 32 * c));
+            const att_short4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(column + 16 * VROW + 32 * c));
+            const att_half8 vb = __builtin_bit_cast(att_half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            oacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pa, vb, oacc[c], 0, 0, 0);
+            oacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pr, vb, oacc[c], 0, 0, 0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();                      // the next block overwrites the tile
+        turn();                                               // the next block overwrites the tile
     };
 
-    att_u32x4 ka[NU], va[NU], kb[NU], vb2[NU];
-    constexpr int STEP = 16 * ATT_WAVES;
-    int p0 = t_begin + wave * 16;
+    att_u32x4 ka[LOADS], va[LOADS], kb[LOADS], vb2[LOADS];
+    constexpr int STEP = ATT_BLOCK * ATT_WAVES;
+    int p0 = t_begin + wave * ATT_BLOCK;
     load_block(ka, va, p0);                                   // (scheduling barriers: see attn_decode_kernel)
     __builtin_amdgcn_sched_barrier(0);
     load_block(kb, vb2, p0 + STEP);
@@ -319,12 +371,13 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s_o[wave][4 * g + e][16 * c + li] = oacc[c][e];
+            for (int e = 0; e < 4; ++e) reinterpret_cast<float *>(myv)[(4 * g + e) * D + 16 * c + li] = oacc[c][e];
     }
     __syncthreads();
     float *ws_o = ws, *ws_m = ws + (int64_t)n_heads * ATT_D * ATT_MAX_SPLITS, *ws_l = ws_m + (int64_t)n_heads * ATT_MAX_SPLITS;
-    for (int idx = tid; idx < rr * D; idx += 64 * ATT_WAVES) {
-        const int r = idx / D, d = idx & (D - 1);
+#pragma unroll
+    for (int i = 0; i < RMAX * D / (64 * ATT_WAVES); ++i) {
+        const int idx = tid + i * 64 * ATT_WAVES, r = idx / D, d = idx & (D - 1);
         float M = s_m[0][r];
 #pragma unroll
         for (int w = 1; w < ATT_WAVES; ++w) M = fmaxf(M, s_m[w][r]);            // finite: the range is not empty
@@ -333,8 +386,9 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
         for (int w = 0; w < ATT_WAVES; ++w) {
             const float f = __builtin_amdgcn_exp2f(s_m[w][r] - M);
             L = __builtin_fmaf(s_l[w][r], f, L);
-            O = __builtin_fmaf(s_o[w][r][d], f, O);
+            O = __builtin_fmaf(reinterpret_cast<const float *>(s_wave[w])[idx], f, O);
         }
+        if (r >= rr) break;                                   // (heads past the piece)
         const int head = j * group + r0 + r;
         if (nsplit == 1) {
             out[(int64_t)head * D + d] = as_u16((half_t)(O / L));
@@ -393,14 +447,19 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
     out[(int64_t)head * head_dim + d] = as_u16((half_t)(O / L));
 }
 
-// positions per split (a multiple of 64, one block per wavefront) and number of splits for a sequence length
-static void attn_geometry(int n_kv_heads, int64_t seq_len, int cus, int *chunk, int *nsplit)
+// Positions per split (a multiple of 64) and number of splits for a sequence length: about one workgroup per compute unit, and one range per key/value head, without
+// the second launch, for short sequences.  Us, ranges and merge / one range, query / key-value heads: on the matrix cores 64/8 at 256 positions 6.4 / 5.0, at 384 6.4 / 6.1, 32/8
+// 5.9 / 4.7 and 5.9 / 6.0, 32/4 of 64 components 5.1 / 3.5 and 5.2 / 4.2; on the vector units 32/32 at 256 positions 4.9 / 4.4, at 384 5.2 / 5.4, 16/16 4.7 / 3.3 and 4.9 / 3.8.
+// (A matrix-core workgroup has a block of 32 positions for two of its wavefronts in a range of 64; ranges of 128 instead: 64/8 at 1001 positions 6.6 -> 7.1.)
+static void attn_geometry(int n_kv_heads, int head_dim, bool vector, int64_t seq_len, int cus, int *chunk, int *nsplit)
 {
-    int64_t want = (1 * (int64_t)cus + n_kv_heads - 1) / n_kv_heads;          // about one workgroup per compute unit
-    if (want < 1) want = 1;
+    int64_t want = ((int64_t)cus + n_kv_heads - 1) / n_kv_heads;
+    if (seq_len <= (vector && n_kv_heads > 16 ? 256 : 384)) want = 1;
     if (want > ATT_MAX_SPLITS) want = ATT_MAX_SPLITS;
     int64_t c = (seq_len + want - 1) / want;
     c = (c + 63) / 64 * 64;
+    const int64_t most = (1LL << 31) / (2 * head_dim);        // a range's bytes are counted in 32 bits
+    if (c > most) c = most;
     *chunk = (int)c;
     *nsplit = (int)((seq_len + c - 1) / c);
 }
@@ -421,7 +480,7 @@ hipError_t launch_attn_decode(const uint16_t *q, const uint16_t *k_cache, const 
     if (head_dim != 64 && head_dim != 128) return hipErrorInvalidValue;
     const int R = n_heads / n_kv_heads;
     int chunk = 0, nsplit = 0;
-    attn_geometry(n_kv_heads, seq_len, cus, &chunk, &nsplit);
+    attn_geometry(n_kv_heads, head_dim, head_dim == 128 && R <= 2, seq_len, cus, &chunk, &nsplit);
     if (nsplit < 1 || nsplit > ATT_MAX_SPLITS) return hipErrorInvalidValue;
     const dim3 block(64 * ATT_WAVES);
     const float scale_log2e = scale * 1.4426950408889634f;

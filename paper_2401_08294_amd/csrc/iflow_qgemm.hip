@@ -241,12 +241,15 @@ template <int F, int G> constexpr int tile_lds_bytes(int rt, int mb, int wr, int
     return stages * wk * mb * 4096 + wr * wk * rt * Parts<F, G>::BUFFERS * Parts<F, G>::BYTES;
 }
 // Chunks fetched at once: 64 bytes of a row, or 128 where the 8-bit formats find room (28672 x 8192, 512 vectors 281 -> 259 us, then 244 with eight
-// wavefronts instead of four: a 64-byte request fetches half a line from memory).
+// wavefronts instead of four: a 64-byte request fetches half a line from memory), and the formats with four bits in their low plane the same in the tiles whose wavefronts do not
+// share K (28672 x 8192, 2000 vectors: 4-bit 806 -> 791 us, 5-bit 864 -> 843, 6-bit 858 -> 844; 4505 x 7104 4-bit, 1706 120.2 -> 116.8; rows of a few hundred columns within
+// 1.5 % either way).  Where they share K, twice as long runs leave some without work: 28672 x 8192 6-bit, 20 vectors 44.0 -> 47.8.  2-bit: 2 % slower.
 template <int F> constexpr int tile_group(int rt, int mb, int wr, int wk, int stages)
 {
     typedef Parts<F> P;
     if (P::WA == 8) return tile_lds_bytes<F, 2>(rt, mb, wr, wk, stages) <= 160 * 1024 && stages <= 3 ? 2 : 1;
-    return P::q3h || P::WA == 2 ? 4 : 2;
+    if (P::q3h || P::WA == 2) return 4;
+    return wk == 1 && tile_lds_bytes<F, 4>(rt, mb, wr, wk, stages) <= 160 * 1024 ? 4 : 2;
 }
 
 // Chunks that wavefront group `group` of WK walks: the runs group, group + WK, ... of G chunks each, and what is left over of the last one.

@@ -61,7 +61,14 @@ struct SmallOps {
 
 // UPPER: more than eight vectors.  A kernel of its own for either case, because on a small matrix the second half's loads under a branch show (us, a
 // branch / a kernel for each: 1024 x 1024 4-bit, blocks of 32, 9 vectors 5.55 / 5.32, 8 vectors 5.15 / 4.80; 4096 x 11008 3.5-bit, 9 vectors 13.4 / 12.7).
-template <int F, int S, int XOP, bool UPPER>
+// LINES (8-bit formats): a load of codes takes the 256 consecutive bytes that the wavefront's columns have in a row, of four rows, and its staging rows turn them.  As the operand
+// layout wants them, one load touches both lines of all sixteen rows for 16 bytes of every 64, four times over; where rows don't begin at multiples of 256
+// bytes this costs most (us, a ring of matrices, 8 vectors and fewer: 9918 x 23680 71.4 -> 60.4, 10826 x 21696 69.2 -> 57.2, 8839 x 7488 25.0 -> 22.1, 512 x 8192 7.5 -> 6.9, 28672 x 8192
+// 50.8 -> 49.9).  Up to SMALL_LINES_COLS columns, half of the sixteen wavefronts or more without any, the turn is what shows (1024 x 1024 4.7 -> 5.0, 16384 x 1088 10.4 -> 11.2,
+// 2048 x 2048 5.4 -> 5.5; 4096 x 2752 6.2 -> 6.1): the loads stay as they were.  So do those of the other formats, which have 128 bytes and less per row (4-bit, 4096 x 4096 4.9 -> 5.2).
+constexpr int64_t SMALL_LINES_COLS = 2048;
+
+template <int F, int S, int XOP, bool UPPER, bool LINES>
 __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                 uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                 int64_t header_offset, int group0, int ngroups, const SmallOps ops)
@@ -92,6 +99,9 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     // 64-byte pieces instead of sixteen); round_body moves every word to the lane the MFMA layout wants it in.
     const int il = lane >> 2, gl = lane & 3;
     const int from = 4 * (4 * i + g);                         // ds_bpermute address of the lane that loaded block (i, g)
+    // (LINES) where row r's 16-byte piece p is while it is turned: permuted by the row, so that the rows' same piece is in different banks
+    auto turned = [&](int r, int p) { return reinterpret_cast<u32x4_t *>(xst + r * 256 + (p ^ r) * 16); };
+    static_assert(8 * SMALL_XROW >= 16 * 256, "a step's codes fit where the activations were turned");
     auto load_step = [&](SmallRaw<KIND> &raw, int t, int r) {
         const bool beyond = t >= nstrips;                     // past the last step: every lane re-reads the matrix's first bytes
         if (beyond) { t = nstrips - 1; r = rounds - 1; }
@@ -130,12 +140,25 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
             for (int h = 0; h < HPL; ++h) raw.hdr[h] = hp[h];
         } else {                                              // code bytes row-major, then the headers
             constexpr int BYTES = KIND == KIND_Q4 ? 32 : 64;
-            const uint8_t *p0 = packed + row * ((int64_t)nbk64 * BYTES) + (int64_t)kbc * BYTES;
-            if (beyond) p0 = packed;
+            if constexpr (LINES) {                            // load q: rows 4q .. 4q + 3
+                int ln = lane;
+                asm volatile("" : "+v"(ln));                  // (addresses worked out per step: the registers are needed in the rounds)
+                const int kb_line = t * 64 + wave * 4 + (ln & 15) / 4;
+                const uint8_t *line = packed + (int64_t)(kb_line < nbk64 ? kb_line : t * 64) * BYTES + (ln & 3) * 16;
 #pragma unroll
-            for (int q = 0; q < BYTES / 16; ++q) {
-                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(p0 + (beyond ? 0 : q * 16));
-                raw.d[4 * q] = v.x; raw.d[4 * q + 1] = v.y; raw.d[4 * q + 2] = v.z; raw.d[4 * q + 3] = v.w;
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t row_q = min(group * 16 + q * 4 + (ln >> 4), rows - 1);
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(beyond ? packed : line + row_q * ((int64_t)nbk64 * BYTES));
+                    raw.d[4 * q] = v.x; raw.d[4 * q + 1] = v.y; raw.d[4 * q + 2] = v.z; raw.d[4 * q + 3] = v.w;
+                }
+            } else {
+                const uint8_t *p0 = packed + row * ((int64_t)nbk64 * BYTES) + (int64_t)kbc * BYTES;
+                if (beyond) p0 = packed;
+#pragma unroll
+                for (int q = 0; q < BYTES / 16; ++q) {
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t *>(p0 + (beyond ? 0 : q * 16));
+                    raw.d[4 * q] = v.x; raw.d[4 * q + 1] = v.y; raw.d[4 * q + 2] = v.z; raw.d[4 * q + 3] = v.w;
+                }
             }
             const uint32_t *hp = reinterpret_cast<const uint32_t *>(packed + header_offset) + (beyond ? 0 : (row * nbk64 + kbc) * HPL);
 #pragma unroll
@@ -157,8 +180,25 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     // one round: dequantize the lane's block, eight MFMA steps (on top of the earlier strips'), the tile to its slot
     auto round_body = [&](const SmallRaw<KIND> &raw, int slot, bool onto) {
         uint32_t d[NWORDS], hdr[2];
+        if constexpr (LINES) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
 #pragma unroll
-        for (int w = 0; w < NWORDS; ++w) d[w] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)raw.d[w]);
+            for (int q = 0; q < 4; ++q) *turned(q * 4 + (ln >> 4), ln & 15) = (u32x4_t){raw.d[4 * q], raw.d[4 * q + 1], raw.d[4 * q + 2], raw.d[4 * q + 3]};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();                  // (the wavefront's own rows: its LDS operations are served in order)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const u32x4_t v = *turned(ln & 15, (ln >> 4) * 4 + q);
+                d[4 * q] = v.x; d[4 * q + 1] = v.y; d[4 * q + 2] = v.z; d[4 * q + 3] = v.w;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();                  // the next round overwrites them
+        } else {
+#pragma unroll
+            for (int w = 0; w < NWORDS; ++w) d[w] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)raw.d[w]);
+        }
         if (KIND != KIND_Q3H) {
 #pragma unroll
             for (int h = 0; h < HPL; ++h) hdr[h] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)raw.hdr[h]);
@@ -426,23 +466,23 @@ __device__ __forceinline__ void gemm_small_body(const uint8_t *__restrict__ pack
     }
 }
 
-template <int F, int S, bool UPPER>
+template <int F, int S, bool UPPER, bool LINES>
 __global__ __launch_bounds__(1024) void gemm_small_kernel(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                           uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                           int64_t header_offset, int group0, int ngroups)
 {
-    gemm_small_body<F, S, -1, UPPER>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, SmallOps{});
+    gemm_small_body<F, S, -1, UPPER, LINES>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, SmallOps{});
 }
 
-template <int F, int S, int XOP, bool UPPER>
+template <int F, int S, int XOP, bool UPPER, bool LINES>
 __global__ __launch_bounds__(1024) void gemm_small_fused_kernel(const uint8_t *__restrict__ packed, const uint16_t *__restrict__ X,
                                                                 uint16_t *__restrict__ Y, int rows, int cols, int batch, int nbk64, int nstrips,
                                                                 int64_t header_offset, int group0, int ngroups, const SmallOps ops)
 {
-    gemm_small_body<F, S, XOP, UPPER>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, ops);
+    gemm_small_body<F, S, XOP, UPPER, LINES>(packed, X, Y, rows, cols, batch, nbk64, nstrips, header_offset, group0, ngroups, ops);
 }
 
-template <int F, int XOP, bool UPPER>
+template <int F, int XOP, bool UPPER, bool LINES>
 static hipError_t small_go(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
                                hipStream_t s)
 {
@@ -453,9 +493,9 @@ static hipError_t small_go(const void *packed, int64_t rows, int64_t cols, const
     int cus = 0;
     hipError_t e0 = once_per_device(pd, &cus, [] {
         if constexpr (XOP < 0)
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_kernel<F, S, UPPER>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_kernel<F, S, UPPER, LINES>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         else
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_fused_kernel<F, S, XOP, UPPER>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_small_fused_kernel<F, S, XOP, UPPER, LINES>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     });
     if (e0 != hipSuccess) return e0;
     const int nbk64 = (int)(cols / 64);
@@ -469,11 +509,11 @@ static hipError_t small_go(const void *packed, int64_t rows, int64_t cols, const
         const int64_t g1 = g0 + per_launch < ngroups ? g0 + per_launch : ngroups;
         const int64_t grid = g1 - g0 < cus ? g1 - g0 : cus;
         if constexpr (XOP < 0)
-            hipLaunchKernelGGL((gemm_small_kernel<F, S, UPPER>), dim3((unsigned)grid), dim3(1024), LDS, s,
+            hipLaunchKernelGGL((gemm_small_kernel<F, S, UPPER, LINES>), dim3((unsigned)grid), dim3(1024), LDS, s,
                                static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk64, nstrips, header_offset,
                                (int)g0, (int)g1);
         else
-            hipLaunchKernelGGL((gemm_small_fused_kernel<F, S, XOP, UPPER>), dim3((unsigned)grid), dim3(1024), LDS, s,
+            hipLaunchKernelGGL((gemm_small_fused_kernel<F, S, XOP, UPPER, LINES>), dim3((unsigned)grid), dim3(1024), LDS, s,
                                static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, nbk64, nstrips, header_offset,
                                (int)g0, (int)g1, ops);
         hipError_t e = hipGetLastError();
@@ -482,12 +522,21 @@ static hipError_t small_go(const void *packed, int64_t rows, int64_t cols, const
     return hipSuccess;
 }
 
+template <int F, int XOP, bool UPPER>
+static hipError_t small_lines(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
+                              hipStream_t s)
+{
+    if constexpr (Fmt<F>::kind == KIND_Q8)
+        if (cols > SMALL_LINES_COLS) return small_go<F, XOP, UPPER, true>(packed, rows, cols, X, batch, Y, ops, s);
+    return small_go<F, XOP, UPPER, false>(packed, rows, cols, X, batch, Y, ops, s);
+}
+
 template <int F, int XOP>
 static hipError_t small_launch(const void *packed, int64_t rows, int64_t cols, const uint16_t *X, int64_t batch, uint16_t *Y, const SmallOps ops,
                                hipStream_t s)
 {
-    if constexpr (XOP == IFLOW_X_SILU_MUL) return small_go<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s);
-    return batch > 8 ? small_go<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s) : small_go<F, XOP, false>(packed, rows, cols, X, batch, Y, ops, s);
+    if constexpr (XOP == IFLOW_X_SILU_MUL) return small_lines<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s);
+    return batch > 8 ? small_lines<F, XOP, true>(packed, rows, cols, X, batch, Y, ops, s) : small_lines<F, XOP, false>(packed, rows, cols, X, batch, Y, ops, s);
 }
 
 hipError_t launch_qgemm_small(int format, const void *packed, int64_t rows, int64_t cols,

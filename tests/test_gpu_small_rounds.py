@@ -51,3 +51,30 @@ def test_rounds(gpu, name):
         ref = v @ w16.double().T.contiguous() + res.double()
         err = ((y.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean(1, keepdim=True).sqrt())).max().item()
         assert err <= TOL, f"{rounds} rounds x {cols}, {batch} vectors, {op}: {err:.2e}"
+
+
+@pytest.mark.parametrize("name", ["Q8_B32", "Q8_B64"])
+def test_long_and_short_rows_of_codes(gpu, name):
+    """8-bit codes on both sides of 2048 columns, where the loads of a step change: a last row group of every remainder that a load of four rows can have, column groups that end inside
+    a wavefront's four and leave whole wavefronts without any, a second strip.  Bound as above."""
+    torch, iflow = gpu
+    fmt = iflow.FORMATS[name]
+    g = torch.Generator(device="cuda")
+    for i, (rows, cols, batch) in enumerate([(16, 2048, 5), (1, 2112, 5), (3, 2176, 8), (17, 2240, 9), (20, 2304, 16), (37, 4032, 6), (46, 4096, 16), (31, 4160, 7), (4099, 6208, 11)]):
+        say(f"[case] small batch codes {name} rows={rows} cols={cols} batch={batch}")
+        g.manual_seed(synth.BASE_SEED + 6100 + i)
+        w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+        x = torch.empty((batch, cols), device="cuda").normal_(generator=g).half()
+        n = iflow.packed_bytes(fmt, rows, cols)
+        packed = torch.empty((n,), dtype=torch.uint8, device="cuda")
+        iflow.quantize(fmt, w, rows, cols, packed, n)
+        w16 = torch.empty((rows, cols), dtype=torch.float16, device="cuda")
+        iflow.dequant(fmt, packed, rows, cols, w16)
+        y = torch.full((batch * rows + 64,), float("nan"), dtype=torch.float16, device="cuda")
+        iflow.qgemm(fmt, packed, rows, cols, x, batch, y)
+        torch.cuda.synchronize()
+        assert torch.isnan(y[batch * rows:]).all(), "wrote past the last output"
+        got = y[:batch * rows].view(batch, rows).double()
+        ref = x.double() @ w16.double().T.contiguous()
+        err = ((got - ref).abs() / torch.maximum(ref.abs(), ref.square().mean(1, keepdim=True).sqrt())).max().item()
+        assert err <= TOL, f"{rows} x {cols}, {batch} vectors: {err:.2e}"

@@ -263,16 +263,20 @@ template <int WK, int G> constexpr __host__ __device__ __forceinline__ int tile_
 // tiles of vectors with those of one row tile next to each other, so that the weights of a row tile are fetched by one die instead of by every die that a tile of vectors
 // puts it on (rows outermost: by one only where the row tiles are a multiple of eight), while a die's 32 workgroups at a time still share their activations.  Bands of 2, 4 and 8 are
 // within 2 % of each other.  Us, rows outermost -> this: 543 x 25856 4-bit, 1254 vectors 86.9 -> 70.4; 2350 x 21632 6-bit, 2035 265 -> 247; 4122 x 24832 5-bit, 78 63.0 -> 60.3; 28672 x 8192
-// 4-bit, 2000 831 -> 821; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; where the row tiles are a multiple of eight (4096 x 11008 8-bit, 33) the same.
+// 4-bit, 2000 831 -> 821; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; where the row tiles are a multiple of eight (4096 x 11008 8-bit, 33) the same.  Over 400 random products, with the tiles of twelve and eight wavefronts below, 3.3 % in
+the mean, 39 % at best and 4 % slower at worst (4221 x 27840 8-bit, 316 vectors 135 -> 140).
 constexpr int TILE_DIES = 8, TILE_BAND = 4;
 struct TilePlace { int tr, tb; };
 __device__ __forceinline__ TilePlace tile_place(int wg, int ntr, int ntb)
 {
     const int total = ntr * ntb, die = wg % TILE_DIES, per = total / TILE_DIES, more = total % TILE_DIES;
     const int tile = die * per + min(die, more) + wg / TILE_DIES;
-    const int band = tile / (ntr * TILE_BAND), wide = min(TILE_BAND, ntb - band * TILE_BAND), in = tile - band * (ntr * TILE_BAND);
-    const int tr = in / wide;
-    return TilePlace{tr, band * TILE_BAND + in - tr * wide};
+    // (divisions by numbers that are not known take 0.1 us off a launch of 5: none where there is one band, and a band is one to four tiles wide)
+    static_assert(TILE_BAND == 4, "the widths below");
+    const int band = ntb <= TILE_BAND ? 0 : tile / (ntr * TILE_BAND), wide = min(TILE_BAND, ntb - band * TILE_BAND);
+    const uint32_t in = (uint32_t)(tile - band * (ntr * TILE_BAND));
+    const int tr = (int)(wide == 4 ? in / 4u : wide == 3 ? in / 3u : wide == 2 ? in / 2u : in);
+    return TilePlace{tr, band * TILE_BAND + (int)in - tr * wide};
 }
 
 // RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
@@ -534,7 +538,7 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     V(1, 4, 3, 2, 2, 3.61, 1.00)    /* 96 x 128 */ \
     V(1, 3, 4, 2, 3, 3.54, 0.91)    /* 128 x 96 */ \
     V(1, 4, 2, 2, 3, 3.83, 0.71)    /* 64 x 128 */ \
-    V(1, 2, 4, 2, 2, 3.30, 0.71)    /* 128 x 64 */ \
+    V(1, 2, 4, 2, 2, 3.50, 0.78)    /* 128 x 64 */ \
     V(3, 2, 1, 4, 2, 5.47, 1.10)    /* 96 x 64 */ \
     V(2, 3, 1, 4, 2, 5.31, 0.93)    /* 64 x 96 */ \
     V(2, 2, 1, 4, 2, 4.03, 0.79)    /* 64 x 64 */ \

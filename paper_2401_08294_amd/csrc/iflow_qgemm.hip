@@ -264,7 +264,7 @@ template <int WK, int G> constexpr __host__ __device__ __forceinline__ int tile_
 // puts it on (rows outermost: by one only where the row tiles are a multiple of eight), while a die's 32 workgroups at a time still share their activations.  Bands of 2, 4 and 8 are
 // within 2 % of each other.  Us, rows outermost -> this: 543 x 25856 4-bit, 1254 vectors 86.9 -> 70.4; 2350 x 21632 6-bit, 2035 265 -> 247; 4122 x 24832 5-bit, 78 63.0 -> 60.3; 28672 x 8192
 // 4-bit, 2000 831 -> 821; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; where the row tiles are a multiple of eight (4096 x 11008 8-bit, 33) the same.  Over 400 random products, with the tiles of twelve and eight wavefronts below, 3.3 % in
-the mean, 39 % at best and 4 % slower at worst (4221 x 27840 8-bit, 316 vectors 135 -> 140).
+// the mean, 39 % at best and 4 % slower at worst (4221 x 27840 8-bit, 316 vectors 135 -> 140).
 constexpr int TILE_DIES = 8, TILE_BAND = 4;
 struct TilePlace { int tr, tb; };
 __device__ __forceinline__ TilePlace tile_place(int wg, int ntr, int ntb)

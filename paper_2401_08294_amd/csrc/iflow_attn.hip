@@ -427,9 +427,10 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
     for (int u = 1; u < ATT_MERGE; ++u) M = fmaxf(M, m[u]);   // finite: no range is empty (a repeated range does not change the maximum)
 #pragma unroll
     for (int u = 0; u < ATT_MERGE; ++u) {
-        const float f = group * ATT_MERGE + u < nsplit ? __builtin_amdgcn_exp2f(m[u] - M) : 0.f;
-        L = __builtin_fmaf(l[u], f, L);
-        O = __builtin_fmaf(o[u], f, O);
+        const bool there = group * ATT_MERGE + u < nsplit;    // (the sums are left out, not multiplied by zero: the last range's may be infinite)
+        const float f = __builtin_amdgcn_exp2f(m[u] - M);
+        L = __builtin_fmaf(there ? l[u] : 0.f, f, L);
+        O = __builtin_fmaf(there ? o[u] : 0.f, f, O);
     }
     if (groups > 1) {                                         // (uniform over the workgroup)
         s_o[group][d] = O;

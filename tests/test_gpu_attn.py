@@ -152,7 +152,7 @@ EDGES = [1, 15, 16, 17, 31, 33, 63, 64, 65, 96, 127, 129, 255, 256, 257, 383, 38
 @pytest.mark.parametrize("n_heads,n_kv,d", [(32, 32, 128), (8, 4, 128), (3, 1, 128), (32, 4, 128), (32, 2, 128), (5, 5, 64), (16, 2, 64), (18, 1, 64)])
 def test_attention_edges(gpu, n_heads, n_kv, d):
     """Lengths at every edge; the cache's rows behind the last position are NaN and reach nothing; an infinite value at the last position makes its component
-    infinite in every head, whatever of a block lies past it (one range of positions).  Tolerance as above (fp32 sums, probabilities and output rounded to fp16 once: 2^-11 each)."""
+    infinite in every head, whatever of a block or of the merge's eight ranges lies past it.  Tolerance as above (fp32 sums, probabilities and output rounded to fp16 once: 2^-11 each)."""
     torch, iflow = gpu
     from oracle import attention as att
     q, k, v = make(n_heads, n_kv, max(EDGES) + 40, synth.BASE_SEED + 1800 + n_heads, d=d)
@@ -164,8 +164,6 @@ def test_attention_edges(gpu, n_heads, n_kv, d):
         got, _ = run(torch, iflow, q, kt, vt, T, scale)
         ref = att.gqa_decode(q.view(np.uint16), k[:, :T + 40].copy().view(np.uint16), v[:, :T + 40].copy().view(np.uint16), T, scale)
         assert np.isfinite(got).all() and rel(got, ref) <= TOL, f"seq_len {T}"
-        if T > 256:
-            continue
         vt[:, T - 1, 3] = np.inf
         got, _ = run(torch, iflow, q, kt, vt, T, scale)
         assert np.isposinf(got[:, 3]).all() and np.isfinite(np.delete(got, 3, 1)).all(), f"seq_len {T}"

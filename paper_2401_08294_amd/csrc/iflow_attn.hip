@@ -30,6 +30,9 @@ constexpr int ATT_D = 128;                                    // head dimension
 constexpr int ATT_WAVES = 4;
 constexpr int ATT_TILES = 4;                                  // tiles of four positions per block: 16 positions per wavefront and block
 constexpr int ATT_MAX_SPLITS = 64;
+// States are merged relative to 2^-16 of the largest reference, so that one whose reference lags its maximum (the matrix-core kernel's, by up to 2^ATT_LAG) is not lost for
+// that: a factor is zero, and an infinite sum times it a NaN, from 2^-142 on.  (Sums are below 2^51 - 2^20 positions, probabilities up to 2^15 - and below 2^99 after three merges.)
+constexpr float ATT_SPARE = 16.f;
 // workspace: value sums O[head][ATT_MAX_SPLITS][component], then maxima M[head][ATT_MAX_SPLITS], then sums L[head][ATT_MAX_SPLITS]
 // (fp32; a state's 128 components are contiguous: written and read by 128 neighbouring threads)
 
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
         bm = max_of_rows(bm);                                 // the head's maximum over the block
         const bool follow = bm > m + ATT_LAG;                 // (the first block with a score above -inf: always)
         if (__builtin_amdgcn_ballot_w64(follow) != 0) {
-            const float alpha = follow ? __builtin_amdgcn_exp2f(m - (bm - ATT_BELOW)) : 1.0f;         // exp2(-inf) = 0: nothing summed yet
+            const float alpha = follow ? __builtin_amdgcn_exp2f(fmaxf(m - (bm - ATT_BELOW), -126.f)) : 1.0f;   // (never zero: an infinite sum stays infinite)
             const bool first = __builtin_amdgcn_ballot_w64(m != -INFINITY) == 0;
             l *= alpha;
             m = follow ? bm - ATT_BELOW : m;
@@ -323,12 +326,15 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
             }
         }
         const float base = (m == -INFINITY) ? 0.f : m;        // (a head that has seen nothing above -inf: no -inf - -inf)
-        att_half8 pa, pr;                                     // the probabilities as fp16, and what that leaves of them
+        // The probabilities as two fp16 numbers, 31/32 and what that leaves: the sum is within 2^-17 of p, and both are positive for every p above 2^-19 (half the smallest
+        // fp16 number and the first one's rounding, 2^-25 each, against p / 32), so that an infinite value stays infinite down to 2^-26 of the maximum.  (One rounded number loses it
+        // at 2^-25; with 1023/1024 the second one is zero for most p below 2^-15, and zero times infinity is a NaN.)
+        att_half8 pa, pr;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float p = __builtin_amdgcn_exp2f(sc[e] - base);                     // exp2(-inf) = 0 for masked positions
             l += p;
-            pa[e] = (_Float16)(p * (1.f - 0x1p-10f));         // less than p, so that the rest is positive: against an infinite value both parts are the same infinity
+            pa[e] = (_Float16)(p * (1.f - 0x1p-5f));
             pr[e] = (_Float16)(p - (float)pa[e]);
         }
         // weighted sums: B = values by columns
@@ -381,6 +387,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_mfma_kernel(const 
         float M = s_m[0][r];
 #pragma unroll
         for (int w = 1; w < ATT_WAVES; ++w) M = fmaxf(M, s_m[w][r]);            // finite: the range is not empty
+        M -= ATT_SPARE;
         float L = 0.f, O = 0.f;
 #pragma unroll
         for (int w = 0; w < ATT_WAVES; ++w) {
@@ -425,6 +432,7 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
     float M = m[0], L = 0.f, O = 0.f;
 #pragma unroll
     for (int u = 1; u < ATT_MERGE; ++u) M = fmaxf(M, m[u]);   // finite: no range is empty (a repeated range does not change the maximum)
+    M -= ATT_SPARE;
 #pragma unroll
     for (int u = 0; u < ATT_MERGE; ++u) {
         const bool there = group * ATT_MERGE + u < nsplit;    // (the sums are left out, not multiplied by zero: the last range's may be infinite)
@@ -438,6 +446,7 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
         __syncthreads();
         if (group > 0) return;
         for (int u = 1; u < groups; ++u) M = fmaxf(M, s_m[u]);
+        M -= ATT_SPARE;
         L = 0.f; O = 0.f;
         for (int u = 0; u < groups; ++u) {
             const float f = __builtin_amdgcn_exp2f(s_m[u] - M);

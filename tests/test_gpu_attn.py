@@ -167,3 +167,27 @@ def test_attention_edges(gpu, n_heads, n_kv, d):
         vt[:, T - 1, 3] = np.inf
         got, _ = run(torch, iflow, q, kt, vt, T, scale)
         assert np.isposinf(got[:, 3]).all() and np.isfinite(np.delete(got, 3, 1)).all(), f"seq_len {T}"
+
+
+@pytest.mark.parametrize("n_heads,n_kv,d", [(8, 8, 128), (6, 2, 128), (16, 2, 128), (16, 1, 128), (4, 2, 64), (16, 2, 64), (18, 1, 64)])
+def test_infinite_value_with_a_small_weight(gpu, n_heads, n_kv, d):
+    """An infinite value makes its component infinite as long as its weight is above 2^-25 of the largest so far, wherever the largest is: in the same block, in another wavefront's or
+    in another range, before it or after; and it stays infinite where scores 2^120 as large come later.  (Scores are whole in units of log2 but for one rounding of the scale.)"""
+    torch, iflow = gpu
+    scale = float(np.log(2.0))
+    for T in (40, 300, 900):
+        rng = np.random.default_rng(synth.BASE_SEED + 1900 + T)
+        q, k = np.zeros((n_heads, d), np.float16), np.zeros((n_kv, T, d), np.float16)
+        q[:, 0] = 1.0
+        v = rng.standard_normal((n_kv, T, d)).astype(np.float16)
+        places = [(down, top, at) for down in (1.0, 7.0, 13.5, 20.0, 21.5, 22.25, 23.0, 24.0, 24.75) for top, at in ((0, 1), (T - 1, 3), (5, T - 1), (T // 2, 0))]
+        places += [(120.0, T - 1, 3)] + ([(120.0, 261, 3)] if T > 261 else [])
+        for down, top, at in places:
+            say(f"[case] attention, infinite value heads={n_heads} kv_heads={n_kv} head_dim={d} seq_len={T} weight 2^-{down} at {at}, largest at {top}")
+            k[:, :, 0] = 60.0 - down - 12.0 if down > 25 else 40.0
+            k[:, top, 0] = 60.0
+            k[:, at, 0] = 60.0 - down
+            vt = v.copy()
+            vt[:, at, 1], vt[:, at, d - 1] = np.inf, -np.inf
+            got, _ = run(torch, iflow, q, k, vt, T, scale)
+            assert np.isposinf(got[:, 1]).all() and np.isneginf(got[:, d - 1]).all() and np.isfinite(np.delete(got, (1, d - 1), 1)).all(), f"seq_len {T}, weight 2^-{down}"

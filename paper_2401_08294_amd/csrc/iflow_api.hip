@@ -171,7 +171,7 @@ iflow_status_t iflow_qgemm(iflow_format_t format, const void *packed, int64_t ro
 }
 
 // For the library's own tests, not part of the ABI: which tile iflow_qgemm takes on a device of `compute_units` (-1: another kernel), what
-// tile number `tile` is (false: no such tile), and the product through that tile.
+// tile number `tile` is (false: no such tile), which row tile and which tile of vectors each workgroup of a launch takes, and the product through that tile.
 int iflow_internal_qgemm_tile(iflow_format_t format, int64_t rows, int64_t cols, int64_t batch, int compute_units)
 {
     iflow::FormatInfo fi;
@@ -186,6 +186,12 @@ int iflow_internal_qgemm_tile_shape(iflow_format_t format, int tile, int64_t sha
     const int64_t v[6] = {t.rows, t.vectors, t.k_groups, t.run, t.buffers, t.max_cols};
     std::copy(v, v + 6, shape);
     return 1;
+}
+
+void iflow_internal_qgemm_tile_places(uint32_t row_tiles, uint32_t vector_tiles, uint32_t (*places)[2])
+{
+    static_assert(sizeof(iflow::TilePlace) == sizeof(*places), "row tile, tile of vectors");
+    iflow::qgemm_tile_places(row_tiles, vector_tiles, reinterpret_cast<iflow::TilePlace *>(places));
 }
 
 iflow_status_t iflow_internal_qgemm_with_tile(iflow_format_t format, int tile, const void *packed, int64_t rows, int64_t cols,

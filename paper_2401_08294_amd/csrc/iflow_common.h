@@ -286,6 +286,10 @@ struct TileShape {
     int k_groups, run, buffers;        // wavefront groups that share K, 64-column chunks they fetch at once, such runs in LDS
     int64_t max_cols;
 };
+// ... and the tiles that the workgroups of a launch of ntr row tiles x ntb tiles of vectors take, in the order of the workgroups
+struct TileOrder { uint32_t per_tile, per_band; };
+struct TilePlace { uint32_t tr, tb; };
+void qgemm_tile_places(uint32_t ntr, uint32_t ntb, TilePlace *places);
 int qgemm_tile_choice(int format, int64_t rows, int64_t cols, int64_t batch, int cus);
 bool qgemm_tile_shape(int format, int tile, TileShape *shape);
 hipError_t launch_qgemm_tile(int format, int tile, const void *packed, int64_t rows, int64_t cols,

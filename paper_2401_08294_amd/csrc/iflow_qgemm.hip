@@ -260,23 +260,49 @@ template <int WK, int G> constexpr __host__ __device__ __forceinline__ int tile_
 }
 
 // Which tile a workgroup takes.  Workgroups go to the eight dies in turn, and each die has an L2 of its own: a die gets a consecutive part of the tiles, in bands of TILE_BAND
-// tiles of vectors with those of one row tile next to each other, so that the weights of a row tile are fetched by one die instead of by every die that a tile of vectors
-// puts it on (rows outermost: by one only where the row tiles are a multiple of eight), while a die's 32 workgroups at a time still share their activations.  Bands of 2, 4 and 8 are
-// within 2 % of each other.  Us, rows outermost -> this: 543 x 25856 4-bit, 1254 vectors 86.9 -> 70.4; 2350 x 21632 6-bit, 2035 265 -> 247; 4122 x 24832 5-bit, 78 63.0 -> 60.3; 28672 x 8192
-// 4-bit, 2000 831 -> 821; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; where the row tiles are a multiple of eight (4096 x 11008 8-bit, 33) the same.  Over 400 random products, with the tiles of twelve and eight wavefronts below, 3.3 % in
-// the mean, 39 % at best and 4 % slower at worst (4221 x 27840 8-bit, 316 vectors 135 -> 140).
-constexpr int TILE_DIES = 8, TILE_BAND = 4;
-struct TilePlace { int tr, tb; };
-__device__ __forceinline__ TilePlace tile_place(int wg, int ntr, int ntb)
+// tiles of vectors (the last one two to TILE_BAND + 1 wide) with those of one row tile next to each other, so that the weights of a row tile are fetched by one die instead of by every
+// die that a tile of vectors puts it on, while a die's 32 workgroups at a time still share their activations.  Us, rows outermost -> this: 543 x 25856 4-bit, 1254 vectors 86.9 -> 70.4; 2350 x 21632
+// 6-bit, 2035 265 -> 247; 11008 x 4096 3.5-bit, 512 55.9 -> 53.2; 3072 x 11840 4-bit, 31 13.5 -> 12.7.
+//   - Rows stay outermost where that puts a row tile on one die by itself (row tiles a multiple of eight) and a die's part would hold the same tiles: two to five tiles of vectors.  With
+//     consecutive row tiles on a die such products took 0.4 to 0.7 % more in the mean (five samples of 38 to 93).
+//   - No band of one: its tiles read every row tile again, all of them on the last dies.  (With it, five tiles of vectors: 2048 x 19264 4-bit, 278 vectors 48.1, 52.7 with it, now 49.3 in the
+//     rows' order; 1280 x 21248 5-bit, 300 43.4, 47.5, 43.4.)
+//   - The kernel divides by numbers that the host has turned into factors: 24 instructions fewer in front of the first copies than with divisions.
+// 750 random products (17 to 2000 vectors) against rows outermost for all: 2.3 % less in the mean, 32 % at best, 4.6 % more at worst (4221 x 27840 8-bit, 316 vectors 123.5 -> 128); what
+// is left of the losses are 36 to 44 row tiles, a multiple of four, with five and seven tiles of vectors.  (Before the three points above: 1.8 % less in the mean, 17 % more at worst.)
+constexpr uint32_t TILE_DIES = 8, TILE_BAND = 4;
+__host__ __device__ __forceinline__ uint32_t tiles_high(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
+static TileOrder tile_order(uint32_t ntr, uint32_t ntb)
 {
-    const int total = ntr * ntb, die = wg % TILE_DIES, per = total / TILE_DIES, more = total % TILE_DIES;
-    const int tile = die * per + min(die, more) + wg / TILE_DIES;
-    // (divisions by numbers that are not known take 0.1 us off a launch of 5: none where there is one band, and a band is one to four tiles wide)
-    static_assert(TILE_BAND == 4, "the widths below");
-    const int band = ntb <= TILE_BAND ? 0 : tile / (ntr * TILE_BAND), wide = min(TILE_BAND, ntb - band * TILE_BAND);
-    const uint32_t in = (uint32_t)(tile - band * (ntr * TILE_BAND));
-    const int tr = (int)(wide == 4 ? in / 4u : wide == 3 ? in / 3u : wide == 2 ? in / 2u : in);
-    return TilePlace{tr, band * TILE_BAND + (int)in - tr * wide};
+    if (ntr % TILE_DIES == 0 && ntb > 1 && ntb <= TILE_BAND + 1) return TileOrder{0, 0};
+    const uint32_t bands = ntb <= TILE_BAND + 1 ? 1 : (ntb + 2) / TILE_BAND, wide = ntb - (bands - 1) * TILE_BAND;
+    return TileOrder{(0x80000000u + wide - 1) / wide, bands == 1 ? 0u : (uint32_t)((1ULL << 32) / (ntr * (uint64_t)TILE_BAND))};
+}
+// (x, y): the workgroup's place in a grid of ntr x ntb where rows are outermost, (its number, 0) otherwise.  A division by a width of one to five is exact below 2^29 tiles; the one by a
+// band's tiles comes out one too small at most.
+__host__ __device__ __forceinline__ TilePlace tile_place(uint32_t x, uint32_t y, uint32_t ntr, uint32_t ntb, const TileOrder order)
+{
+    const uint32_t total = ntr * ntb, die = x % TILE_DIES, more = total % TILE_DIES;
+    uint32_t in = die * (total / TILE_DIES) + (die < more ? die : more) + x / TILE_DIES, first = 0, wide = ntb, per_tile = order.per_tile;
+    if (order.per_band) {
+        const uint32_t last = (ntb + 2) / TILE_BAND - 1, span = ntr * TILE_BAND;
+        uint32_t band = tiles_high(in, order.per_band);
+        if (in - band * span >= span) ++band;
+        if (band > last) band = last;
+        first = band * TILE_BAND;
+        in -= band * span;
+        wide = band == last ? ntb - first : TILE_BAND;
+        per_tile = band == last ? per_tile : 0x80000000u / TILE_BAND;
+    }
+    const uint32_t tr = tiles_high(2 * in, per_tile);
+    return order.per_tile ? TilePlace{tr, first + in - tr * wide} : TilePlace{x, y};
+}
+
+void qgemm_tile_places(uint32_t ntr, uint32_t ntb, TilePlace *places)
+{
+    const TileOrder order = tile_order(ntr, ntb);
+    const uint32_t width = order.per_tile ? ntr * ntb : ntr;
+    for (uint32_t wg = 0; wg < ntr * ntb; ++wg) places[wg] = tile_place(wg % width, wg / width, ntr, ntb, order);
 }
 
 // RT x 32 weight rows and MB x 32 activation vectors per wavefront; WR wavefronts side by side along the rows share a chunk's
@@ -284,7 +310,7 @@ __device__ __forceinline__ TilePlace tile_place(int wg, int ntr, int ntb)
 template <int F, int RT, int MB, int WR, int WK, int STAGES>
 __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile_kernel(const uint8_t *packed, const uint16_t *X, uint16_t *Y,
                                                                                         int rows, int cols, int batch, int64_t header_offset,
-                                                                                        int ntr, int ntb)
+                                                                                        uint32_t per_tile, uint32_t per_band)
 {
     constexpr int G = tile_group<F>(RT, MB, WR, WK, STAGES), BM = 32 * MB;
     typedef Parts<F, G> P;
@@ -307,7 +333,8 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave % WR, wk = wave / WR;
     const int li = lane & 31, h = lane >> 5;
-    const auto [tr, tb] = tile_place((int)blockIdx.x, ntr, ntb);
+    const TilePlace place = tile_place(blockIdx.x, blockIdx.y, ((uint32_t)rows + 32 * RT * WR - 1) / (32 * RT * WR), ((uint32_t)batch + BM - 1) / BM, TileOrder{per_tile, per_band});
+    const int tr = (int)place.tr, tb = (int)place.tb;
     const int n0 = (tr * WR + wr) * (32 * RT), m0 = tb * BM;
     // Run q of G chunks (the last one may be shorter) belongs to wavefront group q % WK.  A group stops at its own last chunk: nothing is
     // multiplied that the product does not have (weights of zero against the last activations again would turn an infinity there into a NaN),
@@ -506,9 +533,10 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
     if (e != hipSuccess) return e;
     const int64_t header_offset = rows * (cols / T::block) * (int64_t)T::code_bytes;
     const int64_t ntr = (rows + 32 * RT * WR - 1) / (32 * RT * WR), ntb = (batch + 32 * MB - 1) / (32 * MB);
-    if (ntr * ntb > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((qgemm_tile_kernel<F, RT, MB, WR, WK, STAGES>), dim3((unsigned)(ntr * ntb)), dim3(64 * WR * WK), lds, s,
-                       static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, header_offset, (int)ntr, (int)ntb);
+    if (ntr * ntb >= 1LL << 29) return hipErrorInvalidValue;   // (Y alone would be a terabyte)
+    const TileOrder order = tile_order((uint32_t)ntr, (uint32_t)ntb);
+    hipLaunchKernelGGL((qgemm_tile_kernel<F, RT, MB, WR, WK, STAGES>), order.per_tile ? dim3((unsigned)(ntr * ntb)) : dim3((unsigned)ntr, (unsigned)ntb), dim3(64 * WR * WK), lds, s,
+                       static_cast<const uint8_t *>(packed), X, Y, (int)rows, (int)cols, (int)batch, header_offset, order.per_tile, order.per_band);
     return hipGetLastError();
 }
 

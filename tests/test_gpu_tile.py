@@ -102,8 +102,9 @@ def test_each_tile_by_number(gpu, name):
             assert err <= 6e-4, f"tile {tile}: {rows} x {cols}, {batch} vectors: {err:.2e}"
 
 
-# row tiles x tiles of vectors: fewer than the dies, one more and one less than a multiple of them, one band of vectors, a whole second one and a short one
-PLACES = [(1, 1), (3, 2), (7, 1), (1, 9), (5, 3), (9, 4), (11, 5), (8, 8), (3, 11), (17, 13)]
+# row tiles x tiles of vectors: fewer than the dies, one more and one less than a multiple of them and a multiple (rows outermost for two to five tiles of vectors), one band of vectors, a
+# whole second one and a short one
+PLACES = [(1, 1), (3, 2), (7, 1), (1, 9), (5, 3), (9, 4), (11, 5), (8, 8), (3, 11), (17, 13), (8, 1), (8, 2), (16, 5), (8, 6)]
 
 
 @pytest.mark.parametrize("ntr,ntb", PLACES)

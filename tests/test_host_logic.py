@@ -667,6 +667,33 @@ def test_tiles_reach_as_far_as_their_offsets(iflow):
         assert tile > 10
 
 
+def tile_places(iflow, ntr, ntb):
+    out = np.full((ntr * ntb, 2), 0xFFFFFFFF, np.uint32)
+    iflow.lib().iflow_internal_qgemm_tile_places(C.c_uint32(ntr), C.c_uint32(ntb), C.c_void_p(out.ctypes.data))
+    return out.astype(np.int64)
+
+
+def test_every_tile_is_some_workgroups(iflow):
+    """Each tile of a product is taken once, whatever the counts; rows are outermost, as the grid counts them, where row tiles come to a multiple of the eight dies and there are two to five
+    tiles of vectors; and elsewhere the tiles of a band (four of vectors, the last two to five) belong to consecutive dies, a row tile's to two at most."""
+    counts = [(ntr, ntb) for ntr in list(range(1, 34)) + [40, 44, 57, 112, 224, 1023] for ntb in list(range(1, 24)) + [33, 63]] + [(3, 4097), (70001, 6), (1, 131071), (262145, 3)]
+    for ntr, ntb in counts:
+        places = tile_places(iflow, ntr, ntb)
+        tr, tb = places[:, 0], places[:, 1]
+        assert tr.max() < ntr and tb.max() < ntb and len(np.unique(tb * ntr + tr)) == ntr * ntb, (ntr, ntb)
+        wg = np.arange(ntr * ntb)
+        if ntr % 8 == 0 and 2 <= ntb <= 5:
+            assert (tr == wg % ntr).all() and (tb == wg // ntr).all(), (ntr, ntb)
+            continue
+        bands = 1 if ntb <= 5 else (ntb + 2) // 4
+        band = np.minimum(tb // 4, bands - 1)
+        widths = np.diff(np.append(np.arange(bands) * 4, ntb))
+        assert (widths[:-1] == 4).all() and (widths[-1] >= 2 or ntb == 1) and widths[-1] <= 5
+        order = np.lexsort((wg // 8, wg % 8))                 # die after die, and each die's workgroups as they start
+        key = (band * ntr + tr) * 8 + tb - 4 * band
+        assert (np.diff(key[order]) > 0).all(), (ntr, ntb)
+
+
 def tile_of(iflow, fmt, rows, cols, batch, cus=256):
     L = iflow.lib()
     shape = (C.c_int64 * 6)()

@@ -458,13 +458,20 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
 }
 
 // Positions per split (a multiple of 64) and number of splits for a sequence length: about one workgroup per compute unit, and one range per key/value head, without
-// the second launch, for short sequences.  Us, ranges and merge / one range, query / key-value heads: on the matrix cores 64/8 at 256 positions 6.4 / 5.0, at 384 6.4 / 6.1, 32/8
-// 5.9 / 4.7 and 5.9 / 6.0, 32/4 of 64 components 5.1 / 3.5 and 5.2 / 4.2; on the vector units 32/32 at 256 positions 4.9 / 4.4, at 384 5.2 / 5.4, 16/16 4.7 / 3.3 and 4.9 / 3.8.
+// the second launch, for short sequences.  Time of one range over that of ranges and merge, in graph replay / as separate calls: mean over head counts and caches of 1024, 4096 and 4160 positions a head [worst]:
+//                                                        256 positions      288               320               352               384               448
+//   matrix cores, 128 components (32/8, 64/8, 128/8, 8/1, 16/4, 64/16, 96/32 heads)
+//                                                        .87 / .84 [.98]    .97 / .95 [1.06]  1.00 / .98 [1.12] 1.01 / .99 [1.08] 1.04 / 1.01 [1.13] 1.13 / 1.10 [1.26]
+//   vector units, up to 16 key/value heads (16/16, 8/8, 4/4, 16/8)
+//                                                        .82 / .70 [.93]    .92 / .78 [1.02]  .97 / .82 [1.05]  1.01 / .86 [1.08] 1.05 / .89 [1.16]  1.17 / 1.01 [1.28]
+//   vector units, more (32/32, 64/64, 64/32)             .80 / .71 [.94]    .90 / .82 [1.04]  .94 / .86 [1.09]  .94 / .85 [1.14]  .95 / .87 [1.18]   1.12 / 1.04 [1.33]
+//   64 components (32/4, 16/16, 32/32, 128/8, 71/1)      .72 / .63 [.73]    .84 / .73 [.92]   .86 / .75 [.92]   .88 / .78 [.95]   .87 / .78 [.94]    .94 / .85 [1.04]
+// The lines lie where graph replay breaks even, and for many heads on the vector units, where it depends on the caches most (32/32: 1.15 and .98 at 384), below.
 // (A matrix-core workgroup has a block of 32 positions for two of its wavefronts in a range of 64; ranges of 128 instead: 64/8 at 1001 positions 6.6 -> 7.1.)
 static void attn_geometry(int n_kv_heads, int head_dim, bool vector, int64_t seq_len, int cus, int *chunk, int *nsplit)
 {
     int64_t want = ((int64_t)cus + n_kv_heads - 1) / n_kv_heads;
-    if (seq_len <= (vector && n_kv_heads > 16 ? 256 : 384)) want = 1;
+    if (seq_len <= (head_dim == 64 ? 384 : !vector ? 320 : n_kv_heads > 16 ? 256 : 352)) want = 1;
     if (want > ATT_MAX_SPLITS) want = ATT_MAX_SPLITS;
     int64_t c = (seq_len + want - 1) / want;
     c = (c + 63) / 64 * 64;

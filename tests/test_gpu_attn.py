@@ -145,8 +145,8 @@ def test_attention_graph_replay(gpu):
         assert rel(out.cpu().numpy().astype(np.float64), ref) <= TOL
 
 
-# around a block (16, 32 positions), a range (64), the lengths from which on a head's positions are shared out (256 and 384), and ranges of more than one block a wavefront
-EDGES = [1, 15, 16, 17, 31, 33, 63, 64, 65, 96, 127, 129, 255, 256, 257, 383, 384, 385, 449, 2047, 2049, 2113]
+# around a block (16, 32 positions), a range (64), the lengths from which on a head's positions are shared out (256, 320, 352 and 384), and ranges of more than one block a wavefront
+EDGES = [1, 15, 16, 17, 31, 33, 63, 64, 65, 96, 127, 129, 255, 256, 257, 319, 320, 321, 351, 352, 353, 383, 384, 385, 449, 2047, 2049, 2113]
 
 
 @pytest.mark.parametrize("n_heads,n_kv,d", [(32, 32, 128), (8, 4, 128), (3, 1, 128), (32, 4, 128), (32, 2, 128), (5, 5, 64), (16, 2, 64), (18, 1, 64)])

@@ -40,7 +40,7 @@ typedef uint32_t att_u32x4 __attribute__((ext_vector_type(4)));
 
 // One head's keys or values of a workgroup's positions, as a buffer that ends with them: blocks are requested ahead without a branch (behind one the compiler waits
 // for everything), and what lies past the end arrives as zeros without a request to memory.  (With the last position requested again in
-// their place, 32/32 heads, 64 positions took 2.78 us and 32/8 heads 3.77.)
+// their place, 32/32 heads, 64 positions took 2.78 us and 32/8 heads 3.77.)  Bytes are counted in 32 bits: a cache has at most 2^20 positions, 2^28 bytes of a head.
 struct AttRange {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ AttRange(const uint16_t *first, int positions, int d)
@@ -220,7 +220,6 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
 constexpr int ATT_BLOCK = 32;                                 // positions per wavefront and block
 constexpr float ATT_BELOW = 7.f, ATT_LAG = 15.f;              // in units of log2
 
-typedef _Float16 att_half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 att_half8 __attribute__((ext_vector_type(8)));
 typedef float att_float4 __attribute__((ext_vector_type(4)));
 typedef short att_short4 __attribute__((ext_vector_type(4)));
@@ -475,8 +474,6 @@ static void attn_geometry(int n_kv_heads, int head_dim, bool vector, int64_t seq
     if (want > ATT_MAX_SPLITS) want = ATT_MAX_SPLITS;
     int64_t c = (seq_len + want - 1) / want;
     c = (c + 63) / 64 * 64;
-    const int64_t most = (1LL << 31) / (2 * head_dim);        // a range's bytes are counted in 32 bits
-    if (c > most) c = most;
     *chunk = (int)c;
     *nsplit = (int)((seq_len + c - 1) / c);
 }

@@ -191,3 +191,32 @@ def test_infinite_value_with_a_small_weight(gpu, n_heads, n_kv, d):
             vt[:, at, 1], vt[:, at, d - 1] = np.inf, -np.inf
             got, _ = run(torch, iflow, q, k, vt, T, scale)
             assert np.isposinf(got[:, 1]).all() and np.isneginf(got[:, d - 1]).all() and np.isfinite(np.delete(got, (1, d - 1), 1)).all(), f"seq_len {T}, weight 2^-{down}"
+
+
+@pytest.mark.parametrize("n_heads,n_kv,d,lengths", [(24, 8, 128, (129, 300, 9000)), (64, 8, 128, (129, 319, 9000)), (64, 4, 128, (300, 16001)), (10, 1, 128, (320, 20000)), (96, 32, 128, (310, 2113)),
+                                                    (32, 8, 64, (129, 384, 9000)), (16, 1, 64, (300, 20000)), (6, 2, 128, (300, 6000)), (32, 32, 128, (200, 2000))])
+def test_attention_scores_that_climb(gpu, n_heads, n_kv, d, lengths):
+    """Scores that climb along the positions, block after block of a wavefront (128 positions apart) and inside a block, by 0 to 40 in units of log2 and by another step for every head, with
+    the largest last, first and in the middle: the reference the sums are kept to follows in some heads of a block and not in others, lags by just less and just more than what it
+    may (8: a block's maximum 15 above a reference that was 7 below the first one), and wavefronts and ranges are merged from references far apart.  Every third head has no noise, so that whole
+    blocks share one score.  Tolerance as above: scores of up to 1500 (n_kv = 1) are rounded at 2^-24 of that, 1e-4 of a probability."""
+    torch, iflow = gpu
+    from oracle import attention as att
+    q, k, v = make(n_heads, n_kv, max(lengths), synth.BASE_SEED + 2100 + n_heads + d, d=d)
+    scale = 1.0 / np.sqrt(float(d))
+    steps = np.array([0.0, 6.0, 7.9, 8.0, 8.1, 10.0, 14.9, 15.1, 20.0, 40.0, -6.0, -20.0, 3.0])
+    q[::3] = 0.0
+    for T in lengths:
+        positions = np.arange(max(lengths))
+        climbs = {"blocks of a wavefront": positions // 128, "blocks": positions // 32, "the middle": -np.abs(positions - T // 2) // 128, "positions": positions / 8.0}
+        for name, climb in climbs.items():
+            most = float(np.abs(climb[:T]).max())
+            # (steps scaled down where the score would leave what 16 bits of key and query hold: 40 per block over 600 blocks)
+            per = np.resize(steps, n_heads) * min(1.0, 1500.0 / (40.0 * max(most, 1.0))) if most * 40.0 > 1500.0 else np.resize(steps, n_heads)
+            q[:, 0] = (per * np.log(2.0) / scale).astype(np.float16)
+            k[:, :, 0] = climb.astype(np.float16)
+            say(f"[case] attention, climbing scores ({name}) heads={n_heads} kv_heads={n_kv} head_dim={d} seq_len={T}")
+            got, _ = run(torch, iflow, q, k[:, :T].copy(), v[:, :T].copy(), T, scale)
+            ref = att.gqa_decode(q.view(np.uint16), k[:, :T].copy().view(np.uint16), v[:, :T].copy().view(np.uint16), T, scale)
+            e = rel(got, ref)
+            assert np.isfinite(got).all() and e <= TOL, f"{name}, seq_len {T}: {e:.2e}"

@@ -137,21 +137,25 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
     att_u32x4 ka[ATT_TILES], va[ATT_TILES], kb[ATT_TILES], vb[ATT_TILES];
     constexpr int STEP = 16 * ATT_WAVES;                      // positions between a wavefront's consecutive blocks
     int p0 = t_begin + wave * 16;
-    // (the scheduling barriers pin the order in which the two sets are requested: the wait in front of a block counts
-    // the requests issued after that block's own, and a reordered prologue would turn it into a wait for everything)
-    load_block(ka, va, p0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_block(kb, vb, p0 + STEP);
-    __builtin_amdgcn_sched_barrier(0);
-    for (; p0 < t_end; p0 += 2 * STEP) {
-        process_block(ka, va, p0);
+    // (The wait in front of a block counts the requests issued after that block's own, so the order in which the two sets are requested has to be the same in front of the loop and in
+    // it, or the wait becomes one for everything.  Scheduling barriers pin it, but not against moving requests behind the loop's own test, one by one: they stand behind it.  Us over a ring
+    // of caches: 32/32 heads, 16001 positions 42.4 with half of the first block's values requested last, now 41.4; 8000 23.9 and 22.8; 3001 11.8 and 11.4; 16/16, 16001 23.7 and 22.6.)
+    if (p0 < t_end) {
+        load_block(ka, va, p0);
         __builtin_amdgcn_sched_barrier(0);
-        load_block(ka, va, p0 + 2 * STEP);
+        load_block(kb, vb, p0 + STEP);
         __builtin_amdgcn_sched_barrier(0);
-        if (p0 + STEP < t_end) process_block(kb, vb, p0 + STEP);              // (uniform over the wavefront)
-        __builtin_amdgcn_sched_barrier(0);
-        load_block(kb, vb, p0 + 3 * STEP);
-        __builtin_amdgcn_sched_barrier(0);
+        do {
+            process_block(ka, va, p0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_block(ka, va, p0 + 2 * STEP);
+            __builtin_amdgcn_sched_barrier(0);
+            if (p0 + STEP < t_end) process_block(kb, vb, p0 + STEP);          // (uniform over the wavefront)
+            __builtin_amdgcn_sched_barrier(0);
+            load_block(kb, vb, p0 + 3 * STEP);
+            __builtin_amdgcn_sched_barrier(0);
+            p0 += 2 * STEP;
+        } while (p0 < t_end);
     }
 
     // ---- merge the sixteen states (4 wavefronts x 4 lane groups) of each head, store or hand over -----------------------
@@ -462,10 +466,10 @@ __global__ __launch_bounds__(ATT_D * (ATT_MAX_SPLITS / ATT_MERGE)) void attn_mer
 //   matrix cores, 128 components (32/8, 64/8, 128/8, 8/1, 16/4, 64/16, 96/32 heads)
 //                                                        .87 / .84 [.98]    .97 / .95 [1.06]  1.00 / .98 [1.12] 1.01 / .99 [1.08] 1.04 / 1.01 [1.13] 1.13 / 1.10 [1.26]
 //   vector units, up to 16 key/value heads (16/16, 8/8, 4/4, 16/8)
-//                                                        .82 / .70 [.93]    .92 / .78 [1.02]  .97 / .82 [1.05]  1.01 / .86 [1.08] 1.05 / .89 [1.16]  1.17 / 1.01 [1.28]
-//   vector units, more (32/32, 64/64, 64/32)             .80 / .71 [.94]    .90 / .82 [1.04]  .94 / .86 [1.09]  .94 / .85 [1.14]  .95 / .87 [1.18]   1.12 / 1.04 [1.33]
+//                                                        .78 / .66 [.89]    .88 / .73 [1.00]  .94 / .78 [1.04]  .98 / .82 [1.05]  1.01 / .84 [1.15]  1.16 / .97 [1.25]
+//   vector units, more (32/32, 64/64, 64/32)             .79 / .71 [.96]    .88 / .80 [1.02]  .93 / .83 [1.08]  .92 / .83 [1.11]  .93 / .83 [1.17]   1.10 / 1.01 [1.33]
 //   64 components (32/4, 16/16, 32/32, 128/8, 71/1)      .72 / .63 [.73]    .84 / .73 [.92]   .86 / .75 [.92]   .88 / .78 [.95]   .87 / .78 [.94]    .94 / .85 [1.04]
-// The lines lie where graph replay breaks even, and for many heads on the vector units, where it depends on the caches most (32/32: 1.15 and .98 at 384), below.
+// The lines lie where graph replay breaks even, and for many heads on the vector units, where it depends on the caches most (32/32: 1.17 and .98 at 384), below.
 // (A matrix-core workgroup has a block of 32 positions for two of its wavefronts in a range of 64; ranges of 128 instead: 64/8 at 1001 positions 6.6 -> 7.1.)
 static void attn_geometry(int n_kv_heads, int head_dim, bool vector, int64_t seq_len, int cus, int *chunk, int *nsplit)
 {

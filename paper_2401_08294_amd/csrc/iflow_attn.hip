@@ -86,12 +86,14 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
 
     // positions past the range are zeros and their scores set to -inf
     auto load_block = [&](att_u32x4 (&kt)[ATT_TILES], att_u32x4 (&vt)[ATT_TILES], int p0) {
+        const uint32_t byte = (uint32_t)(p0 - t_begin) * (2 * ATT_D) + lane * 16;
 #pragma unroll
-        for (int t = 0; t < ATT_TILES; ++t) {
-            const uint32_t byte = (uint32_t)(p0 - t_begin) * (2 * ATT_D) + lane * 16 + t * 1024;
-            kt[t] = keys.load(byte);
-            vt[t] = values.load(byte);
-        }
+        for (int t = 0; t < ATT_TILES; ++t) kt[t] = keys.load(byte + t * 1024);
+        // (all keys first, which are needed first: with both in turn 32/32 heads, 3001 of 4096 positions 9.66 us, now 9.57, over a ring 12.4 and 12.1; 50 lengths and head counts 0.2 to 0.4 % less
+        // in the mean)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < ATT_TILES; ++t) vt[t] = values.load(byte + t * 1024);
     };
     auto process_block = [&](const att_u32x4 (&kt)[ATT_TILES], const att_u32x4 (&vt)[ATT_TILES], int p0) {
         float vf[ATT_TILES][8];

@@ -40,7 +40,7 @@ typedef uint32_t att_u32x4 __attribute__((ext_vector_type(4)));
 
 // One head's keys or values of a workgroup's positions, as a buffer that ends with them: blocks are requested ahead without a branch (behind one the compiler waits
 // for everything), and what lies past the end arrives as zeros without a request to memory.  (With the last position requested again in
-// their place, 32/32 heads, 64 positions took 2.78 us and 32/8 heads 3.77.)  Bytes are counted in 32 bits: a cache has at most 2^20 positions, 2^28 bytes of a head.
+// their place, 32/32 heads, 64 positions took 2.80 us, now 2.67; 64/32 3.74 and 3.49.)  Bytes are counted in 32 bits: a cache has at most 2^20 positions, 2^28 bytes of a head.
 struct AttRange {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ AttRange(const uint16_t *first, int positions, int d)
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
     int p0 = t_begin + wave * 16;
     // (The wait in front of a block counts the requests issued after that block's own, so the order in which the two sets are requested has to be the same in front of the loop and in
     // it, or the wait becomes one for everything.  Scheduling barriers pin it, but not against moving requests behind the loop's own test, one by one: they stand behind it.  Us over a ring
-    // of caches: 32/32 heads, 16001 positions 42.4 with half of the first block's values requested last, now 41.4; 8000 23.9 and 22.8; 3001 11.8 and 11.4; 16/16, 16001 23.7 and 22.6.)
+    // of caches: 32/32 heads, 16001 positions 42.4 with half of the first block's values requested last, now 41.7; 8000 23.9 and 23.2; 3001 11.8 and 11.6; 16/16, 16001 23.7 and 23.1.)
     if (p0 < t_end) {
         load_block(ka, va, p0);
         __builtin_amdgcn_sched_barrier(0);
@@ -216,9 +216,11 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_decode_kernel(const uint1
 //     follows, to 2^-ATT_BELOW of a block's maximum, when a block exceeds it by more than 2^ATT_LAG: a probability is then at most that
 //     large, which fp16 holds as well as one below 1, and the accumulators, which are laid out by (head, component) and need the
 //     factors from other lanes, are left alone in nearly every block.
-// What bounds it: memory at long contexts (64/8 heads, 16001 positions: 65 MB in 13.0 us with the merge's launch, 2.5 of it), and before that the loads of a compute unit.
-// Us (64/8 heads, graph replay) of blocks of sixteen positions, 64-byte pieces and two-byte column reads / 32 positions and the transposing read / and loads of
-// 1 KB / and nothing requested past a range's end: 16001 positions 16.9 / 16.9 / 13.9 / 13.0, 8000 11.2 / 11.6 / 10.3 / 9.5, 128 in one range 5.1 / 5.9 / 5.2 / 4.5.
+// What bounds it: memory at long contexts (64/8 heads, 16001 positions, 65 MB over a ring of caches beyond the last-level cache: 15.8 us with the merge's launch, 17.6 before; one cache
+// again and again stays in that and takes 13.2, before 16.4), and before that the loads of a compute unit.
+// Us (64/8 heads, graph replay on one cache) of blocks of sixteen positions, 64-byte pieces and two-byte column reads / 32 positions and the transposing read / and loads of
+// 1 KB / and nothing requested past a range's end: 16001 positions 16.9 / 16.9 / 13.9 / 13.0, 8000 11.2 / 11.6 / 10.3 / 9.5, 128 in one range 5.1 / 5.9 / 5.2 / 4.5.  Not faster where a
+// wavefront has one block: 4096 positions over a ring 9.2 before, 9.4.
 // RMAX (4, 8 or 16) is the number of query heads a workgroup serves from one pass over its keys and values: a group of up
 // to RMAX heads takes one pass, a larger group (the paper's multi-query models: every head shares one key/value head) is
 // cut into pieces of RMAX heads along the grid's second dimension.  D (64 or 128) is the head dimension: D / 32 pieces of

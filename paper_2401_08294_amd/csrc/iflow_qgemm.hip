@@ -11,13 +11,13 @@
 //   - The operands of a k-step of 16 columns are read and decoded while the matrix instructions of the k-step before run.
 //   - Which lane holds which k of a chunk is free as long as both operands agree: lane half h takes columns 32 h .. 32 h + 31,
 //     so that a lane's weights are 32 consecutive ones of one row.
-// What bounds it, by counters: at 2000 vectors (28672 x 8192, 4-bit) the matrix cores are busy 67 % of the cycles of a launch that runs at 1.4 to 1.55 GHz - the power
-// limit, a loop of nothing but these instructions on random data runs at 1.5 to 1.8 - next to a decode that issues 29 % of them, which is why
-// the largest tile has 256 vectors per decoded weight; at 512 (11008 x 4096, 3.5-bit) both are busy a third of the time, one wavefront per SIMD; at 33
+// What bounds it, by counters: at 2000 vectors (28672 x 8192, 4-bit) the matrix cores are busy 65 % of the cycles of a launch that runs at 1.4 to 1.6 GHz - the power
+// limit, a loop of nothing but these instructions on random data runs at 1.5 to 1.8 - next to a decode that issues 28 % of them, which is why
+// the largest tile has 256 vectors per decoded weight; at 512 (11008 x 4096, 3.5-bit, three wavefronts per SIMD, 1.7 GHz) both are busy 43 to 44 % of the time; at 33
 // (4096 x 11008, 8-bit) wavefronts wait for their copies.
 // Measured, us (before: 128 x 64 tiles with both operands decoded or copied into LDS, passes of sixteen below 32 vectors), one matrix again and again:
-// 11008 x 4096 3.5-bit, 512 vectors 84.4 -> 55.7 (830 TFLOP/s; over a ring of matrices beyond the caches 58 to 61); 28672 x 8192 4-bit, 2000 vectors 1491 -> 831 (1130
-// TFLOP/s; 820 to 864 by machine); 4096 x 11008 8-bit, 33 vectors 49.7 -> 17.4 (ring 23); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.0 (ring 9.6).
+// 11008 x 4096 3.5-bit, 512 vectors 84.4 -> 50 to 51 (910 TFLOP/s; over a ring of matrices beyond the caches more); 28672 x 8192 4-bit, 2000 vectors 1491 -> 817 to 831 by machine (1130 to
+// 1150 TFLOP/s); 4096 x 11008 8-bit, 33 vectors 49.7 -> 17.4 (ring 23); 4096 x 4096 3.5-bit, 64 vectors 23.8 -> 8.0 (ring 9.6).
 #include "iflow_common.h"
 
 namespace iflow {
@@ -242,8 +242,8 @@ template <int F, int G> constexpr int tile_lds_bytes(int rt, int mb, int wr, int
 }
 // Chunks fetched at once: 64 bytes of a row, or 128 where the 8-bit formats find room (28672 x 8192, 512 vectors 281 -> 259 us, then 244 with eight
 // wavefronts instead of four: a 64-byte request fetches half a line from memory), and the formats with four bits in their low plane the same in the tiles whose wavefronts do not
-// share K (28672 x 8192, 2000 vectors: 4-bit 806 -> 791 us, 5-bit 864 -> 843, 6-bit 858 -> 844; 4505 x 7104 4-bit, 1706 120.2 -> 116.8; rows of a few hundred columns within
-// 1.5 % either way).  Where they share K, twice as long runs leave some without work: 28672 x 8192 6-bit, 20 vectors 44.0 -> 47.8.  2-bit: 2 % slower.
+// share K (28672 x 8192, 2000 vectors: 4-bit 848 -> 831 us, 5-bit 904 -> 882, 6-bit 907 -> 888; 4505 x 7104 4-bit, 1706 120.2 -> 117.1; 20000 x 512 4-bit and 30000 x 320 5-bit within
+// half a per cent).  Where they share K, twice as long runs leave some without work: 28672 x 8192 6-bit, 20 vectors 44.0 -> 47.8.  2-bit: 2 % slower.
 template <int F> constexpr int tile_group(int rt, int mb, int wr, int wk, int stages)
 {
     typedef Parts<F> P;
@@ -318,11 +318,10 @@ __global__ __launch_bounds__(64 * WR * WK, RT * MB <= 8 ? 2 : 1) void qgemm_tile
     constexpr int NX = (4 * MB + WR - 1) / WR;                 // 1 KB pieces of its group's chunk a wavefront copies per step
     constexpr int NG = RT * (P::q3h ? 2 * P::NA : P::NA + P::NB + P::NH);      // a wavefront's requests per group of G chunks
     // With two stages a step waits for what was requested one step ago.  Where a group lasts two steps its request goes out behind that step's
-    // activations, so that the wait for them leaves it one step more: these bytes come from memory, the activations from L2.  (us, before -> after, one matrix
-    // again and again: 28672 x 8192 4-bit, 2000 vectors 845 -> 831, 1024 445 -> 436, 8-bit, 1000 479 -> 467; 14336 x 8192 6-bit, 1500 396 -> 386.  A tile by its
-    // number over rings of matrices, 140 random products in these formats, mean: 256 x 160 -10 %, 256 x 256 and 256 x 224 -8 %, 128 x 128 -7 %, 96 x 128 -5 %, 128 x 192
-    // -4 %, 192 x 128 -3.5 %.  Not with groups of four steps - 3.5-bit, 11008 x 4096, 2048 vectors 201 -> 207 - nor without a barrier: 4096 x 11008 8-bit, 33
-    // vectors 17.4 -> 17.7.)
+    // activations, so that the wait for them leaves it one step more: these bytes come from memory, the activations from L2.  It is worth something where a group is whole
+    // lines, in the 8-bit formats (28672 x 8192, 1000 vectors 467 -> 453 us, 2000 886 -> 877; 8192 x 8192, 512 77.5 -> 76.9); to the tiles whose wavefronts share K, in the 4-, 5- and 6-bit formats, nothing
+    // (11008 x 4096, 512, 192 x 128: 57.0 and 57.0).  Groups of four steps keep the other order: 28672 x 8192, 2000 vectors 4-bit 831 -> 833 with this one, 5-bit 882 -> 891, 6-bit 888 -> 884; 3.5-bit,
+    // 11008 x 4096, 2048 201 -> 207.  So do wavefronts without a barrier: 4096 x 11008 8-bit, 33 vectors 17.4 -> 17.7.
     constexpr bool XFIRST = STAGES == 2 && G == 2 && WR > 1;
     // what may still be on its way when a step's activations have to be there: the activations of the STAGES - 2 steps after it and
     // the groups requested among them (XFIRST: behind them)
@@ -541,19 +540,19 @@ static hipError_t tile_go(const void *packed, int64_t rows, int64_t cols, const 
 }
 
 // The tiles in use and what a launch of each costs in microseconds, for every format: rounds * (round + steps * step), rounds = workgroups per compute unit, steps =
-// chunks that one wavefront walks.  `step` is fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000 vectors,
-// `round` (start, first copies, sums and stores) is the median of what rows of 64 to 1024 columns take beyond their steps.  On 200 random products that
-// no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is 0.35 % slower than the best
-// in the mean and 13 % at worst, on 300 of 64 to 1024 columns 1.3 % and 9.5 %.  The steps were fitted before XFIRST made some of these tiles 3.5 to 10 % faster; before it
-// the same 200 products lost 0.30 %, so they were left.  (`round` fitted to the long rows too came out at 0.6 to 4.9 us and took
+// chunks that one wavefront walks.  `step` was fitted to four formats x eleven shapes (1024^2 to 28672 x 8192 and 11885 x 17792) x 17 .. 2000 vectors,
+// `round` (start, first copies, sums and stores) is the median of what rows of 64 to 1024 columns take beyond their steps, both on earlier kernels; the two of 192 x 128 and 128 x 64 are set
+// by hand since.  On 200 random products that no constant was fitted to (all formats, 512 to 28672 rows, 1024 to 28672 columns, 17 to 2000 vectors) the chosen tile is
+// 0.33 % slower than the best in the mean and 11 % at worst; on 300 of 64 to 1024 columns 2.2 % and 18 %: there 128 x 64 is the best for 109, its price takes it for 38 (before it
+// had eight wavefronts 1.3 % and 9.5 %, and the chosen one was slower).  (`round` fitted to the long rows too came out at 0.6 to 4.9 us and took
 // 256 x 160 for nearly everything below 256 columns, 13 % slower than the best: 131072 x 64, 3.5-bit, 33 vectors 9.6 us, now 8.8; 33 x 256, 512 vectors 8.6, now 5.1.)
 // A workgroup too many for the last round costs up to half of a
 // launch, so sizes in between are worth having (with nine tiles 6.5 % slower than the best of 33 in the mean); eight wavefronts of 32 rows beat four of 64 where LDS holds
 // their weights (two per SIMD hide each other's waits: 28672 x 8192, 512 vectors 228 -> 220 us, 8-bit 259 -> 244, in addition to the longer requests; 4096 x 4096 x 512 32 -> 25).
 // 192 x 128 and 128 x 64 were four wavefronts of 96 and 64 rows: twelve and eight of 32, three and two per SIMD instead of one, read the activations from LDS three times and twice
-// as often and are faster all the same (300 random products of all formats, tile against tile: 192 x 128 15 % in the mean, never slower, 128 x 64 10 %; 11008 x 4096, 512 vectors 52.1 -> 50.0 us in
-// 3.5-bit, 55.3 -> 49.2 in 2-bit, 58.1 -> 54.7 in 8-bit, 20112 x 5184 4-bit, 237 vectors 68.2 -> 60.9).  Not so where a wavefront has its vectors to itself (64 x 64 as eight
-// wavefronts of 32 rows 2 to 8 % slower than four of 64).
+// as often and are faster all the same (tile against tile, the places with them, on the 200 and the 300 products above: 192 x 128 14 and 24 % in the mean, at worst the same, 128 x 64 9 and 15 %, at worst
+// 6 % slower where it is not the one to take; 11008 x 4096, 512 vectors 53.9 -> 50.7 us in 4-bit, 62.2 -> 57.2 in 5-bit, 63 -> 56.5 in 8-bit).  Of 1050 products the choice changed for 27, all
+// 6 to 22 % faster.  Not so where a wavefront has its vectors to itself (64 x 64 as eight wavefronts of 32 rows 2 to 8 % slower than four of 64).
 // The choice depends on sizes, format and the number of compute units only, so a call always takes the same path on the same device.
 #define IFLOW_TILES(V) /* RT MB WR WK STAGES  round  step */ \
     V(1, 8, 8, 1, 2, 5.12, 1.47)    /* 256 rows x 256 vectors: the fewest decodes and reads per product */ \

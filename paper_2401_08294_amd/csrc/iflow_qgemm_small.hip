@@ -63,8 +63,8 @@ struct SmallOps {
 // branch / a kernel for each: 1024 x 1024 4-bit, blocks of 32, 9 vectors 5.55 / 5.32, 8 vectors 5.15 / 4.80; 4096 x 11008 3.5-bit, 9 vectors 13.4 / 12.7).
 // LINES (8-bit formats): a load of codes takes the 256 consecutive bytes that the wavefront's columns have in a row, of four rows, and its staging rows turn them.  As the operand
 // layout wants them, one load touches both lines of all sixteen rows for 16 bytes of every 64, four times over; where rows don't begin at multiples of 256
-// bytes this costs most (us, a ring of matrices, 8 vectors and fewer: 9918 x 23680 71.4 -> 60.4, 10826 x 21696 69.2 -> 57.2, 8839 x 7488 25.0 -> 22.1, 512 x 8192 7.5 -> 6.9, 28672 x 8192
-// 50.8 -> 49.9).  Up to SMALL_LINES_COLS columns, half of the sixteen wavefronts or more without any, the turn is what shows (1024 x 1024 4.7 -> 5.0, 16384 x 1088 10.4 -> 11.2,
+// bytes this costs most (us, a ring of matrices, 8 vectors: 9918 x 23680 67.6 -> 57.3, 998 x 25856 26.4 -> 22.5, 512 x 8192 7.5 -> 6.9, 11008 x 4096 14.8 -> 14.2, 28672 x 8192
+// 49.2 -> 47.3; 36 shapes 0 to 16 % faster).  Up to SMALL_LINES_COLS columns, half of the sixteen wavefronts or more without any, the turn is what shows (1024 x 1024 4.7 -> 5.0, 16384 x 1088 10.4 -> 11.2,
 // 2048 x 2048 5.4 -> 5.5; 4096 x 2752 6.2 -> 6.1): the loads stay as they were.  So do those of the other formats, which have 128 bytes and less per row (4-bit, 4096 x 4096 4.9 -> 5.2).
 constexpr int64_t SMALL_LINES_COLS = 2048;
 
